@@ -133,7 +133,9 @@ typedef struct {
   int64_t tile[3];        /* bricks per element tile along x, y, z (build constants) */
   int64_t tiles_interior; /* element tiles over the interior bricks (ragged ones included) */
   int64_t tiles_pml;      /* element tiles over the PML bricks */
-  int64_t element_threads;/* threads of an element-kernel workgroup */
+  int64_t element_threads;/* threads that hold one node of a full tile's node box each:
+                             the FP32 matrix-core workgroups; the scalar stage launch
+                             keeps a column of box nodes per thread */
   int64_t ckpt_states;    /* full states the workspace holds (checkpoint slots) */
   int64_t schedule_advances; /* segment advances of the checkpoint schedule
                              (forward sweep to its checkpoints + adjoint) */
@@ -352,9 +354,11 @@ fwi_status fwi_grid_to_nodes(fwi_plan* plan, void* stream, const float* coarse, 
  * of each kernel class is bracketed by HIP events recorded on the stream the
  * kernel is launched on; fwi_timing_read waits for those events and returns
  * the mean duration of the sampled launches.  stride = 0 disables and clears.
- * Classes: FWI_K_INTERIOR (interior bricks, forward), FWI_K_PML (PML bricks,
- * forward), FWI_K_NODAL (RK4 stage combination), FWI_K_INTERIOR_ADJ (interior
- * bricks with gradient terms), FWI_K_PML_ADJ (PML bricks, transposed). */
+ * Classes: FWI_K_INTERIOR (element operators of a stage: interior and PML
+ * bricks in one launch), FWI_K_INTERIOR_ADJ (the same, transposed, with the
+ * gradient terms), FWI_K_NODAL (RK4 stage combination).  In the matrix-core
+ * precisions the two element classes hold the interior bricks and FWI_K_PML /
+ * FWI_K_PML_ADJ the PML bricks, forward / transposed. */
 enum { FWI_K_INTERIOR = 0, FWI_K_PML = 1, FWI_K_NODAL = 2, FWI_K_INTERIOR_ADJ = 3,
        FWI_K_PML_ADJ = 4, FWI_K_NCLASS = 5 };
 fwi_status fwi_timing_enable(fwi_plan* plan, int stride);

@@ -1,10 +1,7 @@
 // HIP kernels of the hot path (CDNA4 / gfx950).
 //
-//   interior_element_kernel : interior stiffness K_RD applied to a displacement
-//                             field (first term of (3a)); optionally the
-//                             Lame-parameter gradient terms (C.1f)-(C.1g).
-//   pml_element_kernel      : PML coupling terms of (3a) (u-rows) and (3b)
-//                             (S-rows), forward or transposed.
+//   element_kernel (element.h): the element operators of a stage and the
+//                             gradient terms.
 //   nodal_rk_kernel         : nodal PML terms, M^{-1}, classical RK4 stage
 //                             combination of (6), source injection.
 //
@@ -13,14 +10,11 @@
 //   21 x n_pml [x0 u (3) | x0 S (6) | x1 S (6) | x2 S (6)] on the PML shell.
 //   Stress order (xx, yy, zz, yz, xz, xy).
 //
-// Element work is done per tile of bricks: a workgroup per (tile, source), or
-// per tile with the sources in turn where a result is summed over sources (the
-// gradient); each thread keeps one node of the tile's node box.  The PML
-// operator runs as two launches, one per row type.  Scatter without atomics:
-// a node lies on the upper face (local index 2*count) of at most one tile per
-// axis, so the set c of axes on which it is an upper-face node differs for
-// every tile containing it.  A tile
-// stores its partial sum for a box node with a plain store into partial
+// Element work is done per tile of bricks.  Scatter without atomics: a node
+// lies on the upper face (local index 2*count) of at most one tile per axis, so
+// the set c of axes on which it is an upper-face node differs for every tile
+// containing it.  A tile stores its partial sum for a box node with a plain
+// store into partial
 // array c; the nodal kernel adds the arrays c that can be non-zero for the
 // node.  Array 0 uses the register index spaces (full grid for u-rows, PML
 // shell for S-rows); arrays c != 0 use the full grid with the axes in c
@@ -33,9 +27,8 @@
 #pragma once
 #include "geometry.h"
 
-// Threads of an element-kernel workgroup: at least the tile's box nodes (one
-// node per thread; the kernels loop over the tile's LGL points in strides of
-// the workgroup size).  512 fits the 11 x 9 x 5 node box of a 5x4x2 tile.
+// Threads that hold one node each of a tile's node box: 512 fits the
+// 11 x 9 x 5 node box of a 5x4x2 tile.
 #ifndef PMLFWI_ETHREADS
 #define PMLFWI_ETHREADS 512
 #endif
@@ -194,198 +187,6 @@ __device__ __forceinline__ void atomic_add(R* p, R v) {
 }
 
 // ---------------------------------------------------------------------------
-// Interior bricks: r_u += K_RD u  (u = x1 displacement of the input register).
-// GRAD: also  g -= b_s * sum_e w|J| (div z div u_f, 2 eps(z):eps(u_f)) at the
-// LGL nodes, z = the displacement read here, u_f = stored forward stage field,
-// summed over sources and added to FP64 accumulators (gacc: [8][2][n_nodes],
-// slot c indexed like the partial arrays).
-template <typename R, int TX, int TY, int TZ, bool GRAD, bool SRCLOOP>
-__global__ void __launch_bounds__(PMLFWI_ETHREADS)
-interior_element_kernel(Geo g, const Tile* __restrict__ tiles, int ntiles, int nsrc,
-                        const R* __restrict__ Ybase, long long ystride, const R* __restrict__ lam,
-                        const R* __restrict__ mu, R* __restrict__ rbase, Part PT,
-                        const R* __restrict__ fwd, long long fstride, double gw,
-                        double* __restrict__ gacc, Part PG) {
-  constexpr int BX = 2 * TX + 1, BY = 2 * TY + 1, BZ = 2 * TZ + 1;
-  constexpr int NB = BX * BY * BZ, NP = 27 * TX * TY * TZ;
-  __shared__ R sU[3][NB];
-  __shared__ R sLam[NB], sMu[NB];
-  __shared__ R sS[6][NP];
-  __shared__ R sR[3][NP];   // brick-local rows B^T S, summed over bricks per node below
-  __shared__ R sV[GRAD ? 3 : 1][GRAD ? NB : 1];
-  __shared__ R sG[GRAD ? 2 : 1][GRAD ? NP : 1];
-  __shared__ double sGacc[GRAD ? 2 : 1][GRAD ? NB : 1];   // summed over sources
-
-  static_assert(NB <= PMLFWI_ETHREADS, "one box node per thread");
-  const int ti = xcd_tile();
-  if (ti >= ntiles) return;
-  const Tile t = tiles[ti];
-  const int cx = t.c & 255, cy = (t.c >> 8) & 255, cz = (t.c >> 16) & 255;
-  const size_t nn = (size_t)g.sn;
-  const R s2h = R(2.0 / g.h);
-  const double wh3 = 0.125 * g.h * g.h * g.h;
-
-  // this thread's box node and its constants, shared by the sources
-  const int n = threadIdx.x;
-  const int lx = n % BX, ly = (n / BX) % BY, lz = n / (BX * BY);
-  const bool live = n < NB && lx <= 2 * cx && ly <= 2 * cy && lz <= 2 * cz;
-  const int i = 2 * t.x + lx, j = 2 * t.y + ly, k = 2 * t.z + lz;
-  const size_t node = (size_t)i + (size_t)g.NX * (j + (size_t)g.NY * k);
-  const int mi = live ? interior_index(g, i, j, k) : 0;
-  const int cs = (lx == 2 * cx) | ((ly == 2 * cy) << 1) | ((lz == 2 * cz) << 2);
-  if (live) {
-    sLam[n] = lam[mi];
-    sMu[n] = mu[mi];
-    if constexpr (GRAD) {
-      sGacc[0][n] = 0.0;
-      sGacc[1][n] = 0.0;
-    }
-  }
-
-  static_assert(SRCLOOP || !GRAD, "gradient sums over sources inside the workgroup");
-  const int src0 = SRCLOOP ? 0 : (int)blockIdx.y, src1 = SRCLOOP ? nsrc : src0 + 1;
-  for (int src = src0; src < src1; ++src) {
-    const R* Yu = Ybase + (size_t)src * ystride;
-    if (live) {
-#pragma unroll
-      for (int d = 0; d < 3; ++d) sU[d][n] = Yu[u_at(nn, d, node)];
-      if constexpr (GRAD) {
-        const R* F = fwd + (size_t)src * fstride;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sV[d][n] = __builtin_nontemporal_load(&F[3 * (size_t)mi + d]);
-      }
-    }
-    __syncthreads();
-
-    for (int q = threadIdx.x; q < NP; q += blockDim.x) {
-      const int pt = q % 27, e = q / 27;
-      const int ea = e % TX, eb = (e / TX) % TY, ec = e / (TX * TY);
-      if (ea >= cx || eb >= cy || ec >= cz) continue;
-      const int qa = pt % 3, qb = (pt / 3) % 3, qc = pt / 9;
-      const int px = 2 * ea + qa, py = 2 * eb + qb, pz = 2 * ec + qc;   // box node of the point
-      const int nq = px + BX * (py + BY * pz);
-      R G[3][3], Gf[3][3];
-      const R xa = R(qa - 1), xb = R(qb - 1), xc = R(qc - 1);
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        R gx = 0, gy = 0, gz = 0, fx = 0, fy = 0, fz = 0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          const R cxa = dbasis(xa, a), cya = dbasis(xb, a), cza = dbasis(xc, a);
-          const int nx = (2 * ea + a) + BX * (py + BY * pz);
-          const int ny = px + BX * ((2 * eb + a) + BY * pz);
-          const int nz = px + BX * (py + BY * (2 * ec + a));
-          gx += cxa * sU[d][nx];
-          gy += cya * sU[d][ny];
-          gz += cza * sU[d][nz];
-          if constexpr (GRAD) {
-            fx += cxa * sV[d][nx];
-            fy += cya * sV[d][ny];
-            fz += cza * sV[d][nz];
-          }
-        }
-        G[d][0] = gx * s2h; G[d][1] = gy * s2h; G[d][2] = gz * s2h;
-        if constexpr (GRAD) { Gf[d][0] = fx * s2h; Gf[d][1] = fy * s2h; Gf[d][2] = fz * s2h; }
-      }
-      const R wq = R(wh3 * wlgl(qa) * wlgl(qb) * wlgl(qc));
-      const R la = sLam[nq], m = sMu[nq];
-      const R tr = G[0][0] + G[1][1] + G[2][2];
-      sS[0][q] = wq * (la * tr + 2 * m * G[0][0]);
-      sS[1][q] = wq * (la * tr + 2 * m * G[1][1]);
-      sS[2][q] = wq * (la * tr + 2 * m * G[2][2]);
-      sS[3][q] = wq * (m * (G[1][2] + G[2][1]));
-      sS[4][q] = wq * (m * (G[0][2] + G[2][0]));
-      sS[5][q] = wq * (m * (G[0][1] + G[1][0]));
-      if constexpr (GRAD) {
-        // per-stage products in the state precision; summed in FP64 below
-        const R du = Gf[0][0] + Gf[1][1] + Gf[2][2];
-        R ee = 2 * (G[0][0] * Gf[0][0] + G[1][1] * Gf[1][1] + G[2][2] * Gf[2][2]);
-        ee += (G[1][2] + G[2][1]) * (Gf[1][2] + Gf[2][1]);
-        ee += (G[0][2] + G[2][0]) * (Gf[0][2] + Gf[2][0]);
-        ee += (G[0][1] + G[1][0]) * (Gf[0][1] + Gf[1][0]);
-        sG[0][q] = wq * tr * du;
-        sG[1][q] = wq * ee;
-      }
-    }
-    __syncthreads();
-
-    // brick-local rows: for local node (pa, pb, pc) of brick e and component i,
-    // sum over the points on the three lines through the node of
-    // D(point, node) times the stress column of that axis (sum-factorized B^T S)
-    for (int q = threadIdx.x; q < NP; q += blockDim.x) {
-      const int pt = q % 27, e0 = q - pt;
-      const int pa = pt % 3, pb = (pt / 3) % 3, pc = pt / 9;
-      R ax1, ax0, ay1, ay0, az1, az0;
-      dbasis_coef<R>(pa, ax1, ax0);
-      dbasis_coef<R>(pb, ay1, ay0);
-      dbasis_coef<R>(pc, az1, az0);
-      R r0 = 0, r1 = 0, r2 = 0;
-#pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        // derivative of the node's basis function at point a: c1 xi_a + c0
-        const R cxa = ax0 + R(a - 1) * ax1, cya = ay0 + R(a - 1) * ay1, cza = az0 + R(a - 1) * az1;
-        const int qx = e0 + a + 3 * pb + 9 * pc;
-        const int qy = e0 + pa + 3 * a + 9 * pc;
-        const int qz = e0 + pa + 3 * pb + 9 * a;
-        r0 += cxa * sS[0][qx] + cya * sS[5][qy] + cza * sS[4][qz];
-        r1 += cxa * sS[5][qx] + cya * sS[1][qy] + cza * sS[3][qz];
-        r2 += cxa * sS[4][qx] + cya * sS[3][qy] + cza * sS[2][qz];
-      }
-      sR[0][q] = r0;
-      sR[1][q] = r1;
-      sR[2][q] = r2;
-    }
-    __syncthreads();
-
-    R* res = rbase + (size_t)src * PT.per_src;
-    if (live) {
-      int ox[2], oy[2], oz[2];
-      bool vx[2], vy[2], vz[2];
-      axis_bricks(lx, cx, 27, 1, ox, vx);
-      axis_bricks(ly, cy, 27 * TX, 3, oy, vy);
-      axis_bricks(lz, cz, 27 * TX * TY, 9, oz, vz);
-      R r0 = 0, r1 = 0, r2 = 0;
-      R gl = 0, gm = 0;
-#pragma unroll
-      for (int a3 = 0; a3 < 2; ++a3)
-#pragma unroll
-        for (int a2 = 0; a2 < 2; ++a2)
-#pragma unroll
-          for (int a1 = 0; a1 < 2; ++a1) {
-            if (!(vx[a1] && vy[a2] && vz[a3])) continue;
-            const int qn = ox[a1] + oy[a2] + oz[a3];
-            r0 += sR[0][qn];
-            r1 += sR[1][qn];
-            r2 += sR[2][qn];
-            if constexpr (GRAD) {
-              gl += sG[0][qn];
-              gm += sG[1][qn];
-            }
-          }
-      if (!is_dirichlet(g, i, j, k)) {
-        const RowAddr ra = row_addr(g, PT, cs, i, j, k, node, 0);
-        res[ra.u] = r0 * s2h;
-        res[ra.u + 1] = r1 * s2h;
-        res[ra.u + 2] = r2 * s2h;
-      }
-      if constexpr (GRAD) {
-        sGacc[0][n] += (double)gl;
-        sGacc[1][n] += (double)gm;
-      }
-    }
-    __syncthreads();
-  }
-  if constexpr (GRAD) {
-    if (live) {
-      const size_t o = (size_t)PG.off[cs] + part_node(g, PG, cs, i, j, k), gs = (size_t)PG.size[cs];
-      const double a0 = gacc[o], a1 = gacc[o + gs];
-      gacc[o] = a0 + gw * sGacc[0][n];
-      gacc[o + gs] = a1 + gw * sGacc[1][n];
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // PML bricks.  Forward (ADJ = false), for the input register (x0, x1, x2):
 //   u-rows:  r_u += int grad w~ : (S' Le + S Lp + Sbar Lw)
 //   S-rows:  r_S -= int T~ : (mu (H + H^T) + lam tr(H) I),
@@ -398,13 +199,8 @@ interior_element_kernel(Geo g, const Tile* __restrict__ tiles, int ntiles, int n
 //
 // The S-rows depend on the displacements only (through W and Q) and the
 // u-rows on the stresses only (through T), so the operator splits into two
-// independent parts (PART: PML_SROWS, PML_UROWS or both).  A workgroup works
-// in up to three phases per source: (1) every box node's register values
-// become the nodal fields W and/or T in LDS, (2) S-rows: every LGL point of
-// every brick forms Q from the gradients of W, (3) every box node sums its
-// u-rows (a stencil along each axis, T being nodal) and/or S-rows and stores
-// them.
-enum { PML_SROWS = 1, PML_UROWS = 2, PML_ALL = 3 };
+// independent parts.
+enum { PML_SROWS = 1, PML_UROWS = 2 };
 
 template <typename R>
 struct PmlNode {          // register values of one box node for one source
@@ -470,111 +266,6 @@ __device__ __forceinline__ void pml_node_t(const PmlNode<R>& v, const R Le[3], c
   }
 }
 
-// Q (6 values) at LGL point q of the tile's bricks; false for points of bricks
-// outside a ragged tile.  sLam, sMu: box-node materials (forward only).
-template <typename R, int TX, int TY, int TZ, bool ADJ>
-__device__ __forceinline__ bool pml_point_value(const Geo& g, int cx, int cy, int cz, int q,
-                                                const R* __restrict__ sW, const R* __restrict__ sLam,
-                                                const R* __restrict__ sMu, R Q[6]) {
-  constexpr int BX = 2 * TX + 1, BY = 2 * TY + 1, NB = BX * BY * (2 * TZ + 1);
-  const R s2h = R(2.0 / g.h);
-  const int pt = q % 27, e = q / 27;
-  const int ea = e % TX, eb = (e / TX) % TY, ec = e / (TX * TY);
-  if (ea >= cx || eb >= cy || ec >= cz) return false;
-  const int qa = pt % 3, qb = (pt / 3) % 3, qc = pt / 9;
-  const int lx = 2 * ea + qa, ly = 2 * eb + qb, lz = 2 * ec + qc;
-  R H[3][3];
-  const R xa = R(qa - 1), xb = R(qb - 1), xc = R(qc - 1);
-#pragma unroll
-  for (int ii = 0; ii < 3; ++ii) {
-    R hx = 0, hy = 0, hz = 0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      hx += dbasis(xa, a) * sW[(0 + ii) * NB + (2 * ea + a) + BX * (ly + BY * lz)];
-      hy += dbasis(xb, a) * sW[(3 + ii) * NB + lx + BX * ((2 * eb + a) + BY * lz)];
-      hz += dbasis(xc, a) * sW[(6 + ii) * NB + lx + BX * (ly + BY * (2 * ec + a))];
-    }
-    H[ii][0] = hx * s2h; H[ii][1] = hy * s2h; H[ii][2] = hz * s2h;
-  }
-  const R wq = R(0.125 * g.h * g.h * g.h * wlgl(qa) * wlgl(qb) * wlgl(qc));
-  if constexpr (!ADJ) {
-    const int nq = lx + BX * (ly + BY * lz);
-    const R la = sLam[nq], m = sMu[nq];
-    const R tr = H[0][0] + H[1][1] + H[2][2];
-    Q[0] = -wq * (la * tr + 2 * m * H[0][0]);
-    Q[1] = -wq * (la * tr + 2 * m * H[1][1]);
-    Q[2] = -wq * (la * tr + 2 * m * H[2][2]);
-    Q[3] = -wq * (m * (H[1][2] + H[2][1]));
-    Q[4] = -wq * (m * (H[0][2] + H[2][0]));
-    Q[5] = -wq * (m * (H[0][1] + H[1][0]));
-  } else {
-    Q[0] = wq * H[0][0];
-    Q[1] = wq * H[1][1];
-    Q[2] = wq * H[2][2];
-    Q[3] = wq * (H[1][2] + H[2][1]);
-    Q[4] = wq * (H[0][2] + H[2][0]);
-    Q[5] = wq * (H[0][1] + H[1][0]);
-  }
-  return true;
-}
-
-// Along one axis, the u-row term of local node l (0 <= l <= 2 cnt) is
-// sum_k c[k] T(l - 2 + k): over the tile's bricks containing l, the LGL weight
-// of point a times the derivative of the node's basis function at a, placed
-// at the box node of a.  Brick below (l odd: position 1, else 2) and brick
-// above (l even: position 0) give
-//   l odd:   (0, 2/3, 0, -2/3, 0)
-//   l even:  below (-1/6, 2/3, 1/2, 0, 0) + above (0, 0, -1/2, -2/3, 1/6).
-// S: the sum of the 1D weights of those bricks at l.  Indices are clamped
-// to the tile box (the clamped reads have coefficient 0).
-template <typename R>
-__device__ __forceinline__ void axis_stencil(int l, int cnt, R c[5], int o[5], R& S) {
-  const bool odd = l & 1, lo = l >= 1, hi = !odd && (l >> 1) < cnt;
-  const R third = R(1.0 / 3.0), sixth = R(1.0 / 6.0), two3 = R(2.0 / 3.0);
-  c[0] = (!odd && lo) ? -sixth : R(0);
-  c[1] = lo ? two3 : R(0);
-  c[2] = odd ? R(0) : R(lo ? 0.5 : 0.0) - R(hi ? 0.5 : 0.0);
-  c[3] = (odd || hi) ? -two3 : R(0);
-  c[4] = hi ? sixth : R(0);
-  S = odd ? R(4.0 / 3.0) : R(lo ? third : R(0)) + R(hi ? third : R(0));
-#pragma unroll
-  for (int k = 0; k < 5; ++k) o[k] = min(max(l - 2 + k, 0), 2 * cnt);
-}
-
-// Phase 3, u-rows of box node (lx, ly, lz) from the nodal T.
-template <typename R, int TX, int TY, int TZ>
-__device__ __forceinline__ void pml_u_rows(const Geo& g, int cx, int cy, int cz, int lx, int ly, int lz,
-                                           const R* __restrict__ sT, R out[3]) {
-  constexpr int BX = 2 * TX + 1, BY = 2 * TY + 1, NB = BX * BY * (2 * TZ + 1);
-  R c[5], Sx, Sy, Sz;
-  int o[5];
-  R dx[3] = {0, 0, 0}, dy[3] = {0, 0, 0}, dz[3] = {0, 0, 0};
-  axis_stencil<R>(lx, cx, c, o, Sx);
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const int n = o[k] + BX * (ly + BY * lz);
-#pragma unroll
-    for (int ii = 0; ii < 3; ++ii) dx[ii] += c[k] * sT[(3 * ii + 0) * NB + n];
-  }
-  axis_stencil<R>(ly, cy, c, o, Sy);
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const int n = lx + BX * (o[k] + BY * lz);
-#pragma unroll
-    for (int ii = 0; ii < 3; ++ii) dy[ii] += c[k] * sT[(3 * ii + 1) * NB + n];
-  }
-  axis_stencil<R>(lz, cz, c, o, Sz);
-#pragma unroll
-  for (int k = 0; k < 5; ++k) {
-    const int n = lx + BX * (ly + BY * o[k]);
-#pragma unroll
-    for (int ii = 0; ii < 3; ++ii) dz[ii] += c[k] * sT[(3 * ii + 2) * NB + n];
-  }
-  const R f = R(0.125 * g.h * g.h * g.h) * R(2.0 / g.h);
-#pragma unroll
-  for (int ii = 0; ii < 3; ++ii) out[ii] = f * (Sy * Sz * dx[ii] + Sx * Sz * dy[ii] + Sx * Sy * dz[ii]);
-}
-
 // Phase 3, S-rows of box node (lx, ly, lz): the sum of the point values of
 // every tile brick containing the node.
 template <typename R, int TX, int TY, int TZ>
@@ -617,215 +308,6 @@ __device__ __forceinline__ void pml_node_setup(const Geo& g, int gi, int gj, int
   Le[0] = ay * az; Lp[0] = ay * bz + by * az; Lw[0] = by * bz;
   Le[1] = ax * az; Lp[1] = ax * bz + bx * az; Lw[1] = bx * bz;
   Le[2] = ax * ay; Lp[2] = ax * by + bx * ay; Lw[2] = bx * by;
-}
-
-// One workgroup per (tile, source) (SRCLOOP = false) or per tile with the
-// sources in turn (SRCLOOP = true); PART selects the rows (see above).
-template <typename R, int TX, int TY, int TZ, bool ADJ, bool SRCLOOP, int PART>
-__global__ void __launch_bounds__(PMLFWI_ETHREADS)
-pml_element_kernel(Geo g, const Tile* __restrict__ tiles, int ntiles, int nsrc,
-                   const R* __restrict__ Ybase, long long ystride, const R* __restrict__ lam,
-                   const R* __restrict__ mu, R* __restrict__ rbase, Part PT) {
-  constexpr int BX = 2 * TX + 1, BY = 2 * TY + 1, BZ = 2 * TZ + 1;
-  constexpr int NB = BX * BY * BZ, NP = 27 * TX * TY * TZ;
-  constexpr bool DS = PART & PML_SROWS, DU = PART & PML_UROWS;
-  constexpr bool MATQ = DS && !ADJ;   // box-node materials in LDS for the forward Q
-  static_assert(NB <= PMLFWI_ETHREADS, "one box node per thread");
-  __shared__ R sW[DS ? 9 : 1][DS ? NB : 1];   // [3k + i]: Le_kk u'_i + Lp_kk u_i + Lw_kk ubar_i
-  __shared__ R sQ[DS ? 6 : 1][DS ? NP : 1];
-  __shared__ R sT[DU ? 9 : 1][DU ? NB : 1];   // [3i + k]: nodal stress-like tensor of the u-rows
-  __shared__ R sLam[MATQ ? NB : 1], sMu[MATQ ? NB : 1];
-
-  const int ti = xcd_tile();
-  if (ti >= ntiles) return;
-  const Tile t = tiles[ti];
-  const int cx = t.c & 255, cy = (t.c >> 8) & 255, cz = (t.c >> 16) & 255;
-  const size_t nn = (size_t)g.sn, np = (size_t)g.sp;
-
-  // this thread's box node and its constants, shared by the sources
-  const int n = threadIdx.x;
-  const int lx = n % BX, ly = (n / BX) % BY, lz = n / (BX * BY);
-  const bool live = n < NB && lx <= 2 * cx && ly <= 2 * cy && lz <= 2 * cz;
-  const int gi = 2 * t.x + lx, gj = 2 * t.y + ly, gk = 2 * t.z + lz;
-  R Le[3] = {0, 0, 0}, Lp[3] = {0, 0, 0}, Lw[3] = {0, 0, 0}, la = 0, m = 0;
-  bool hist = false, free_u = false;
-  size_t gnode = 0, gp = 0;
-  RowAddr ra{};
-  if (live) {
-    pml_node_setup<R>(g, gi, gj, gk, Le, Lp, Lw, hist, gnode, gp);
-    const int cs = (lx == 2 * cx) | ((ly == 2 * cy) << 1) | ((lz == 2 * cz) << 2);
-    ra = row_addr(g, PT, cs, gi, gj, gk, gnode, gp);
-    free_u = !is_dirichlet(g, gi, gj, gk);
-    if constexpr (MATQ || (DU && ADJ)) {
-      const int mi = material_index(g, gi, gj, gk);
-      la = lam[mi];
-      m = mu[mi];
-      if constexpr (MATQ) {
-        sLam[n] = la;
-        sMu[n] = m;
-      }
-    }
-  }
-
-  const int src0 = SRCLOOP ? 0 : (int)blockIdx.y, src1 = SRCLOOP ? nsrc : src0 + 1;
-  for (int src = src0; src < src1; ++src) {
-    const R* Y = Ybase + (size_t)src * ystride;
-    if (live) {
-      PmlNode<R> v;
-      pml_load_node<R, DS, DU>(Y, nn, np, gnode, gp, hist, v);
-      if constexpr (DS) pml_node_w<R, NB>(v, Le, Lp, Lw, n, sW);
-      if constexpr (DU) pml_node_t<R, ADJ, NB>(v, Le, Lp, Lw, la, m, n, sT);
-    }
-    __syncthreads();
-    if constexpr (DS) {
-      for (int q = threadIdx.x; q < NP; q += blockDim.x) {
-        R Q[6];
-        if (!pml_point_value<R, TX, TY, TZ, ADJ>(g, cx, cy, cz, q, &sW[0][0], &sLam[0], &sMu[0], Q)) continue;
-#pragma unroll
-        for (int v = 0; v < 6; ++v) sQ[v][q] = Q[v];
-      }
-      __syncthreads();
-    }
-    R* res = rbase + (size_t)src * PT.per_src;
-    if (live) {
-      if constexpr (DS) {
-        R q6[6];
-        pml_s_rows<R, TX, TY, TZ>(cx, cy, cz, lx, ly, lz, &sQ[0][0], q6);
-#pragma unroll
-        for (int v = 0; v < 6; ++v) res[ra.s + v] = q6[v];
-      }
-      if constexpr (DU) {
-        if (free_u) {
-          R u3[3];
-          pml_u_rows<R, TX, TY, TZ>(g, cx, cy, cz, lx, ly, lz, &sT[0][0], u3);
-#pragma unroll
-          for (int ii = 0; ii < 3; ++ii) res[ra.u + ii] = u3[ii];
-        }
-      }
-    }
-    if constexpr (SRCLOOP) __syncthreads();
-  }
-}
-
-// Gradient terms of the PML S-rows under the material extension (the chain
-// rule through the interface values a PML node takes, used when the full
-// gradient is asked for).  The S-row of a PML node j in brick e carries
-// -w_q [mu_j (H + H^T) + lam_j tr(H) I], H_ik = sum_L L_kk d_k u^L_i at the
-// node's point, u^L the forward stage's (u', u, ubar) for L = (Le, Lp, Lw).
-// With z the adjoint stress at j (x1 S part of the adjoint stage register),
-// the gradient gains gw * (-w_q) (tr(H) sum_a z_aa, sum_v z_v (H_ab + H_ba))
-// at node j, summed over sources and the node's PML bricks, into the FP64
-// accumulators indexed like the partial arrays (gacc: full grid, 2 rows).
-// fwd: stored forward PML displacements of the stage, per source
-// [x1 u (3) | x2 u (3) | x0 u (3)] x sp on the PML shell.
-template <typename R, int TX, int TY, int TZ>
-__global__ void __launch_bounds__(PMLFWI_ETHREADS)
-pml_gradient_kernel(Geo g, const Tile* __restrict__ tiles, int ntiles, int nsrc, const R* __restrict__ Ybase,
-                    long long ystride, const R* __restrict__ fwd, long long fstride, double gw,
-                    double* __restrict__ gacc, Part PG) {
-  constexpr int BX = 2 * TX + 1, BY = 2 * TY + 1, BZ = 2 * TZ + 1;
-  constexpr int NB = BX * BY * BZ, NP = 27 * TX * TY * TZ;
-  static_assert(NB <= PMLFWI_ETHREADS, "one box node per thread");
-  __shared__ R sW[9][NB];
-  __shared__ R sZ[6][NB];
-  __shared__ R sG[2][NP];
-  __shared__ double sGacc[2][NB];
-
-  const int ti = xcd_tile();
-  if (ti >= ntiles) return;
-  const Tile t = tiles[ti];
-  const int cx = t.c & 255, cy = (t.c >> 8) & 255, cz = (t.c >> 16) & 255;
-  const size_t np = (size_t)g.sp, nn = (size_t)g.sn;
-  const R s2h = R(2.0 / g.h);
-
-  const int n = threadIdx.x;
-  const int lx = n % BX, ly = (n / BX) % BY, lz = n / (BX * BY);
-  const bool live = n < NB && lx <= 2 * cx && ly <= 2 * cy && lz <= 2 * cz;
-  const int gi = 2 * t.x + lx, gj = 2 * t.y + ly, gk = 2 * t.z + lz;
-  R Le[3] = {0, 0, 0}, Lp[3] = {0, 0, 0}, Lw[3] = {0, 0, 0};
-  bool hist = false, free_u = false;
-  size_t gnode = 0, gp = 0;
-  if (live) {
-    pml_node_setup<R>(g, gi, gj, gk, Le, Lp, Lw, hist, gnode, gp);
-    free_u = !is_dirichlet(g, gi, gj, gk);
-    sGacc[0][n] = 0.0;
-    sGacc[1][n] = 0.0;
-  }
-  for (int src = 0; src < nsrc; ++src) {
-    if (live) {
-      const R* F = fwd + (size_t)src * fstride;
-      const R* P = Ybase + (size_t)src * ystride + 6 * nn;
-      PmlNode<R> v;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        v.u1[d] = free_u ? F[d * np + gp] : R(0);
-        v.u2[d] = free_u ? F[(3 + d) * np + gp] : R(0);
-        v.u0[d] = (free_u && hist) ? F[(6 + d) * np + gp] : R(0);
-      }
-      pml_node_w<R, NB>(v, Le, Lp, Lw, n, sW);
-#pragma unroll
-      for (int c = 0; c < 6; ++c) sZ[c][n] = P[p_at(np, P_X1S + c, gp)];
-    }
-    __syncthreads();
-    for (int q = threadIdx.x; q < NP; q += blockDim.x) {
-      const int pt = q % 27, e = q / 27;
-      const int ea = e % TX, eb = (e / TX) % TY, ec = e / (TX * TY);
-      if (ea >= cx || eb >= cy || ec >= cz) continue;
-      const int qa = pt % 3, qb = (pt / 3) % 3, qc = pt / 9;
-      const int px = 2 * ea + qa, py = 2 * eb + qb, pz = 2 * ec + qc;
-      const int nq = px + BX * (py + BY * pz);
-      R H[3][3];
-      const R xa = R(qa - 1), xb = R(qb - 1), xc = R(qc - 1);
-#pragma unroll
-      for (int ii = 0; ii < 3; ++ii) {
-        R hx = 0, hy = 0, hz = 0;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-          hx += dbasis(xa, a) * sW[0 + ii][(2 * ea + a) + BX * (py + BY * pz)];
-          hy += dbasis(xb, a) * sW[3 + ii][px + BX * ((2 * eb + a) + BY * pz)];
-          hz += dbasis(xc, a) * sW[6 + ii][px + BX * (py + BY * (2 * ec + a))];
-        }
-        H[ii][0] = hx * s2h; H[ii][1] = hy * s2h; H[ii][2] = hz * s2h;
-      }
-      const R wq = R(0.125 * g.h * g.h * g.h * wlgl(qa) * wlgl(qb) * wlgl(qc));
-      const R z0 = sZ[0][nq], z1 = sZ[1][nq], z2 = sZ[2][nq], z3 = sZ[3][nq], z4 = sZ[4][nq], z5 = sZ[5][nq];
-      const R tr = H[0][0] + H[1][1] + H[2][2];
-      R em = 2 * (z0 * H[0][0] + z1 * H[1][1] + z2 * H[2][2]);
-      em += z3 * (H[1][2] + H[2][1]) + z4 * (H[0][2] + H[2][0]) + z5 * (H[0][1] + H[1][0]);
-      sG[0][q] = -wq * tr * (z0 + z1 + z2);
-      sG[1][q] = -wq * em;
-    }
-    __syncthreads();
-    if (live) {
-      int ox[2], oy[2], oz[2];
-      bool vx[2], vy[2], vz[2];
-      axis_bricks(lx, cx, 27, 1, ox, vx);
-      axis_bricks(ly, cy, 27 * TX, 3, oy, vy);
-      axis_bricks(lz, cz, 27 * TX * TY, 9, oz, vz);
-      R gl = 0, gm = 0;
-#pragma unroll
-      for (int a3 = 0; a3 < 2; ++a3)
-#pragma unroll
-        for (int a2 = 0; a2 < 2; ++a2)
-#pragma unroll
-          for (int a1 = 0; a1 < 2; ++a1) {
-            if (!(vx[a1] && vy[a2] && vz[a3])) continue;
-            const int qn = ox[a1] + oy[a2] + oz[a3];
-            gl += sG[0][qn];
-            gm += sG[1][qn];
-          }
-      sGacc[0][n] += (double)gl;
-      sGacc[1][n] += (double)gm;
-    }
-    __syncthreads();
-  }
-  if (live) {
-    const int cs = (lx == 2 * cx) | ((ly == 2 * cy) << 1) | ((lz == 2 * cz) << 2);
-    const size_t o = (size_t)PG.off[cs] + part_node(g, PG, cs, gi, gj, gk), gs = (size_t)PG.size[cs];
-    const double a0 = gacc[o], a1 = gacc[o + gs];
-    gacc[o] = a0 + gw * sGacc[0][n];
-    gacc[o + gs] = a1 + gw * sGacc[1][n];
-  }
 }
 
 // Nodal part of one RK4 stage.  With r the element residual of the stage input

@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "element.h"
 #include "regularize.h"
 #include "mfma.h"
 #include "convnet.h"
@@ -177,13 +178,10 @@ struct fwi_plan {
   long long launches[FWI_K_NCLASS] = {};
   std::vector<std::pair<hipEvent_t, hipEvent_t>> ev[FWI_K_NCLASS];
   size_t ev_used[FWI_K_NCLASS] = {};
-  // second stream for the interior bricks, which run beside the PML bricks
-  // (fork and join through events on the caller's stream)
+  // second stream for the interior bricks beside the PML bricks in the
+  // matrix-core precisions (fork and join through events on the caller's stream)
   hipStream_t side = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
-  // third stream: the second PML part beside the first (PMLFWI_CONCURRENT 2)
-  hipStream_t side2 = nullptr;
-  hipEvent_t join2_ev = nullptr;
   // largest eigenvalues of M^{-1} K for the unit reference brick with lam = 1,
   // mu = 0 and lam = 0, mu = 1 (stability bound of fwi_check_model)
   double c_lam = 0.0, c_mu = 0.0;
@@ -224,43 +222,17 @@ struct TimedLaunch {
 
 namespace {
 
-// Element tiles (bricks per axis; 5x4x2 measured fastest on the 5-brick PML
-// and 40x40x20-brick interior workload among 4x2x2 .. 10x1x1 at 256-640
-// threads) and whether a workgroup walks all sources of its tile (true) or one
-// source per workgroup (false).
+// Element tiles (bricks per axis).  5x4x2 cuts the 5-brick PML and the
+// 40x40x20-brick interior without ragged tiles along x and y.
 #ifndef PMLFWI_TX
 #define PMLFWI_TX 5
 #define PMLFWI_TY 4
 #define PMLFWI_TZ 2
 #endif
-// PML operator as two launches, one per row type (smaller LDS and register
-// footprints, 8 waves per SIMD; they interleave with the interior launch on
-// the other stream), rather than one launch for both.  Forward stages launch
-// the S-rows first, transposed stages the u-rows first: in each order the PML
-// pair and the interior launch beside it end closest together.
-#ifndef PMLFWI_PML_SPLIT
-#define PMLFWI_PML_SPLIT 1
-#endif
-// Nodal launch: 0 one grid, 1 one grid with the (heavier) PML-row blocks
-// dispatched first, 2 node rows and PML rows as two launches.
-#ifndef PMLFWI_NODAL_ORDER
-#define PMLFWI_NODAL_ORDER 1
-#endif
-#ifndef PMLFWI_SPLIT_FIRST_FWD
-#define PMLFWI_SPLIT_FIRST_FWD PML_SROWS
-#endif
-#ifndef PMLFWI_SPLIT_FIRST_ADJ
-#define PMLFWI_SPLIT_FIRST_ADJ PML_UROWS
-#endif
-#ifndef PMLFWI_CONCURRENT
-#define PMLFWI_CONCURRENT 1
-#endif
-#ifndef PMLFWI_SRCLOOP
-#define PMLFWI_SRCLOOP false
-#endif
 constexpr int TX = PMLFWI_TX, TY = PMLFWI_TY, TZ = PMLFWI_TZ;
-constexpr bool SRCLOOP = PMLFWI_SRCLOOP;
-constexpr int ETHREADS = PMLFWI_ETHREADS;   // threads per element workgroup
+// Threads that hold one box node each (the FP32 matrix-core workgroups); the
+// scalar element launch keeps a column of box nodes per thread (TileDims).
+constexpr int ETHREADS = PMLFWI_ETHREADS;
 
 fwi_status fail(fwi_plan* p, fwi_status s, const std::string& msg) {
   if (p) p->err = msg;
@@ -1000,9 +972,6 @@ struct Run {
     return false;
   }
 
-  // The interior and PML bricks write disjoint partial-array entries, so the
-  // two launches may run at the same time: the interior one goes to the plan's
-  // second stream when both lists are non-empty.
   // PML rows on the matrix cores for the FP32-state precisions that ask for it
   // (one source per workgroup, one row type per launch); false when the scalar
   // kernel is to be used.
@@ -1011,10 +980,7 @@ struct Run {
     if constexpr (std::is_same<R, float>::value) {
       const int pr = p->prob.precision;
       if (pr != FWI_FP32_MFMA && pr != FWI_FP32_BF16X3) return false;
-      if constexpr (PART == PML_ALL) {
-        mfma_pml<PML_UROWS>(adj, gx, nt, Y, reg, sp);
-        mfma_pml<PML_SROWS>(adj, gx, nt, Y, reg, sp);
-      } else {
+      {
         const dim3 grid(gx, p->nsrc);
         const Tile* T = p->d_tiles_pml;
         if (pr == FWI_FP32_MFMA) {
@@ -1040,74 +1006,67 @@ struct Run {
     return false;
   }
 
-  template <int PART>
-  void launch_pml(bool adj, dim3 grid, int nt, const R* Y, long long reg, hipStream_t sp) {
-    if (mfma_pml<PART>(adj, grid.x, nt, Y, reg, sp)) return;
-    if (adj)
-      pml_element_kernel<R, TX, TY, TZ, true, SRCLOOP, PART><<<grid, ETHREADS, 0, sp>>>(
-          g(), p->d_tiles_pml, nt, p->nsrc, Y, reg, lam(), mu(), res(), L.part);
-    else
-      pml_element_kernel<R, TX, TY, TZ, false, SRCLOOP, PART><<<grid, ETHREADS, 0, sp>>>(
-          g(), p->d_tiles_pml, nt, p->nsrc, Y, reg, lam(), mu(), res(), L.part);
-  }
-
+  // The element operators of one stage for the register Y (see element.h): one
+  // launch; with fwd the gradient terms too (interior_only: only those, if
+  // asked for).  The matrix-core precisions take their own kernels for what those
+  // cover (the interior without gradient terms, the PML rows), the interior
+  // on the plan's second stream beside the PML rows.
   fwi_status elements(bool adj, const R* Y, const R* fwd, double gw, bool interior_only = false,
                       const R* pfwd = nullptr) {
     const Geo& G = g();
-    const long long reg = (long long)L.reg_elems;
-    const int ns = p->nsrc;
+    const bool mfma = p->prob.precision == FWI_FP32_MFMA || p->prob.precision == FWI_FP32_BF16X3;
+    auto pad8 = [](size_t n) { return 8 * (int)((n + 7) / 8); };
+    ElementArgs<R> A{};
+    A.tiles_int = p->d_tiles_int; A.tiles_pml = p->d_tiles_pml;
+    A.nint = (int)p->tiles_int.size(); A.npml = (int)p->tiles_pml.size(); A.nsrc = p->nsrc;
+    A.Y = Y; A.ystride = (long long)L.reg_elems;
+    A.lam = lam(); A.mu = mu(); A.res = res(); A.PT = L.part;
+    A.fwd = fwd; A.fstride = 3LL * G.si; A.pfwd = pfwd; A.pfstride = 9LL * G.sp;
+    A.gw = gw; A.gacc = gacc(); A.PG = L.gpart;
+    A.gint = interior_only && fwd ? 0 : pad8(A.nint);
+    A.gpml = interior_only ? 0 : pad8(A.npml);
+    A.ggint = fwd ? pad8(A.nint) : 0;
+    // the S-row terms of the full gradient; their gacc slots differ from the
+    // interior launch's, so the two need no order
+    if (fwd && pfwd && A.gpml)
+      pml_gradient_kernel<R, TX, TY, TZ><<<(unsigned)A.gpml, TileDims<TX, TY, TZ>::THREADS, 0, st>>>(G, A);
+    if (!mfma) {
+      TimedLaunch tl(p, fwd ? FWI_K_INTERIOR_ADJ : FWI_K_INTERIOR, st);
+      launch_elements(adj, fwd != nullptr, A, st);
+      HIP_TRY(p, hipGetLastError());
+      return FWI_OK;
+    }
+    const bool fork = A.gpml > 0;
     hipStream_t si = st;
-    const bool pml = !interior_only && !p->tiles_pml.empty();
-    const bool fork = PMLFWI_CONCURRENT && !p->tiles_int.empty() && pml;
-    const bool fork2 = fork && PMLFWI_CONCURRENT == 2 && PMLFWI_PML_SPLIT;
     if (fork) {
       HIP_TRY(p, hipEventRecord(p->fork_ev, st));
       HIP_TRY(p, hipStreamWaitEvent(p->side, p->fork_ev, 0));
-      if (fork2) HIP_TRY(p, hipStreamWaitEvent(p->side2, p->fork_ev, 0));
       si = p->side;
     }
-    if (!p->tiles_int.empty()) {
-      const int nt = (int)p->tiles_int.size();
-      const unsigned gx = 8u * (unsigned)((nt + 7) / 8);
+    {
       TimedLaunch tl(p, fwd ? FWI_K_INTERIOR_ADJ : FWI_K_INTERIOR, si);
-      if (fwd)
-        interior_element_kernel<R, TX, TY, TZ, true, true><<<dim3(gx, 1), ETHREADS, 0, si>>>(
-            G, p->d_tiles_int, nt, ns, Y, reg, lam(), mu(), res(), L.part, fwd, 3LL * G.si, gw, gacc(), L.gpart);
-      else if (!mfma_interior(Y, nt, gx, si))
-        interior_element_kernel<R, TX, TY, TZ, false, SRCLOOP><<<dim3(gx, SRCLOOP ? 1 : ns), ETHREADS, 0, si>>>(
-            G, p->d_tiles_int, nt, ns, Y, reg, lam(), mu(), res(), L.part, nullptr, 0, 0.0, nullptr, L.gpart);
+      const int gpml = A.gpml;
+      A.gpml = 0;
+      if (fwd || !mfma_interior(Y, A.nint, (unsigned)A.gint, si)) launch_elements(adj, fwd != nullptr, A, si);
+      A.gpml = gpml;
     }
-    if (fork) HIP_TRY(p, hipEventRecord(p->join_ev, si));
-    if (pml) {
-      const int nt = (int)p->tiles_pml.size();
-      const dim3 grid(8u * (unsigned)((nt + 7) / 8), SRCLOOP ? 1 : ns);
+    if (fork) {
+      HIP_TRY(p, hipEventRecord(p->join_ev, si));
       TimedLaunch tl(p, adj ? FWI_K_PML_ADJ : FWI_K_PML, st);
-      if (PMLFWI_PML_SPLIT) {
-        // the two row types write disjoint rows: with three streams the
-        // second part runs beside the first and the interior bricks
-        if (adj) {
-          launch_pml<PMLFWI_SPLIT_FIRST_ADJ>(adj, grid, nt, Y, reg, st);
-          launch_pml<PML_ALL ^ PMLFWI_SPLIT_FIRST_ADJ>(adj, grid, nt, Y, reg, fork2 ? p->side2 : st);
-        } else {
-          launch_pml<PMLFWI_SPLIT_FIRST_FWD>(adj, grid, nt, Y, reg, st);
-          launch_pml<PML_ALL ^ PMLFWI_SPLIT_FIRST_FWD>(adj, grid, nt, Y, reg, fork2 ? p->side2 : st);
-        }
-        if (fork2) HIP_TRY(p, hipEventRecord(p->join2_ev, p->side2));
-      } else {
-        launch_pml<PML_ALL>(adj, grid, nt, Y, reg, st);
-      }
+      mfma_pml<PML_SROWS>(adj, (unsigned)A.gpml, A.npml, Y, A.ystride, st);
+      mfma_pml<PML_UROWS>(adj, (unsigned)A.gpml, A.npml, Y, A.ystride, st);
+      HIP_TRY(p, hipStreamWaitEvent(st, p->join_ev, 0));
     }
-    if (pml && pfwd) {
-      // S-row terms of the gradient under the material extension; gacc slots
-      // differ from the interior launch's, so the two may overlap
-      const int nt = (int)p->tiles_pml.size();
-      pml_gradient_kernel<R, TX, TY, TZ><<<8u * (unsigned)((nt + 7) / 8), ETHREADS, 0, st>>>(
-          G, p->d_tiles_pml, nt, ns, Y, reg, pfwd, (long long)(9LL * G.sp), gw, gacc(), L.gpart);
-    }
-    if (fork) HIP_TRY(p, hipStreamWaitEvent(st, p->join_ev, 0));
-    if (fork2) HIP_TRY(p, hipStreamWaitEvent(st, p->join2_ev, 0));
     HIP_TRY(p, hipGetLastError());
     return FWI_OK;
+  }
+
+  void launch_elements(bool adj, bool grad, const ElementArgs<R>& A, hipStream_t s) {
+    const unsigned nb = (unsigned)(A.ggint + (A.gint + 2 * A.gpml) * A.nsrc);
+    constexpr int th = TileDims<TX, TY, TZ>::THREADS;
+    if (grad) element_kernel<R, TX, TY, TZ, true, true><<<nb, th, 0, s>>>(g(), A);
+    else if (adj) element_kernel<R, TX, TY, TZ, true, false><<<nb, th, 0, s>>>(g(), A);
+    else element_kernel<R, TX, TY, TZ, false, false><<<nb, th, 0, s>>>(g(), A);
   }
 
   fwi_status nodal(int s, R* Yin, R* Yout, R* Xn, R* acc, const double* wav, int step, R* store,
@@ -1141,20 +1100,12 @@ struct Run {
           {nodal_rk_kernel<R, 2, 0>, nodal_rk_kernel<R, 2, 1>, nodal_rk_kernel<R, 2, 2>}};
       const K kern = table[A.mode][sm];
       constexpr int NT = PMLFWI_NODAL_THREADS;
-      if (PMLFWI_NODAL_ORDER == 2) {
-        A.first = 0;
-        A.last = G.sn;
-        kern<<<dim3(blocks((size_t)G.sn, NT), p->nsrc), NT, 0, st>>>(G, A);
-        A.first = G.sn;
-        A.last = rows;
-        kern<<<dim3(blocks((size_t)G.n_pml, NT), p->nsrc), NT, 0, st>>>(G, A);
-      } else {
-        const unsigned nb = (unsigned)blocks((size_t)rows, NT);
-        A.first = 0;
-        A.last = rows;
-        A.rot = PMLFWI_NODAL_ORDER == 1 ? (unsigned)(G.sn / NT) % nb : 0u;
-        kern<<<dim3(nb, p->nsrc), NT, 0, st>>>(G, A);
-      }
+      // the (heavier) PML-row blocks are dispatched first
+      const unsigned nb = (unsigned)blocks((size_t)rows, NT);
+      A.first = 0;
+      A.last = rows;
+      A.rot = (unsigned)(G.sn / NT) % nb;
+      kern<<<dim3(nb, p->nsrc), NT, 0, st>>>(G, A);
     }
     if (wav && p->nload > 0) {
       load_kernel<R><<<blocks(p->nload, 128), 128, 0, st>>>(
@@ -1609,10 +1560,6 @@ fwi_status fwi_plan_create(const fwi_problem* prob, const int32_t* src_node, con
   }
   if (e == hipSuccess) e = hipEventCreateWithFlags(&p->fork_ev, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&p->join_ev, hipEventDisableTiming);
-  if (e == hipSuccess && PMLFWI_CONCURRENT == 2) {
-    e = hipStreamCreateWithFlags(&p->side2, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&p->join2_ev, hipEventDisableTiming);
-  }
   if (e == hipSuccess) {
     what = "pinned model-check result";
     e = hipHostMalloc((void**)&p->h_info, 8 * sizeof(double), hipHostMallocDefault);
@@ -1761,9 +1708,6 @@ fwi_status fwi_plan_destroy(fwi_plan* p) {
   if (p->fork_ev) (void)hipEventDestroy(p->fork_ev);
   if (p->join_ev) (void)hipEventDestroy(p->join_ev);
   if (p->side) (void)hipStreamDestroy(p->side);
-  if (p->side2) (void)hipStreamSynchronize(p->side2);
-  if (p->join2_ev) (void)hipEventDestroy(p->join2_ev);
-  if (p->side2) (void)hipStreamDestroy(p->side2);
   (void)hipFree(p->d_tiles_int);
   (void)hipFree(p->d_tiles_pml);
   (void)hipFree(p->d_src);
