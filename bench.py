@@ -142,12 +142,28 @@ def pass_bytes_per_dof_step(sizes, prob, nsrc, es, n_hist):
     return (nsrc * per_src + shared) / (sizes.n_state * nsrc)
 
 
+def nodal_launch_bytes(sizes, prob, nsrc, es):
+    """HBM bytes of the library's nodal launch, averaged over the 4 stages: every
+    stage keeps its own register, so per step an x1 row is read and written 8
+    times (stages 1-3: Xn read, output written; stage 4: Xn read and written;
+    its rates are the x2 rows), an x2 row 13 times (2, 3, 3 and 5) and, on
+    history nodes, an x0 row and the x1 rows its terms need 16 times; plus the
+    residual, the kept stage displacement and 1/M."""
+    nn, npml = sizes.n_nodes, sizes.n_pml_nodes
+    nfree = (sizes.n_state - 6 * npml) // 3
+    rows = 3.0 * nfree + 6.0 * npml
+    per_src = rows * (8 + 13) / 4 + 9.0 * history_nodes(prob) * 16 / 4 + rows + 3.0 * sizes.n_int_nodes
+    return es * nsrc * per_src + es * nn
+
+
 def algorithmic_bytes(cls, sizes, prob, nsrc, es):
     """Compulsory HBM bytes of one launch of a kernel class (all sources).
 
-    nodal: per free node, stage input (6) + residual (3) + register traffic of
-    the stage mode; per PML node, stage input stresses (12, +9 on history
-    nodes) + residual (6) + register traffic; averaged over the 4 RK4 modes.
+    nodal: three-register classical RK4 (see pass_bytes_per_dof_step): per free
+    node, stage input (6) + residual (3) + register traffic of the stage mode;
+    per PML node, stage input stresses (12, +9 on history nodes) + residual (6)
+    + register traffic; averaged over the 4 RK4 modes.  The library's launch
+    moves less (nodal_launch_bytes).
     element kernels: stage input read once, residual rows written once,
     materials once per launch.
     """
@@ -268,6 +284,8 @@ def main():
     def launch_bytes(k):
         """One launch of class k; a stage's interior and PML bricks are one launch
         unless the PML classes have launches of their own."""
+        if k == "nodal":
+            return nodal_launch_bytes(S.sizes, prob, wl.nsrc, es)
         b = algorithmic_bytes(k, S.sizes, prob, wl.nsrc, es)
         pml = k.replace("interior", "pml")
         return b + algorithmic_bytes(pml, S.sizes, prob, wl.nsrc, es) if k != pml and pml not in kstats else b

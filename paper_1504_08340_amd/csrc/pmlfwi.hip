@@ -524,10 +524,10 @@ __global__ void impulse_kernel(R* __restrict__ Y, long long reg, int sn, const R
 // z = (y0, -y1, y2) the scheme is classical RK4 on the transposed operator
 // plus the rate -M^{-1} R^T r(t) in the x2 rows, r(t) = a_hi r_hi + a_lo r_lo
 // at the stage time; the stage combination the nodal kernel just applied gets
-// that rate's share: mode 0/1: Yout += cY g, acc += cA g; mode 2: Xn += cA g.
+// that rate's share: stages 1-3: Yout += cY g (and Xn's through Yout), stage 4:
+// Xn += cY g (cY = dt/6).  D: the register the stage produced.
 template <typename R>
-__global__ void appb_force_kernel(R* __restrict__ Yout, R* __restrict__ Xn, R* __restrict__ acc, long long reg,
-                                  int sn, int mode, double cA, double cY, const R* __restrict__ invMu,
+__global__ void appb_force_kernel(R* __restrict__ D, long long reg, int sn, double cY, const R* __restrict__ invMu,
                                   const int* __restrict__ rec, int nrec, const double* __restrict__ resid,
                                   int n_hi, int n_lo, double a_hi, double a_lo, int nsteps) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x, src = blockIdx.y;
@@ -539,13 +539,7 @@ __global__ void appb_force_kernel(R* __restrict__ Yout, R* __restrict__ Xn, R* _
   const double im = (double)invMu[node];
   for (int d = 0; d < 3; ++d) {
     const double gval = -im * (a_hi * Eh[d] + a_lo * El[d]);
-    const size_t o = off + u_at(sn, 3 + d, node);
-    if (mode == 2) {
-      atomic_add(&Xn[o], R(cA * gval));
-    } else {
-      atomic_add(&Yout[o], R(cY * gval));
-      atomic_add(&acc[o], R(cA * gval));
-    }
+    atomic_add(&D[off + u_at(sn, 3 + d, node)], R(cY * gval));
   }
 }
 
@@ -555,14 +549,12 @@ __global__ void appb_force_kernel(R* __restrict__ Yout, R* __restrict__ Xn, R* _
 constexpr int MISFIT_BLOCKS = 2048;
 
 // General nodal loads after a nodal stage pass: the stage rate of x2 at the
-// load's node gains M^{-1} f, f = vec * wavelet(stage time); the stage
-// combination the nodal kernel applied gets that rate's share (mode 0/1:
-// Yout += cY g, acc += cA g; mode 2: Xn += cA g).  Entries are unique per
-// (source, node), so plain read-modify-writes do not race.
+// load's node gains M^{-1} f, f = vec * wavelet(stage time); the register D that
+// the pass produced gets that rate's share cY g (cY = dt/6 in stage 4).  Entries
+// are unique per (source, node), so plain read-modify-writes do not race.
 template <typename R>
-__global__ void load_kernel(R* __restrict__ Yout, R* __restrict__ Xn, R* __restrict__ acc, long long reg, int sn,
-                            int mode, double cA, double cY, const R* __restrict__ invMu, int nload,
-                            const int* __restrict__ lsrc, const int* __restrict__ lnode,
+__global__ void load_kernel(R* __restrict__ D, long long reg, int sn, double cY, const R* __restrict__ invMu,
+                            int nload, const int* __restrict__ lsrc, const int* __restrict__ lnode,
                             const double* __restrict__ lvec, const double* __restrict__ wav, int wav_len,
                             int wav_idx) {
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -571,16 +563,7 @@ __global__ void load_kernel(R* __restrict__ Yout, R* __restrict__ Xn, R* __restr
   const double f = wav[(size_t)src * wav_len + wav_idx];
   const double im = (double)invMu[node];
   const size_t off = (size_t)src * reg;
-  for (int d = 0; d < 3; ++d) {
-    const double g = im * lvec[3 * e + d] * f;
-    const size_t o = off + u_at(sn, 3 + d, node);
-    if (mode == 2) {
-      Xn[o] += R(cA * g);
-    } else {
-      Yout[o] += R(cY * g);
-      acc[o] += R(cA * g);
-    }
-  }
+  for (int d = 0; d < 3; ++d) D[off + u_at(sn, 3 + d, node)] += R(cY * (im * lvec[3 * e + d] * f));
 }
 
 __global__ void __launch_bounds__(256) misfit_kernel(const double* __restrict__ tr, const double* __restrict__ obs,
@@ -1069,20 +1052,26 @@ struct Run {
     else element_kernel<R, TX, TY, TZ, false, false><<<nb, th, 0, s>>>(g(), A);
   }
 
-  fwi_status nodal(int s, R* Yin, R* Yout, R* Xn, R* acc, const double* wav, int step, R* store,
-                   R* pstore_ = nullptr) {
-    static const double cA[4] = {1.0 / 6, 1.0 / 3, 1.0 / 3, 1.0 / 6};
-    static const double cY[4] = {0.5, 0.5, 1.0, 0.0};
+  // Weight of a stage's rate in the register it produces.
+  double stage_weight(int s) const {
+    static const double c[4] = {0.5, 0.5, 1.0, 1.0 / 6};
+    return c[s] * p->prob.dt;
+  }
+
+  // Nodal part of stage s (0..3) of the step in the registers r0 .. r0 + 3
+  // (Xn and the inputs of stages 2, 3, 4).
+  fwi_status nodal(int s, int r0, const double* wav, int step, R* store, R* pstore_ = nullptr) {
     static const int toff[4] = {0, 1, 1, 2};
-    if (s == 0 && Yin != Xn) return fail(p, FWI_ERR_STATE, "internal: the first RK4 stage must start from Xn");
     const Geo& G = g();
-    const double dt = p->prob.dt;
     NodalArgs<R> A{};
-    A.Yin = Yin; A.Yout = Yout; A.Xn = Xn; A.acc = acc; A.res = res(); A.invMu = invm();
+    R* const D = s < 3 ? reg(r0 + s + 1) : reg(r0);
+    A.Yin = reg(r0 + s); A.Yout = s < 3 ? D : nullptr; A.Xn = reg(r0);
+    A.Y2 = reg(r0 + 1); A.Y3 = reg(r0 + 2);
+    A.res = res(); A.invMu = invm();
     A.part = L.part;
     A.reg = (long long)L.reg_elems;
-    A.cA = R(cA[s] * dt); A.cY = R(cY[s] * dt);
-    A.mode = s == 0 ? 0 : (s == 3 ? 2 : 1);
+    A.cY = R(stage_weight(s));
+    const int mode = s == 0 ? 0 : (s == 3 ? 2 : 1);
     if (wav && p->nload == 0) {
       A.src_node = p->d_src; A.src_dir = p->d_dir; A.wav = wav;
       A.wav_len = 2 * p->prob.nsteps + 1; A.wav_idx = 2 * step + toff[s];
@@ -1098,7 +1087,7 @@ struct Run {
           {nodal_rk_kernel<R, 0, 0>, nodal_rk_kernel<R, 0, 1>, nodal_rk_kernel<R, 0, 2>},
           {nodal_rk_kernel<R, 1, 0>, nodal_rk_kernel<R, 1, 1>, nodal_rk_kernel<R, 1, 2>},
           {nodal_rk_kernel<R, 2, 0>, nodal_rk_kernel<R, 2, 1>, nodal_rk_kernel<R, 2, 2>}};
-      const K kern = table[A.mode][sm];
+      const K kern = table[mode][sm];
       constexpr int NT = PMLFWI_NODAL_THREADS;
       // the (heavier) PML-row blocks are dispatched first
       const unsigned nb = (unsigned)blocks((size_t)rows, NT);
@@ -1109,29 +1098,23 @@ struct Run {
     }
     if (wav && p->nload > 0) {
       load_kernel<R><<<blocks(p->nload, 128), 128, 0, st>>>(
-          Yout, Xn, acc, (long long)L.reg_elems, G.sn, A.mode, cA[s] * dt, cY[s] * dt, invm(), p->nload,
-          p->d_load_src, p->d_load_node, p->d_load_vec, wav, 2 * p->prob.nsteps + 1, 2 * step + toff[s]);
+          D, (long long)L.reg_elems, G.sn, stage_weight(s), invm(), p->nload, p->d_load_src, p->d_load_node,
+          p->d_load_vec, wav, 2 * p->prob.nsteps + 1, 2 * step + toff[s]);
     }
     HIP_TRY(p, hipGetLastError());
     return FWI_OK;
   }
 
-  // One RK4 step on (Xn, Ya, Yb, acc); `store_nl` >= 0 writes the stage
+  // One RK4 step on the registers r0 .. r0 + 3; `store_nl` >= 0 writes the stage
   // displacements of this step to store slot store_nl (and the next step's
   // first stage to store_nl+1 when store_next).
   fwi_status step(bool adj, int r0, int n, const double* wav, int store_nl, bool store_next,
                   int fwd_nl) {
     static const double bw[4] = {1.0 / 6, 1.0 / 3, 1.0 / 3, 1.0 / 6};
-    R* Xn = reg(r0);
-    R* Ya = reg(r0 + 1);
-    R* Yb = reg(r0 + 2);
-    R* acc = reg(r0 + 3);
-    R* in = Xn;
-    R* outs[4] = {Ya, Yb, Ya, nullptr};
     for (int s = 0; s < 4; ++s) {
       const R* fwd = fwd_nl >= 0 ? store(fwd_nl, 3 - s) : nullptr;
       const R* pfwd = fwd_nl >= 0 ? pstore(fwd_nl, 3 - s) : nullptr;
-      fwi_status e = elements(adj, in, fwd, -bw[s] * p->prob.dt, false, pfwd);
+      fwi_status e = elements(adj, reg(r0 + s), fwd, -bw[s] * p->prob.dt, false, pfwd);
       if (e != FWI_OK) return e;
       R* st_ = nullptr;
       R* pst_ = nullptr;
@@ -1144,9 +1127,7 @@ struct Run {
           pst_ = pstore(store_nl + 1, 0);
         }
       }
-      e = nodal(s, in, outs[s], Xn, acc, wav, n, st_, pst_);
-      if (e != FWI_OK) return e;
-      in = outs[s];
+      if ((e = nodal(s, r0, wav, n, st_, pst_)) != FWI_OK) return e;
     }
     return FWI_OK;
   }
@@ -1279,8 +1260,6 @@ struct Run {
   // g += dt w_n z1^T (dK_RD/dm) u^n.
   fwi_status adjoint_appb(const double* rho, const double* lam_, const double* mu_, const double* wav,
                           const double* resid, double* gl, double* gm) {
-    static const double cA[4] = {1.0 / 6, 1.0 / 3, 1.0 / 3, 1.0 / 6};
-    static const double cY[4] = {0.5, 0.5, 1.0, 0.0};
     const fwi_problem& P = p->prob;
     const Geo& G = g();
     const double dt = P.dt;
@@ -1293,24 +1272,19 @@ struct Run {
     auto reverse = [&](int a, int b) -> fwi_status {
       fwi_status e2 = FWI_OK;
       for (int n = b - 1; n >= a; --n) {
-        R* Xn = reg(ra);
-        R* outs[4] = {reg(ra + 1), reg(ra + 2), reg(ra + 1), nullptr};
-        R* in = Xn;
         for (int s = 0; s < 4; ++s) {
-          if ((e2 = elements(true, in, nullptr, 0.0)) != FWI_OK) return e2;
-          if ((e2 = nodal(s, in, outs[s], Xn, reg(ra + 3), nullptr, n, nullptr)) != FWI_OK) return e2;
+          if ((e2 = elements(true, reg(ra + s), nullptr, 0.0)) != FWI_OK) return e2;
+          if ((e2 = nodal(s, ra, nullptr, n, nullptr)) != FWI_OK) return e2;
           if (p->nrec > 0) {
-            const int mode = s == 0 ? 0 : (s == 3 ? 2 : 1);
             const double ah = s == 0 ? 1.0 : (s == 3 ? 0.0 : 0.5), al = 1.0 - ah;
             appb_force_kernel<R><<<dim3(blocks(p->nrec, 128), P.nsrc), 128, 0, st>>>(
-                outs[s], Xn, reg(ra + 3), (long long)L.reg_elems, G.sn, mode, cA[s] * dt, cY[s] * dt, invm(),
-                p->d_rec, p->nrec, resid, n + 1, n, ah, al, P.nsteps);
+                s < 3 ? reg(ra + s + 1) : reg(ra), (long long)L.reg_elems, G.sn, stage_weight(s), invm(), p->d_rec,
+                p->nrec, resid, n + 1, n, ah, al, P.nsteps);
             HIP_TRY(p, hipGetLastError());
           }
-          in = outs[s];
         }
         const double w = (n == 0 || n == P.nsteps) ? 0.5 : 1.0;
-        if ((e2 = elements(true, Xn, store(n - a, 0), dt * w, true)) != FWI_OK) return e2;
+        if ((e2 = elements(true, reg(ra), store(n - a, 0), dt * w, true)) != FWI_OK) return e2;
       }
       return e2;
     };
