@@ -287,7 +287,7 @@ fwi_status fwi_check_model(fwi_plan* plan, void* stream, const double* rho,
                            const double* lam, const double* mu, double* info);
 
 /* out[0] = sum_i a_i b_i w_i (w null: weights 1), device vectors of length n;
- * one workgroup, fixed summation order (deterministic).  Used for the norms
+ * a fixed summation order that depends on n alone (deterministic).  Used for the norms
  * of (24) and the inner products of the line search (Algorithm 1). */
 fwi_status fwi_dot(void* stream, int64_t n, const double* a, const double* b,
                    const double* w, double* out);

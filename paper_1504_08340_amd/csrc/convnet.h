@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include "mfma.h"
+#include "reduce.h"
 
 namespace pmlfwi {
 
@@ -225,25 +226,25 @@ __global__ void __launch_bounds__(256) conv3d_backward_bias_kernel(ConvShape c, 
   if (threadIdx.x == 0) db[co] = part[0];
 }
 
-// L = 1/(2n) sum (y - t)^2 over n entries; grad = (y - t)/n; one workgroup.
-__global__ void __launch_bounds__(1024) mse_kernel(long long n, const float* __restrict__ y,
-                                                   const float* __restrict__ t, float* __restrict__ loss,
-                                                   float* __restrict__ grad) {
-  __shared__ float part[1024];
-  float acc = 0.0f;
+// L = 1/(2n) sum (y - t)^2 over n entries; grad = (y - t)/n (parts and slot as
+// in reduce.h).
+__global__ void __launch_bounds__(RED_THREADS) mse_kernel(long long n, const float* __restrict__ y,
+                                                          const float* __restrict__ t, float* __restrict__ loss,
+                                                          float* __restrict__ grad, int nb, int slot) {
+  __shared__ double sh[RED_THREADS];
   const float inv = 1.0f / (float)n;
-  for (long long i = threadIdx.x; i < n; i += blockDim.x) {
-    const float r = y[i] - t[i];
-    acc += r * r;
-    if (grad) grad[i] = r * inv;
-  }
-  part[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0 && loss) loss[0] = 0.5f * part[0] * inv;
+  const long long step = (long long)nb * RED_THREADS;
+  double s;
+  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, s, [&](int part) {
+        double acc = 0.0;
+        for (long long i = (long long)part * RED_THREADS + threadIdx.x; i < n; i += step) {
+          const float r = y[i] - t[i];
+          acc += (double)r * (double)r;
+          if (grad) grad[i] = r * inv;
+        }
+        return acc;
+      }) && threadIdx.x == 0 && loss)
+    loss[0] = (float)(0.5 * s / (double)n);
 }
 
 // Adam (Kingma and Ba, 2015) with bias correction; step t counts from 1.

@@ -688,38 +688,18 @@ __global__ void gradient_reduce_kernel(Geo g, const double* __restrict__ gacc, P
   g_mu[mi] = b;
 }
 
-// out = [min rho, min mu, min (3 lam + 2 mu), max vp, max over interior bricks of
-// (max(lam, 0) c_lam + max mu c_mu) / min rho] (nodal values of each brick):
-// one workgroup, fixed order.
-__global__ void __launch_bounds__(1024) model_check_kernel(Geo g, const double* __restrict__ rho,
-                                                           const double* __restrict__ lam,
-                                                           const double* __restrict__ mu, double c_lam,
-                                                           double c_mu, double* __restrict__ out) {
-  __shared__ double red[5][1024];
-  double mr = 1e300, mm = 1e300, mk = 1e300, vp = 0.0, wb = 0.0;
-  for (int j = threadIdx.x; j < g.n_int; j += blockDim.x) {
-    mr = fmin(mr, rho[j]);
-    mm = fmin(mm, mu[j]);
-    mk = fmin(mk, 3.0 * lam[j] + 2.0 * mu[j]);
-    if (rho[j] > 0.0 && lam[j] + 2.0 * mu[j] > 0.0) vp = fmax(vp, sqrt((lam[j] + 2.0 * mu[j]) / rho[j]));
-  }
-  const long long nb = (long long)g.ex * g.ey * g.ez;
-  for (long long e = threadIdx.x; e < nb; e += blockDim.x) {
-    const int ex = (int)(e % g.ex), ey = (int)((e / g.ex) % g.ey), ez = (int)(e / ((long long)g.ex * g.ey));
-    double lmax = 0.0, mmax = 0.0, rmin = 1e300;
-    for (int c = 0; c < 27; ++c) {
-      const int j = (2 * ex + c % 3) + g.NIX * ((2 * ey + (c / 3) % 3) + g.NIY * (2 * ez + c / 9));
-      lmax = fmax(lmax, lam[j]);
-      mmax = fmax(mmax, mu[j]);
-      rmin = fmin(rmin, rho[j]);
-    }
-    if (rmin > 0.0) wb = fmax(wb, (lmax * c_lam + mmax * c_mu) / rmin);
-  }
-  red[0][threadIdx.x] = mr;
-  red[1][threadIdx.x] = mm;
-  red[2][threadIdx.x] = mk;
-  red[3][threadIdx.x] = vp;
-  red[4][threadIdx.x] = wb;
+// Per workgroup [min rho, min mu, min (3 lam + 2 mu), max vp, max over interior
+// bricks of (max(lam, 0) c_lam + max mu c_mu) / min rho] (nodal values of each
+// brick), then one workgroup joins them into out (minima and maxima: any order
+// gives the same bits).  In one workgroup the check took 0.4 ms of every solve
+// at 138,000 material nodes; over CHECK_BLOCKS workgroups both launches take
+// about 15 us.
+constexpr int CHECK_BLOCKS = 256;
+static_assert(5 * CHECK_BLOCKS <= MISFIT_BLOCKS, "the partials fit the plan's buffer");
+
+__device__ __forceinline__ void check_tree(double v[5], double* __restrict__ out) {
+  __shared__ double red[5][256];
+  for (int k = 0; k < 5; ++k) red[k][threadIdx.x] = v[k];
   __syncthreads();
   for (int s = blockDim.x / 2; s > 0; s >>= 1) {
     if ((int)threadIdx.x < s) {
@@ -730,6 +710,44 @@ __global__ void __launch_bounds__(1024) model_check_kernel(Geo g, const double* 
   }
   if (threadIdx.x == 0)
     for (int k = 0; k < 5; ++k) out[k] = red[k][0];
+}
+
+__global__ void __launch_bounds__(256) model_check_kernel(Geo g, const double* __restrict__ rho,
+                                                          const double* __restrict__ lam,
+                                                          const double* __restrict__ mu, double c_lam,
+                                                          double c_mu, double* __restrict__ partials) {
+  double v[5] = {1e300, 1e300, 1e300, 0.0, 0.0};
+  const int first = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+  for (int j = first; j < g.n_int; j += step) {
+    v[0] = fmin(v[0], rho[j]);
+    v[1] = fmin(v[1], mu[j]);
+    v[2] = fmin(v[2], 3.0 * lam[j] + 2.0 * mu[j]);
+    if (rho[j] > 0.0 && lam[j] + 2.0 * mu[j] > 0.0) v[3] = fmax(v[3], sqrt((lam[j] + 2.0 * mu[j]) / rho[j]));
+  }
+  const int nb = g.ex * g.ey * g.ez;
+  for (int e = first; e < nb; e += step) {
+    const int ex = e % g.ex, ey = (e / g.ex) % g.ey, ez = e / (g.ex * g.ey);
+    double lmax = 0.0, mmax = 0.0, rmin = 1e300;
+#pragma unroll
+    for (int c = 0; c < 27; ++c) {
+      const int j = (2 * ex + c % 3) + g.NIX * ((2 * ey + (c / 3) % 3) + g.NIY * (2 * ez + c / 9));
+      lmax = fmax(lmax, lam[j]);
+      mmax = fmax(mmax, mu[j]);
+      rmin = fmin(rmin, rho[j]);
+    }
+    if (rmin > 0.0) v[4] = fmax(v[4], (lmax * c_lam + mmax * c_mu) / rmin);
+  }
+  check_tree(v, partials + 5 * blockIdx.x);
+}
+
+__global__ void __launch_bounds__(256) model_check_final_kernel(const double* __restrict__ partials, int nb,
+                                                                double* __restrict__ out) {
+  double v[5] = {1e300, 1e300, 1e300, 0.0, 0.0};
+  for (int b = threadIdx.x; b < nb; b += blockDim.x) {
+    for (int k = 0; k < 3; ++k) v[k] = fmin(v[k], partials[5 * b + k]);
+    for (int k = 3; k < 5; ++k) v[k] = fmax(v[k], partials[5 * b + k]);
+  }
+  check_tree(v, out);
 }
 
 // Power iteration for the largest eigenvalue of M_RD^{-1} K_RD, the interior
@@ -1355,7 +1373,9 @@ fwi_status dispatch(fwi_plan* p, hipStream_t st, void* ws, F&& f, bool keep = tr
 
 fwi_status check_model(fwi_plan* p, hipStream_t st, const double* rho, const double* lam, const double* mu,
                        double* info, const char* who, void* ws = nullptr, bool keep = true) {
-  model_check_kernel<<<1, 1024, 0, st>>>(p->g, rho, lam, mu, p->c_lam, p->c_mu, p->d_info);
+  const int nb = std::min((int)blocks(p->g.n_int, 256), CHECK_BLOCKS);
+  model_check_kernel<<<nb, 256, 0, st>>>(p->g, rho, lam, mu, p->c_lam, p->c_mu, nb == 1 ? p->d_info : p->d_partials);
+  if (nb > 1) model_check_final_kernel<<<1, 256, 0, st>>>(p->d_partials, nb, p->d_info);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(p->h_info, p->d_info, 5 * sizeof(double), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -1435,6 +1455,35 @@ hipError_t scratch_address(int device, void** out) {
   }
   *out = g_scratch_addr[device];
   return hipSuccess;
+}
+}  // namespace
+
+// ------------------------------------------------ reduction slots (reduce.h)
+namespace {
+// Slot of a stream's many-workgroup reductions, or -1 (the reduction then runs
+// in one workgroup, with the same bits): for a stream being captured, whose
+// graph may later run beside its own eager launches; for the per-thread default
+// stream, one handle for many streams; and once RED_SLOTS streams hold one.  A
+// slot stays with its stream's handle; on every device the same index names
+// that device's own array, so the null stream needs one entry.
+int stream_slot(hipStream_t st) {
+  static std::mutex mu;
+  static hipStream_t held[RED_SLOTS];
+  static int n = 0;
+  if (st == hipStreamPerThread) return -1;
+  if (st == hipStreamLegacy) st = nullptr;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return -1;
+  }
+  if (cs != hipStreamCaptureStatusNone) return -1;
+  std::lock_guard<std::mutex> lk(mu);
+  for (int i = 0; i < n; ++i)
+    if (held[i] == st) return i;
+  if (n == RED_SLOTS) return -1;
+  held[n] = st;
+  return n++;
 }
 }  // namespace
 
@@ -1821,7 +1870,10 @@ fwi_status fwi_regularization(fwi_plan* p, void* stream, int kind, double eps, c
   const Geo& G = p->g;
   const int k = kind == FWI_REG_TIKHONOV ? REG_TN : REG_TV;
   if (grad) reg_gradient_kernel<<<blocks(G.n_int, 256), 256, 0, st>>>(G, k, eps, field, grad);
-  if (value) reg_value_kernel<<<1, 1024, 0, st>>>(G, k, eps, field, value);
+  if (value) {
+    const int nb = red_parts(27LL * G.ex * G.ey * G.ez), slot = nb > 1 ? stream_slot(st) : -1;
+    reg_value_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>(G, k, eps, field, value, nb, slot);
+  }
   HIP_TRY(p, hipGetLastError());
   return FWI_OK;
 }
@@ -1852,7 +1904,9 @@ fwi_status fwi_check_model(fwi_plan* p, void* stream, const double* rho, const d
 
 fwi_status fwi_dot(void* stream, int64_t n, const double* a, const double* b, const double* w, double* out) {
   if (n < 0 || !out || (n > 0 && (!a || !b))) return FWI_ERR_ARG;
-  dot_kernel<<<1, 1024, 0, (hipStream_t)stream>>>((long long)n, a, b, w, out);
+  hipStream_t st = (hipStream_t)stream;
+  const int nb = red_parts(n), slot = nb > 1 ? stream_slot(st) : -1;
+  dot_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>((long long)n, a, b, w, out, nb, slot);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
@@ -1867,7 +1921,9 @@ fwi_status fwi_axpby(void* stream, int64_t n, double alpha, const double* x, dou
 
 fwi_status fwi_absmax(void* stream, int64_t n, const double* x, double* out) {
   if (n < 0 || !out || (n > 0 && !x)) return FWI_ERR_ARG;
-  absmax_kernel<<<1, 1024, 0, (hipStream_t)stream>>>((long long)n, x, out);
+  hipStream_t st = (hipStream_t)stream;
+  const int nb = red_parts(n), slot = nb > 1 ? stream_slot(st) : -1;
+  absmax_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>((long long)n, x, out, nb, slot);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
@@ -1924,7 +1980,9 @@ fwi_status fwi_conv3d_backward(void* stream, const fwi_conv_shape* shape, const 
 
 fwi_status fwi_mse(void* stream, int64_t n, const float* y, const float* t, float* loss, float* grad) {
   if (n < 1 || !y || !t || (!loss && !grad)) return FWI_ERR_ARG;
-  mse_kernel<<<1, 1024, 0, (hipStream_t)stream>>>((long long)n, y, t, loss, grad);
+  hipStream_t st = (hipStream_t)stream;
+  const int nb = red_parts(n), slot = nb > 1 ? stream_slot(st) : -1;
+  mse_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>((long long)n, y, t, loss, grad, nb, slot);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 

@@ -11,6 +11,7 @@
 // carries R rather than R/2 so that its derivative is the TV form of (17).
 #pragma once
 #include "geometry.h"
+#include "reduce.h"
 
 namespace pmlfwi {
 
@@ -111,31 +112,29 @@ __global__ void __launch_bounds__(256) reg_gradient_kernel(Geo g, int kind, doub
   grad[j] = acc;
 }
 
-// value[0] = R(f): one workgroup, fixed summation order (deterministic).
-__global__ void __launch_bounds__(1024) reg_value_kernel(Geo g, int kind, double eps,
-                                                         const double* __restrict__ f,
-                                                         double* __restrict__ value) {
-  __shared__ double part[1024];
-  const long long npts = 27LL * g.ex * g.ey * g.ez;
+// value[0] = R(f) (parts and slot as in reduce.h: deterministic).
+__global__ void __launch_bounds__(RED_THREADS) reg_value_kernel(Geo g, int kind, double eps,
+                                                                const double* __restrict__ f,
+                                                                double* __restrict__ value, int nb, int slot) {
+  __shared__ double sh[RED_THREADS];
+  const long long npts = 27LL * g.ex * g.ey * g.ez, step = (long long)nb * RED_THREADS;
   const double vol = 0.125 * g.h * g.h * g.h;
-  double acc = 0.0;
-  for (long long t = threadIdx.x; t < npts; t += blockDim.x) {
-    const int q = (int)(t % 27);
-    const long long e = t / 27;
-    const int ex = (int)(e % g.ex), ey = (int)((e / g.ex) % g.ey), ez = (int)(e / ((long long)g.ex * g.ey));
-    const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
-    double G[3], val, coef;
-    point_grad(g, f, 2 * ex, 2 * ey, 2 * ez, qx, qy, qz, G);
-    point_terms(kind, eps, G, vol * wlgl64(qx) * wlgl64(qy) * wlgl64(qz), &val, &coef);
-    acc += val;
-  }
-  part[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) value[0] = part[0];
+  double r;
+  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, r, [&](int part) {
+        double acc = 0.0;
+        for (long long t = (long long)part * RED_THREADS + threadIdx.x; t < npts; t += step) {
+          const int q = (int)(t % 27);
+          const long long e = t / 27;
+          const int ex = (int)(e % g.ex), ey = (int)((e / g.ex) % g.ey), ez = (int)(e / ((long long)g.ex * g.ey));
+          const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
+          double G[3], val, coef;
+          point_grad(g, f, 2 * ex, 2 * ey, 2 * ez, qx, qy, qz, G);
+          point_terms(kind, eps, G, vol * wlgl64(qx) * wlgl64(qy) * wlgl64(qz), &val, &coef);
+          acc += val;
+        }
+        return acc;
+      }) && threadIdx.x == 0)
+    value[0] = r;
 }
 
 // M~ diagonal (C.1a): interior lumped mass of every closed-interior node.
@@ -160,22 +159,6 @@ __global__ void gradient_finalize_kernel(Geo g, const double* __restrict__ gmis,
   out[j] = v / mrd;
 }
 
-// out[0] = sum_i a_i b_i (w_i): one workgroup, fixed order.
-__global__ void __launch_bounds__(1024) dot_kernel(long long n, const double* __restrict__ a,
-                                                   const double* __restrict__ b, const double* __restrict__ w,
-                                                   double* __restrict__ out) {
-  __shared__ double part[1024];
-  double acc = 0.0;
-  for (long long i = threadIdx.x; i < n; i += blockDim.x) acc += a[i] * b[i] * (w ? w[i] : 1.0);
-  part[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) part[threadIdx.x] += part[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = part[0];
-}
-
 // out = alpha x + beta y (y may be null when beta = 0; out may alias x or y):
 // the vector updates of the optimizer (L-BFGS two-loop recursion, the model
 // update (19), the biased direction (25), y = g1 - g).  FP64, elementwise.
@@ -183,21 +166,6 @@ __global__ void axpby_kernel(long long n, double alpha, const double* x, double 
                              double* out) {
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
     out[i] = beta == 0.0 ? alpha * x[i] : alpha * x[i] + beta * y[i];
-}
-
-// out[0] = max_i |x_i| (one workgroup; max is exact, so any order gives the same bits).
-__global__ void __launch_bounds__(1024) absmax_kernel(long long n, const double* __restrict__ x,
-                                                      double* __restrict__ out) {
-  __shared__ double part[1024];
-  double m = 0.0;
-  for (long long i = threadIdx.x; i < n; i += blockDim.x) m = fmax(m, fabs(x[i]));
-  part[threadIdx.x] = m;
-  __syncthreads();
-  for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) part[threadIdx.x] = fmax(part[threadIdx.x], part[threadIdx.x + s]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = part[0];
 }
 
 }  // namespace pmlfwi
