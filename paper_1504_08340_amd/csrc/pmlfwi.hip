@@ -1935,12 +1935,32 @@ static bool conv_shape(const fwi_conv_shape* s, ConvShape& c) {
   return c.Do >= 1 && c.Ho >= 1 && c.Wo >= 1;
 }
 
+}  // extern "C"
+
+// Forward (DATA = false) or data gradient of a convolution: 32 rows a wave where
+// that still gives every one of the 1024 SIMDs a wave, 16 (half the chain of
+// products per wave, twice the gathers in all) otherwise.
+template <bool DATA>
+static void launch_conv(const ConvShape& c, const float* src, const float* act, const float* w, const float* b,
+                        int relu, float* out, hipStream_t st) {
+  const long long P = DATA ? (long long)c.D * c.H * c.W : (long long)c.Do * c.Ho * c.Wo;
+  const int M = DATA ? c.Ci : c.Co, ptiles = (int)((P + 63) / 64);
+  const long long tiles = (long long)ptiles * c.N;
+  const int big = M > 16 && tiles * ((M + 31) / 32) >= 1024, R = big ? 32 : 16;
+  const dim3 grid((unsigned)((tiles + 3) / 4), (unsigned)((M + R - 1) / R));
+  using CK = void (*)(ConvShape, const float*, const float*, const float*, const float*, int, int, float*);
+  static const CK table[2][2] = {{conv3d_f32_kernel<1, DATA, 16>, conv3d_f32_kernel<1, DATA, 32>},
+                                 {conv3d_f32_kernel<3, DATA, 16>, conv3d_f32_kernel<3, DATA, 32>}};
+  table[c.K == 3][big]<<<grid, CONV_THREADS, 0, st>>>(c, src, act, w, b, relu, ptiles, out);
+}
+
+extern "C" {
+
 fwi_status fwi_conv3d_forward(void* stream, const fwi_conv_shape* shape, const float* x, const float* w,
                               const float* b, int relu, float* y) {
   ConvShape c;
   if (!conv_shape(shape, c) || !x || !w || !y) return FWI_ERR_ARG;
-  const long long n = (long long)c.N * c.Co * c.Do * c.Ho * c.Wo;
-  conv3d_forward_kernel<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(c, x, w, b, relu, y);
+  launch_conv<false>(c, x, nullptr, w, b, relu, y, (hipStream_t)stream);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
@@ -1958,9 +1978,10 @@ fwi_status fwi_conv3d_forward_bf16(void* stream, const fwi_conv_shape* shape, co
   if (!conv_shape(shape, c) || !x || !w || !y) return FWI_ERR_ARG;
   const long long P = (long long)c.Do * c.Ho * c.Wo;
   if (c.N > 65535) return FWI_ERR_ARG;
-  const dim3 grid((unsigned)((P + 63) / 64), (unsigned)c.N);
-  conv3d_bf16_mfma_kernel<<<grid, CONV_MFMA_THREADS, 0, (hipStream_t)stream>>>(
-      c, (const unsigned short*)x, (const unsigned short*)w, b, relu, out_fp32, y);
+  const dim3 grid((unsigned)((P + 31) / 32), (unsigned)c.N, (unsigned)((c.Co + 31) / 32));
+  (c.K == 3 ? conv3d_bf16_mfma_kernel<3> : conv3d_bf16_mfma_kernel<1>)<<<grid, CONV_THREADS, 0, (hipStream_t)stream>>>(
+      c, (const unsigned short*)x, (const unsigned short*)w, b, relu, out_fp32,
+      c.Ci % 8 == 0 && ((uintptr_t)w & 15) == 0, y);   // rows of weights start on 16 bytes
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
@@ -1969,12 +1990,28 @@ fwi_status fwi_conv3d_backward(void* stream, const fwi_conv_shape* shape, const 
   ConvShape c;
   if (!conv_shape(shape, c) || !x || !w || !dy || (relu && !y) || !dw) return FWI_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
-  if (dx) {
-    const long long n = (long long)c.N * c.Ci * c.D * c.H * c.W;
-    conv3d_backward_data_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(c, dy, y, relu, w, dx);
-  }
-  conv3d_backward_weight_kernel<<<(unsigned)(c.Co * c.Ci * c.K * c.K * c.K), 256, 0, st>>>(c, dy, y, relu, x, dw);
-  if (db) conv3d_backward_bias_kernel<<<(unsigned)c.Co, 256, 0, st>>>(c, dy, y, relu, db);
+  if (dx) launch_conv<true>(c, dy, y, w, nullptr, relu, dx, st);
+  // vector loads: four neighbouring outputs lie in one row and on 16 bytes, and
+  // so do their places in x at w stride 1 or 2
+  auto on16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
+  const bool vec = c.Wo % 4 == 0 && c.sw <= 2 && c.W == c.Wo * c.sw && on16(dy) && (!relu || on16(y)) && on16(x);
+  const int sw = vec ? c.sw : 0;
+  const int pchunks = (int)(((long long)c.Do * c.Ho * c.Wo + 15) / 16);
+  const long long ntiles = (long long)c.K * c.K * ((c.Co + 15) / 16) * ((c.Ci + 15) / 16);
+  // shares of the outputs per tile: about four workgroups a CU, at least 64
+  // chunks of 16 outputs each, and no more than a slot holds
+  const long long want = std::min({(1024 + ntiles - 1) / ntiles, (long long)c.N * pchunks / 64,
+                                   (long long)WGRAD_ENTRIES / ntiles});
+  const int nsplit = ntiles > WGRAD_TILES || want < 1 ? 1 : (int)want;
+  const int held = nsplit > 1 ? stream_slot(st) : -1, slot = held < WGRAD_SLOTS ? held : -1;
+  const unsigned nb = (unsigned)(ntiles * (slot < 0 ? 1 : nsplit));
+  using WK = void (*)(ConvShape, const float*, const float*, int, const float*, float*, float*, FastDiv, FastDiv, int,
+                      int, int, int);
+  static const WK table[2][3] = {
+      {conv3d_wgrad_kernel<1, 0>, conv3d_wgrad_kernel<1, 1>, conv3d_wgrad_kernel<1, 2>},
+      {conv3d_wgrad_kernel<3, 0>, conv3d_wgrad_kernel<3, 1>, conv3d_wgrad_kernel<3, 2>}};
+  table[c.K == 3][sw]<<<nb, WGRAD_THREADS, 0, st>>>(c, dy, y, relu, x, dw, db, fast_div((unsigned)c.Wo),
+                                                    fast_div((unsigned)c.Ho), pchunks, (int)ntiles, nsplit, slot);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
