@@ -3,7 +3,8 @@
 // the Lame-gradient terms (C.1f)-(C.1g), as ONE launch.
 //
 // A workgroup takes one part of one tile of bricks (and one source; the
-// gradient part takes the tile's sources in turn, whose terms it sums):
+// gradient part takes a group of the tile's sources in turn, whose terms it
+// sums):
 //   gradient   products of the adjoint's and the stored forward's strains
 //   interior   K_RD u
 //   S-rows     from the displacements
@@ -29,9 +30,9 @@
 //    the plane exchanges one value per point and component along z through LDS.
 // Measured (62,500 bricks, 4 sources, mean per stage): three launches of a
 // thread per point 117 us (FP32, forward) and 135 us (with gradient), this
-// launch 66 us and 90 us; FP64 138 us and 201 us.  One launch instead of three
+// launch 61 us and 81 us; FP64 133 us and 181 us.  One launch instead of three
 // on two streams also halves a small problem's pass: at 864 bricks a stage
-// waited 45 us for the host and the streams' events, now 19 us.
+// waited 45 us for the host and the streams' events, now 17 us.
 #pragma once
 #include "kernels.h"
 
@@ -55,22 +56,24 @@ struct ElementArgs {
   const Tile* tiles_int;
   const Tile* tiles_pml;
   int nint, npml, nsrc;   // tiles and sources
-  // workgroups per part and source (the gradient part: in all): its tiles
-  // rounded up to a multiple of 8, or 0 for a part that is not asked for
-  int gint, gpml, ggint;
+  // workgroups per part and source (the gradient part: per group of sources):
+  // its tiles rounded up to a multiple of 8, or 0 for a part that is not asked
+  // for; the gradient's groups (group q: sources q, q + ggrp, ..)
+  int gint, gpml, ggint, ggrp;
   const R* Y;
   long long ystride;
   const R* lam;
   const R* mu;
   R* res;
   Part PT;
-  // gradient (GRAD): stored forward stage, its weight, FP64 accumulators
+  // gradient (GRAD): stored forward stage, its weight, FP64 accumulators of
+  // every group
   const R* fwd;
   long long fstride;
   const R* pfwd;
   long long pfstride;
   double gw;
-  double* gacc;
+  double* gacc;           // [ggrp][PG.per_src]
   Part PG;
 };
 
@@ -435,17 +438,31 @@ __device__ __forceinline__ void pml_u_part(const Geo& g, const ElementArgs<R>& A
   }
 }
 
-// Adds a tile's gradient terms to the accumulators (column sums gl, gm).
+// Adds a tile's gradient terms to the accumulators (column sums gl, gm).  All
+// loads of the column stand before its first store: node by node, where the
+// compiler has to keep their order, the ten round trips to memory took longer
+// than the rest of a tile of one source.
 template <int BZ>
 __device__ __forceinline__ void add_gradient(const Geo& g, const Part& PG, const Column& c, int cz, double gw,
                                              const double (&gl)[BZ], const double (&gm)[BZ], double* gacc) {
+  const int ct = c.cxy | 4;
+  double* low = gacc + PG.off[c.cxy] + part_node(g, PG, c.cxy, c.gi, c.gj, c.gk0);
+  double* top = gacc + PG.off[ct] + part_node(g, PG, ct, c.gi, c.gj, c.gk0 + 2 * cz);
+  const size_t d = (size_t)PG.nx[c.cxy] * PG.ny[c.cxy];
+  const long long slow = PG.size[c.cxy], stop_ = PG.size[ct];
+  double vl[BZ], vm[BZ];
+#pragma unroll
+  for (int l = 0; l < BZ; ++l) {
+    const double* p = l >= 2 * cz ? top : low + (size_t)l * d;   // above the top: its value again
+    vl[l] = p[0];
+    vm[l] = p[l >= 2 * cz ? stop_ : slow];
+  }
 #pragma unroll
   for (int l = 0; l < BZ; ++l) {
     if (l > 2 * cz) break;
-    const int cs = c.cxy | (l == 2 * cz ? 4 : 0);
-    const size_t o = (size_t)PG.off[cs] + part_node(g, PG, cs, c.gi, c.gj, c.gk0 + l), gs = (size_t)PG.size[cs];
-    gacc[o] += gw * gl[l];
-    gacc[o + gs] += gw * gm[l];
+    double* p = l == 2 * cz ? top : low + (size_t)l * d;
+    p[0] = vl[l] + gw * gl[l];
+    p[l == 2 * cz ? stop_ : slow] = vm[l] + gw * gm[l];
   }
 }
 
@@ -518,6 +535,27 @@ __device__ __forceinline__ void point_strain(const R* x0, const R (&u)[3][3][3],
     const R* x = x0 + d * D::NB + a + D::BX * b;
     gx[d] = line_diff<R>(a, u[d][b][0], u[d][b][1], u[d][b][2]);
     gy[d] = line_diff<R>(b, u[d][0][a], u[d][1][a], u[d][2][a]);
+    gz[d] = dbasis(xc, 0) * x[0] + dbasis(xc, 1) * x[D::NC] + dbasis(xc, 2) * x[2 * D::NC];
+  }
+  e[0] = gx[0];
+  e[1] = gy[1];
+  e[2] = gz[2];
+  e[3] = gz[1] + gy[2];
+  e[4] = gz[0] + gx[2];
+  e[5] = gy[0] + gx[1];
+}
+
+// The same with the plane's values read from LDS (plane qc of the brick).
+template <typename R, typename D>
+__device__ __forceinline__ void row_strain(const R* x0, int qc, R xc, int a, int b, R (&e)[6]) {
+  R gx[3], gy[3], gz[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const R* x = x0 + d * D::NB + a + D::BX * b;
+    const R* r = x0 + d * D::NB + qc * D::NC + D::BX * b;
+    const R* t = x0 + d * D::NB + qc * D::NC + a;
+    gx[d] = line_diff<R>(a, r[0], r[1], r[2]);
+    gy[d] = line_diff<R>(b, t[0], t[D::BX], t[2 * D::BX]);
     gz[d] = dbasis(xc, 0) * x[0] + dbasis(xc, 1) * x[D::NC] + dbasis(xc, 2) * x[2 * D::NC];
   }
   e[0] = gx[0];
@@ -673,13 +711,15 @@ __device__ __forceinline__ void interior_part(const Geo& g, const ElementArgs<R>
 // Gradient terms of the interior bricks of one tile:
 //   g -= b_s * sum_e w|J| (div z div u_f, 2 eps(z):eps(u_f))
 // at the LGL nodes, z = the x1 displacement of the input register, u_f = the
-// stored forward stage, summed over sources and added to the FP64
-// accumulators (gacc: [8][2][n_nodes], slot c indexed like the partial arrays).
+// stored forward stage, summed over the sources of group grp and added to its
+// FP64 accumulators (gacc: [8][2][n_nodes], slot c indexed like the partial
+// arrays).
 // A part of its own: with the stiffness in the same workgroup a thread held
 // both fields' strains, the stresses and the rows (247 registers in FP32, two
 // waves per SIMD for every part of the launch).
 template <typename R, int TX, int TY, int TZ>
-__device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementArgs<R>& A, const Tile& t, R* X) {
+__device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementArgs<R>& A, const Tile& t, int grp,
+                                                   R* X) {
   using D = TileDims<TX, TY, TZ>;
   constexpr int BZ = D::BZ, NC = D::NC, NB = D::NB, NIT = D::NIT;
   const int cx = t.c & 255, cy = (t.c >> 8) & 255, cz = (t.c >> 16) & 255;
@@ -692,7 +732,7 @@ __device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementAr
 #pragma unroll
   for (int l = 0; l < BZ; ++l) gl[l] = gm[l] = 0.0;
 #pragma unroll 1
-  for (int src = 0; src < A.nsrc; ++src) {
+  for (int src = grp; src < A.nsrc; src += A.ggrp) {
     if (c.live) {
       const R* Yu = A.Y + (size_t)src * A.ystride + 3 * node;
       const R* F = A.fwd + (size_t)src * A.fstride + 3 * mi;
@@ -720,16 +760,30 @@ __device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementAr
     __syncthreads();
     R pl[9], pm[9];   // products at the points in the state precision; summed in FP64 below
     if (it.live) {
+      // FP32: both fields' planes in registers.  FP64: a point's values read
+      // from LDS as it comes (both planes and the sums are more than the 256
+      // registers of two waves; the clobber keeps the reads where they stand).
+      // With gradient at 62,500 bricks and 4 sources FP64 196 -> 181 us, while
+      // FP32 read so takes 90 us instead of 81.
+      constexpr bool ROWS = sizeof(R) == 8;
       R u[3][3][3], v[3][3][3];
-      plane_nodes<R, D>(X + it.n0 + it.qc * NC, u);
-      plane_nodes<R, D>(X + 3 * NB + it.n0 + it.qc * NC, v);
+      if constexpr (!ROWS) {
+        plane_nodes<R, D>(X + it.n0 + it.qc * NC, u);
+        plane_nodes<R, D>(X + 3 * NB + it.n0 + it.qc * NC, v);
+      }
 #pragma unroll
       for (int b = 0; b < 3; ++b)
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
           R e[6], f[6];
-          point_strain<R, D>(X + it.n0, u, it.xc, a, b, e);
-          point_strain<R, D>(X + 3 * NB + it.n0, v, it.xc, a, b, f);
+          if constexpr (ROWS) {
+            row_strain<R, D>(X + it.n0, it.qc, it.xc, a, b, e);
+            row_strain<R, D>(X + 3 * NB + it.n0, it.qc, it.xc, a, b, f);
+            asm volatile("" ::: "memory");
+          } else {
+            point_strain<R, D>(X + it.n0, u, it.xc, a, b, e);
+            point_strain<R, D>(X + 3 * NB + it.n0, v, it.xc, a, b, f);
+          }
           const R w = it.weight(a, b);
           R ee = 2 * (e[0] * f[0] + e[1] * f[1] + e[2] * f[2]);
           ee += e[3] * f[3] + e[4] * f[4] + e[5] * f[5];
@@ -758,7 +812,7 @@ __device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementAr
     }
     __syncthreads();
   }
-  if (c.live) add_gradient<BZ>(g, A.PG, c, cz, A.gw, gl, gm, A.gacc);
+  if (c.live) add_gradient<BZ>(g, A.PG, c, cz, A.gw, gl, gm, A.gacc + (size_t)grp * A.PG.per_src);
 }
 
 // The launch: 1D grid; first the gradient part (with GRAD; it walks the
@@ -773,12 +827,13 @@ element_kernel(Geo g, ElementArgs<R> A) {
   int b = blockIdx.x;
   auto tile_of = [](int i, int n) { return (i & 7) * (n >> 3) + (i >> 3); };
   if constexpr (GRAD) {
-    if (b < A.ggint) {
-      const int ti = tile_of(b, A.ggint);
-      if (ti < A.nint) interior_grad_part<R, TX, TY, TZ>(g, A, A.tiles_int[ti], smem);
+    if (b < A.ggint * A.ggrp) {
+      const int grp = b / A.ggint;
+      const int ti = tile_of(b - grp * A.ggint, A.ggint);
+      if (ti < A.nint) interior_grad_part<R, TX, TY, TZ>(g, A, A.tiles_int[ti], grp, smem);
       return;
     }
-    b -= A.ggint;
+    b -= A.ggint * A.ggrp;
   }
   if (b < A.gint * A.nsrc) {
     const int src = b / A.gint;
@@ -803,7 +858,7 @@ element_kernel(Geo g, ElementArgs<R> A) {
 // H from the forward stage's (u', u, ubar); with z the adjoint stress at j
 // (x1 S of the adjoint stage), the gradient gains
 // -gw (tr(e) sum_a z_aa, sum_v z_v (e_ab + e_ba)), e the weighted sum of H,
-// summed over sources, in the FP64 accumulators indexed like the partial
+// summed over a group's sources, in its FP64 accumulators indexed like the partial
 // arrays.  pfwd: stored forward PML displacements of the stage, per source
 // [x1 u (3) | x2 u (3) | x0 u (3)] x sp on the PML shell.
 // A launch of its own (full gradient only): in the stage launch its registers
@@ -813,7 +868,15 @@ __global__ void __launch_bounds__((TileDims<TX, TY, TZ>::THREADS)) pml_gradient_
   using D = TileDims<TX, TY, TZ>;
   constexpr int BZ = D::BZ;
   __shared__ R smem[6 * D::NB];
-  const int ti = xcd_tile();
+  // The sums of the two terms over sources: in FP64 a thread's own entries in
+  // LDS, which brings it from 420 registers to 234 (62,500 bricks, 4 sources:
+  // 110 -> 69 us); in FP32 they fit the registers (55 us, in LDS 60 us).
+  constexpr bool SUM_LDS = sizeof(R) == 8;
+  __shared__ double sum[SUM_LDS ? 2 * D::NB : 1];
+  double gl[BZ], gm[BZ];
+#pragma unroll
+  for (int l = 0; l < BZ; ++l) gl[l] = gm[l] = 0.0;
+  const int ti = xcd_tile(), grp = blockIdx.y;
   if (ti >= A.npml) return;
   const Tile t = A.tiles_pml[ti];
   const int cx = t.c & 255, cy = (t.c >> 8) & 255, cz = (t.c >> 16) & 255;
@@ -825,11 +888,10 @@ __global__ void __launch_bounds__((TileDims<TX, TY, TZ>::THREADS)) pml_gradient_
   line_stencil<R, false>(c.lx, cx, cX, oX, Sx);
   line_stencil<R, false>(c.ly, cy, cY, oY, Sy);
   const bool side = c.gi == 0 || c.gi == g.NX - 1 || c.gj == 0 || c.gj == g.NY - 1;
-  double gl[BZ], gm[BZ];
-#pragma unroll
-  for (int l = 0; l < BZ; ++l) gl[l] = gm[l] = 0.0;
+  if (SUM_LDS && c.live)
+    for (int l = 0; l < BZ; ++l) sum[threadIdx.x + D::NC * l] = sum[D::NB + threadIdx.x + D::NC * l] = 0.0;
 #pragma unroll 1
-  for (int src = 0; src < A.nsrc; ++src) {
+  for (int src = grp; src < A.nsrc; src += A.ggrp) {
     // the column's profile is formed anew for every source: kept, it and the
     // addresses and stretch factors of all its nodes take 200 registers
     Column cs = c;
@@ -875,13 +937,21 @@ __global__ void __launch_bounds__((TileDims<TX, TY, TZ>::THREADS)) pml_gradient_
         for (int v = 0; v < 6; ++v) z[v] = P[p_at(np, P_X1S, p) + v];
         R em = 2 * (z[0] * ex_[0] + z[1] * ey_[1] + z[2] * ez_[2]);
         em += z[3] * (ez_[1] + ey_[2]) + z[4] * (ez_[0] + ex_[2]) + z[5] * (ey_[0] + ex_[1]);
-        gl[l] -= (double)((ex_[0] + ey_[1] + ez_[2]) * (z[0] + z[1] + z[2]));
-        gm[l] -= (double)em;
+        double* pl = SUM_LDS ? &sum[threadIdx.x + D::NC * l] : &gl[l];
+        double* pm = SUM_LDS ? &sum[D::NB + threadIdx.x + D::NC * l] : &gm[l];
+        *pl -= (double)((ex_[0] + ey_[1] + ez_[2]) * (z[0] + z[1] + z[2]));
+        *pm -= (double)em;
       }
     }
     __syncthreads();
   }
-  if (c.live) add_gradient<BZ>(g, A.PG, c, cz, A.gw, gl, gm, A.gacc);
+  if (!c.live) return;
+#pragma unroll
+  for (int l = 0; SUM_LDS && l < BZ; ++l) {
+    gl[l] = sum[threadIdx.x + D::NC * l];
+    gm[l] = sum[D::NB + threadIdx.x + D::NC * l];
+  }
+  add_gradient<BZ>(g, A.PG, c, cz, A.gw, gl, gm, A.gacc + (size_t)grp * A.PG.per_src);
 }
 
 }  // namespace pmlfwi

@@ -60,3 +60,23 @@ def test_operator_and_gradient_at_tile_edges(P, ne, ps, pb):
             assert rel_l2(gm.cpu().numpy(), gm_o) <= tol
             T.close()
     S.close()
+
+
+# Tiles of 5x4x2 bricks: 8, 180 and 648 of them, so that the sources' gradient
+# terms are summed in three groups, in two (of two sources and one), and in one.
+@pytest.mark.parametrize("ne,full", [((6, 5, 3), True), ((30, 24, 10), False), ((40, 36, 18), False)])
+def test_gradient_of_several_sources_is_the_sum_of_each(P, ne, full):
+    """FP64, a few steps: other orders of the same sums, 1e-12."""
+    wl = W.tiny(ne_int=ne, npml_side=1, npml_bottom=1, nsteps=3, nsrc=3, seed=5)
+    want = None
+    for k in (slice(0, 1), slice(1, 2), slice(2, 3), slice(0, 3)):
+        T = P.Solver(wl.prob, wl.src_node[k], wl.src_dir[k], wl.rec_node, grad_full=full)
+        m = [T.tensor(a) for a in (wl.rho, wl.lam, wl.mu, wl.wavelet[k])]
+        tr = T.forward(*m)
+        _, res = T.misfit(tr, 0.5 * tr)
+        g = [x.cpu().numpy() for x in T.adjoint_gradient(*m, res)]
+        T.close()
+        if k == slice(0, 3):
+            assert all(np.abs(a).max() > 0 and rel_l2(a, b) <= 1e-12 for a, b in zip(g, want))
+        else:
+            want = g if want is None else [a + b for a, b in zip(want, g)]
