@@ -30,9 +30,14 @@
 //    the plane exchanges one value per point and component along z through LDS.
 // Measured (62,500 bricks, 4 sources, mean per stage): three launches of a
 // thread per point 117 us (FP32, forward) and 135 us (with gradient), this
-// launch 61 us and 81 us; FP64 133 us and 181 us.  One launch instead of three
+// launch 57 us and 75 us; FP64 128 us and 165 us.  One launch instead of three
 // on two streams also halves a small problem's pass: at 864 bricks a stage
-// waited 45 us for the host and the streams' events, now 17 us.
+// waited 45 us for the host and the streams' events, now 15 us.  Two things in
+// it count beyond the instructions: the loads of a column are all on their way
+// before the first is used (with the z profile read node by node between them
+// each node waited in turn: FP32 61 and 81 us, FP64 133 and 181 us), and a
+// plane's own values stay in registers for the derivatives along z, which takes
+// a quarter off the interior's LDS reads (FP64 131 and 177 us without).
 #pragma once
 #include "kernels.h"
 
@@ -76,6 +81,19 @@ struct ElementArgs {
   double* gacc;           // [ggrp][PG.per_src]
   Part PG;
 };
+
+// Entry i of a table that no kernel writes (tile lists, axis profiles), i the
+// same in all lanes: one scalar load, in the constant address space because the
+// compiler cannot see that the table is constant.
+template <typename T>
+__device__ __forceinline__ T uniform_entry(const T* table, int i) {
+  return ((const __attribute__((address_space(4))) T*)table)[__builtin_amdgcn_readfirstlane(i)];
+}
+
+__device__ __forceinline__ Tile uniform_tile(const Tile* tiles, int i) {
+  const int* t = (const int*)(tiles + __builtin_amdgcn_readfirstlane(i));
+  return Tile{uniform_entry(t, 0), uniform_entry(t, 1), uniform_entry(t, 2), uniform_entry(t, 3)};
+}
 
 // A thread's column of box nodes: node (lx, ly, 0) and what its nodes share.
 struct Column {
@@ -177,19 +195,18 @@ __device__ __forceinline__ R z_weight(int l, int cz) {
   return (l > 0 ? R(1.0 / 3.0) : R(0)) + ((l + 2 < BZ && l < 2 * cz) ? R(1.0 / 3.0) : R(0));
 }
 
-// PML profile of a column (x and y factors) and its nodes' places in the shell.
-template <typename R>
+// PML profile of a column and its nodes' places in the shell.
+template <typename R, int BZ>
 struct PmlColumn {
   R ax, ay, bx, by;
   int nbeta;                // of the two axes
-  const double* az;         // z profile from the column's lowest node
-  const double* bz;
+  R az[BZ], bz[BZ];         // z profile (the same for the whole workgroup)
   size_t node, ring0;       // node id of the lowest node; shell index on the first frame plane
 };
 
-template <typename R>
-__device__ __forceinline__ PmlColumn<R> pml_column(const Geo& g, const Column& c) {
-  PmlColumn<R> p;
+template <typename R, int BZ>
+__device__ __forceinline__ PmlColumn<R, BZ> pml_column(const Geo& g, const Column& c, int cz) {
+  PmlColumn<R, BZ> p;
   const double* A = g.tab;
   const double* B = g.tab + ax_n(g);
   const double bx = B[c.gi], by = B[ax_y(g) + c.gj];
@@ -198,16 +215,20 @@ __device__ __forceinline__ PmlColumn<R> pml_column(const Geo& g, const Column& c
   p.bx = R(bx);
   p.by = R(by);
   p.nbeta = (bx > 0.0) + (by > 0.0);
-  p.az = A + ax_z(g) + c.gk0;
-  p.bz = B + ax_z(g) + c.gk0;
+#pragma unroll
+  for (int l = 0; l < BZ; ++l) {
+    const int k = ax_z(g) + c.gk0 + min(l, 2 * cz);
+    p.az[l] = R(uniform_entry(A, k));
+    p.bz[l] = R(uniform_entry(B, k));
+  }
   p.node = (size_t)c.gi + (size_t)g.NX * (c.gj + (size_t)g.NY * c.gk0);
   p.ring0 = (size_t)pml_index(g, c.gi, c.gj, g.zb + 1);
   return p;
 }
 
 // Shell index of a column's node at plane k = gk0 + l.
-template <typename R>
-__device__ __forceinline__ size_t shell_index(const Geo& g, const PmlColumn<R>& p, int gk0, int l) {
+template <typename R, int BZ>
+__device__ __forceinline__ size_t shell_index(const Geo& g, const PmlColumn<R, BZ>& p, int gk0, int l) {
   const int k = gk0 + l;
   return k <= g.zb ? p.node + (size_t)l * g.plane : p.ring0 + (size_t)(k - g.zb - 1) * g.ring;
 }
@@ -218,9 +239,10 @@ struct Stretch {
   R Le[3], Lp[3], Lw[3];
 };
 
-template <typename R>
-__device__ __forceinline__ Stretch<R> stretch_at(const PmlColumn<R>& p, R az, R bz) {
+template <typename R, int BZ>
+__device__ __forceinline__ Stretch<R> stretch_at(const PmlColumn<R, BZ>& p, int l) {
   Stretch<R> s;
+  const R az = p.az[l], bz = p.bz[l];
   s.Le[0] = p.ay * az; s.Lp[0] = p.ay * bz + p.by * az; s.Lw[0] = p.by * bz;
   s.Le[1] = p.ax * az; s.Lp[1] = p.ax * bz + p.bx * az; s.Lw[1] = p.bx * bz;
   s.Le[2] = p.ax * p.ay; s.Lp[2] = p.ax * p.by + p.bx * p.ay; s.Lw[2] = p.bx * p.by;
@@ -263,9 +285,9 @@ __device__ __forceinline__ void pml_s_part(const Geo& g, const ElementArgs<R>& A
   const Column c = tile_column<D>(t, cx, cy);
   const size_t nn = (size_t)g.sn, np = (size_t)g.sp;
   R ez[BZ][3], la[BZ], m[BZ];
-  PmlColumn<R> pc{};
+  PmlColumn<R, BZ> pc{};
   if (c.live) {
-    pc = pml_column<R>(g, c);
+    pc = pml_column<R, BZ>(g, c, cz);
     const R* Y = A.Y + (size_t)src * A.ystride;
     const R* P = Y + 6 * nn;
     R wz[BZ][3], u1[BZ][3], u2[BZ][3], u0[BZ][3];
@@ -278,14 +300,6 @@ __device__ __forceinline__ void pml_s_part(const Geo& g, const ElementArgs<R>& A
           u1[l][d] = Y[n3 + d];
           u2[l][d] = Y[3 * nn + n3 + d];
         }
-        if (pc.nbeta + (pc.bz[l] > 0.0) >= 2) {
-          const size_t p = shell_index(g, pc, c.gk0, l);
-#pragma unroll
-          for (int d = 0; d < 3; ++d) u0[l][d] = P[p_at(np, P_X0U, p) + d];
-        } else {
-#pragma unroll
-          for (int d = 0; d < 3; ++d) u0[l][d] = R(0);
-        }
         if constexpr (!ADJ) {
           const int mi = material_index(g, c.gi, c.gj, c.gk0 + l);
           la[l] = A.lam[mi];
@@ -293,10 +307,21 @@ __device__ __forceinline__ void pml_s_part(const Geo& g, const ElementArgs<R>& A
         }
       }
     }
+    // after the loads above, as these wait for the x and y profile
+#pragma unroll
+    for (int l = 0; l < BZ; ++l) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) u0[l][d] = R(0);
+      if (l <= 2 * cz && pc.nbeta + (pc.bz[l] > 0) >= 2) {
+        const size_t p = shell_index(g, pc, c.gk0, l);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) u0[l][d] = P[p_at(np, P_X0U, p) + d];
+      }
+    }
 #pragma unroll
     for (int l = 0; l < BZ; ++l) {
       if (l <= 2 * cz) {
-        const Stretch<R> s = stretch_at(pc, R(pc.az[l]), R(pc.bz[l]));
+        const Stretch<R> s = stretch_at(pc, l);
         const int n = threadIdx.x + D::NC * l;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
@@ -358,27 +383,37 @@ __device__ __forceinline__ void pml_u_part(const Geo& g, const ElementArgs<R>& A
   const size_t nn = (size_t)g.sn, np = (size_t)g.sp;
   R ez[BZ][3];
   if (c.live) {
-    const PmlColumn<R> pc = pml_column<R>(g, c);
+    const PmlColumn<R, BZ> pc = pml_column<R, BZ>(g, c, cz);
     const R* P = A.Y + (size_t)src * A.ystride + 6 * nn;
     R tz[BZ][3];
+    R f0[BZ][6], f1[BZ][6], f2[BZ][6];
+    // the stresses of node l, loaded AHEAD nodes before they are used (as the
+    // registers allow; five ahead in FP32 or two in FP64 measured no faster)
+    constexpr int AHEAD = sizeof(R) == 4 ? 3 : 1;
+    auto load = [&](int l) {
+      if (l > 2 * cz) return;
+      const size_t p = shell_index(g, pc, c.gk0, l);
+#pragma unroll
+      for (int v = 0; v < 6; ++v) f1[l][v] = P[p_at(np, P_X1S, p) + v];
+#pragma unroll
+      for (int v = 0; v < 6; ++v) f2[l][v] = P[p_at(np, P_X2S, p) + v];
+#pragma unroll
+      for (int v = 0; v < 6; ++v) f0[l][v] = R(0);
+      if (pc.nbeta + (pc.bz[l] > 0) >= 2) {
+#pragma unroll
+        for (int v = 0; v < 6; ++v) f0[l][v] = P[p_at(np, P_X0S, p) + v];
+      }
+    };
+#pragma unroll
+    for (int l = 0; l < AHEAD && l < BZ; ++l) load(l);
 #pragma unroll
     for (int l = 0; l < BZ; ++l) {
+      if (l + AHEAD < BZ) load(l + AHEAD);
       if (l <= 2 * cz) {
-        const size_t p = shell_index(g, pc, c.gk0, l);
-        const R az = R(pc.az[l]), bz = R(pc.bz[l]);
-        R s0[6], s1[6], s2[6];
-#pragma unroll
-        for (int v = 0; v < 6; ++v) s1[v] = P[p_at(np, P_X1S, p) + v];
-#pragma unroll
-        for (int v = 0; v < 6; ++v) s2[v] = P[p_at(np, P_X2S, p) + v];
-        if (pc.nbeta + (pc.bz[l] > 0.0) >= 2) {
-#pragma unroll
-          for (int v = 0; v < 6; ++v) s0[v] = P[p_at(np, P_X0S, p) + v];
-        } else {
-#pragma unroll
-          for (int v = 0; v < 6; ++v) s0[v] = R(0);
-        }
-        const Stretch<R> s = stretch_at(pc, az, bz);
+        const R(&s0)[6] = f0[l];
+        const R(&s1)[6] = f1[l];
+        const R(&s2)[6] = f2[l];
+        const Stretch<R> s = stretch_at(pc, l);
         const int n = threadIdx.x + D::NC * l;
         R T[3][3];
         if constexpr (!ADJ) {
@@ -525,17 +560,37 @@ __device__ __forceinline__ void plane_nodes(const R* x, R (&u)[3][3][3]) {
       for (int a = 0; a < 3; ++a) u[d][b][a] = x[d * D::NB + a + D::BX * b];
 }
 
-// Strain (xx, yy, zz, 2 yz, 2 xz, 2 xy, times h/2) at point (a, b) of a plane
-// at coordinate xc of its brick; x0: the brick's first node in the box fields.
+// This thread's (brick, plane) item of an interior tile, and the weights
+// w_q (h/2)^3 (2/h)^2 of its points by their place in the plane.
+template <typename R>
+struct PlaneItem {
+  bool live;
+  int q, n0;                 // item; the plane's first box node
+  R wc, we, wm;              // weight of the plane's corners, edges, centre
+  // The brick's two other planes (distance in box nodes and in items) and,
+  // with D the derivative of the 1D basis, what this one, the next (1) and the
+  // one after (2) weigh in the derivative along z at this plane's points, and
+  // in its transpose at this plane's nodes.  A thread so takes its own plane's
+  // values from registers.
+  int n1, n2, q1, q2;
+  R d0, d1, d2, t1, t2;      // d0 is its own transpose
+  __device__ __forceinline__ R weight(int a, int b) const {
+    return (a == 1) + (b == 1) == 0 ? wc : ((a == 1) + (b == 1) == 1 ? we : wm);
+  }
+};
+
+// Strain (xx, yy, zz, 2 yz, 2 xz, 2 xy, times h/2) at point (a, b) of an item's
+// plane; x0: the plane's first node in the box fields.
 template <typename R, typename D>
-__device__ __forceinline__ void point_strain(const R* x0, const R (&u)[3][3][3], R xc, int a, int b, R (&e)[6]) {
+__device__ __forceinline__ void point_strain(const R* x0, const R (&u)[3][3][3], const PlaneItem<R>& it, int a, int b,
+                                             R (&e)[6]) {
   R gx[3], gy[3], gz[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const R* x = x0 + d * D::NB + a + D::BX * b;
     gx[d] = line_diff<R>(a, u[d][b][0], u[d][b][1], u[d][b][2]);
     gy[d] = line_diff<R>(b, u[d][0][a], u[d][1][a], u[d][2][a]);
-    gz[d] = dbasis(xc, 0) * x[0] + dbasis(xc, 1) * x[D::NC] + dbasis(xc, 2) * x[2 * D::NC];
+    gz[d] = it.d0 * u[d][b][a] + it.d1 * x[it.n1] + it.d2 * x[it.n2];
   }
   e[0] = gx[0];
   e[1] = gy[1];
@@ -545,18 +600,18 @@ __device__ __forceinline__ void point_strain(const R* x0, const R (&u)[3][3][3],
   e[5] = gy[0] + gx[1];
 }
 
-// The same with the plane's values read from LDS (plane qc of the brick).
+// The same with the plane's values read from LDS.
 template <typename R, typename D>
-__device__ __forceinline__ void row_strain(const R* x0, int qc, R xc, int a, int b, R (&e)[6]) {
+__device__ __forceinline__ void row_strain(const R* x0, const PlaneItem<R>& it, int a, int b, R (&e)[6]) {
   R gx[3], gy[3], gz[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const R* x = x0 + d * D::NB + a + D::BX * b;
-    const R* r = x0 + d * D::NB + qc * D::NC + D::BX * b;
-    const R* t = x0 + d * D::NB + qc * D::NC + a;
+    const R* r = x0 + d * D::NB + D::BX * b;
+    const R* t = x0 + d * D::NB + a;
     gx[d] = line_diff<R>(a, r[0], r[1], r[2]);
     gy[d] = line_diff<R>(b, t[0], t[D::BX], t[2 * D::BX]);
-    gz[d] = dbasis(xc, 0) * x[0] + dbasis(xc, 1) * x[D::NC] + dbasis(xc, 2) * x[2 * D::NC];
+    gz[d] = it.d0 * x[0] + it.d1 * x[it.n1] + it.d2 * x[it.n2];
   }
   e[0] = gx[0];
   e[1] = gy[1];
@@ -565,18 +620,6 @@ __device__ __forceinline__ void row_strain(const R* x0, int qc, R xc, int a, int
   e[4] = gz[0] + gx[2];
   e[5] = gy[0] + gx[1];
 }
-
-// This thread's (brick, plane) item of an interior tile, and the weights
-// w_q (h/2)^3 (2/h)^2 of its points by their place in the plane.
-template <typename R>
-struct PlaneItem {
-  bool live;
-  int q, qc, n0;             // item, place of the plane in its brick, the brick's first box node
-  R xc, wc, we, wm;          // coordinate of the plane; weight of its corners, edges, centre
-  __device__ __forceinline__ R weight(int a, int b) const {
-    return (a == 1) + (b == 1) == 0 ? wc : ((a == 1) + (b == 1) == 1 ? we : wm);
-  }
-};
 
 template <typename R, int TX, int TY, int TZ>
 __device__ __forceinline__ PlaneItem<R> plane_item(const Geo& g, int cx, int cy, int cz) {
@@ -584,11 +627,20 @@ __device__ __forceinline__ PlaneItem<R> plane_item(const Geo& g, int cx, int cy,
   PlaneItem<R> it;
   it.q = threadIdx.x;
   const int ex = it.q % TX, ey = (it.q / TX) % TY, zz = it.q / D::NE, ez = zz / 3;
-  it.qc = zz - 3 * ez;
+  const int qc = zz - 3 * ez;   // place of the plane in its brick
   it.live = it.q < D::NIT && ex < cx && ey < cy && ez < cz;
-  it.n0 = 2 * ex + D::BX * (2 * ey) + D::NC * (2 * ez);
-  it.xc = R(it.qc - 1);
-  const R wz = R(0.5 * g.h) * (it.qc == 1 ? R(4.0 / 3.0) : R(1.0 / 3.0));
+  it.n0 = 2 * ex + D::BX * (2 * ey) + D::NC * (2 * ez + qc);
+  const int s1 = qc == 2 ? -2 : 1, s2 = qc == 0 ? 2 : -1;
+  it.n1 = s1 * D::NC;
+  it.n2 = s2 * D::NC;
+  it.q1 = s1 * D::NE;
+  it.q2 = s2 * D::NE;
+  it.d0 = R(1.5) * R(qc - 1);
+  it.d1 = qc == 0 ? R(2) : R(0.5);
+  it.d2 = qc == 2 ? R(-2) : R(-0.5);
+  it.t1 = qc == 1 ? R(-2) : R(-0.5);
+  it.t2 = qc == 1 ? R(2) : R(0.5);
+  const R wz = R(0.5 * g.h) * (qc == 1 ? R(4.0 / 3.0) : R(1.0 / 3.0));
   it.wc = wz * R(1.0 / 9.0);
   it.we = wz * R(4.0 / 9.0);
   it.wm = wz * R(16.0 / 9.0);
@@ -600,7 +652,7 @@ __device__ __forceinline__ PlaneItem<R> plane_item(const Geo& g, int cx, int cy,
 template <typename R, int TX, int TY, int TZ>
 __device__ __forceinline__ void interior_part(const Geo& g, const ElementArgs<R>& A, const Tile& t, int src, R* smem) {
   using D = TileDims<TX, TY, TZ>;
-  constexpr int BX = D::BX, BZ = D::BZ, NC = D::NC, NB = D::NB, NE = D::NE, NIT = D::NIT;
+  constexpr int BX = D::BX, BZ = D::BZ, NC = D::NC, NB = D::NB, NIT = D::NIT;
   const int cx = t.c & 255, cy = (t.c >> 8) & 255, cz = (t.c >> 16) & 255;
   const Column c = tile_column<D>(t, cx, cy);
   R* sLam = smem;
@@ -638,13 +690,13 @@ __device__ __forceinline__ void interior_part(const Geo& g, const ElementArgs<R>
   R s[9][6];        // strains, then weighted stresses, at the points
   if (it.live) {
     R u[3][3][3];
-    plane_nodes<R, D>(X + it.n0 + it.qc * NC, u);
+    plane_nodes<R, D>(X + it.n0, u);
 #pragma unroll
     for (int b = 0; b < 3; ++b)
 #pragma unroll
       for (int a = 0; a < 3; ++a) {
-        const int k = 3 * b + a, nq = it.n0 + a + BX * b + it.qc * NC;
-        point_strain<R, D>(X + it.n0, u, it.xc, a, b, s[k]);
+        const int k = 3 * b + a, nq = it.n0 + a + BX * b;
+        point_strain<R, D>(X + it.n0, u, it, a, b, s[k]);
         const R w = it.weight(a, b);
         const R m = w * sMu[nq], m2 = 2 * m, lt = w * sLam[nq] * (s[k][0] + s[k][1] + s[k][2]);
 #pragma unroll
@@ -676,15 +728,20 @@ __device__ __forceinline__ void interior_part(const Geo& g, const ElementArgs<R>
   if (it.live) {
     // transposed derivative along z: this plane's nodes gather the z stress of
     // the brick's three planes
-    R c1, c0;
-    dbasis_coef<R>(it.qc, c1, c0);
 #pragma unroll
-    for (int d = 0; d < 3; ++d)
+    for (int d = 0; d < 3; ++d) {
+      R z1[9], z2[9];
 #pragma unroll
       for (int k = 0; k < 9; ++k) {
-        const R* x = X + (9 * d + k) * NIT + it.q - it.qc * NE;
-        out[d][k / 3][k % 3] += (c0 - c1) * x[0] + c0 * x[NE] + (c0 + c1) * x[2 * NE];
+        const R* x = X + (9 * d + k) * NIT + it.q;
+        z1[k] = x[it.q1];
+        z2[k] = x[it.q2];
       }
+      constexpr int vz[3] = {4, 3, 2};
+#pragma unroll
+      for (int k = 0; k < 9; ++k)
+        out[d][k / 3][k % 3] += it.d0 * s[k][vz[d]] + it.t1 * z1[k] + it.t2 * z2[k];
+    }
   }
   __syncthreads();
   if (it.live) {
@@ -768,8 +825,8 @@ __device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementAr
       constexpr bool ROWS = sizeof(R) == 8;
       R u[3][3][3], v[3][3][3];
       if constexpr (!ROWS) {
-        plane_nodes<R, D>(X + it.n0 + it.qc * NC, u);
-        plane_nodes<R, D>(X + 3 * NB + it.n0 + it.qc * NC, v);
+        plane_nodes<R, D>(X + it.n0, u);
+        plane_nodes<R, D>(X + 3 * NB + it.n0, v);
       }
 #pragma unroll
       for (int b = 0; b < 3; ++b)
@@ -777,12 +834,12 @@ __device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementAr
         for (int a = 0; a < 3; ++a) {
           R e[6], f[6];
           if constexpr (ROWS) {
-            row_strain<R, D>(X + it.n0, it.qc, it.xc, a, b, e);
-            row_strain<R, D>(X + 3 * NB + it.n0, it.qc, it.xc, a, b, f);
+            row_strain<R, D>(X + it.n0, it, a, b, e);
+            row_strain<R, D>(X + 3 * NB + it.n0, it, a, b, f);
             asm volatile("" ::: "memory");
           } else {
-            point_strain<R, D>(X + it.n0, u, it.xc, a, b, e);
-            point_strain<R, D>(X + 3 * NB + it.n0, v, it.xc, a, b, f);
+            point_strain<R, D>(X + it.n0, u, it, a, b, e);
+            point_strain<R, D>(X + 3 * NB + it.n0, v, it, a, b, f);
           }
           const R w = it.weight(a, b);
           R ee = 2 * (e[0] * f[0] + e[1] * f[1] + e[2] * f[2]);
@@ -830,7 +887,7 @@ element_kernel(Geo g, ElementArgs<R> A) {
     if (b < A.ggint * A.ggrp) {
       const int grp = b / A.ggint;
       const int ti = tile_of(b - grp * A.ggint, A.ggint);
-      if (ti < A.nint) interior_grad_part<R, TX, TY, TZ>(g, A, A.tiles_int[ti], grp, smem);
+      if (ti < A.nint) interior_grad_part<R, TX, TY, TZ>(g, A, uniform_tile(A.tiles_int, ti), grp, smem);
       return;
     }
     b -= A.ggint * A.ggrp;
@@ -838,7 +895,7 @@ element_kernel(Geo g, ElementArgs<R> A) {
   if (b < A.gint * A.nsrc) {
     const int src = b / A.gint;
     const int ti = tile_of(b - src * A.gint, A.gint);
-    if (ti < A.nint) interior_part<R, TX, TY, TZ>(g, A, A.tiles_int[ti], src, smem);
+    if (ti < A.nint) interior_part<R, TX, TY, TZ>(g, A, uniform_tile(A.tiles_int, ti), src, smem);
     return;
   }
   b -= A.gint * A.nsrc;
@@ -847,7 +904,7 @@ element_kernel(Geo g, ElementArgs<R> A) {
   const int src = b / A.gpml;
   const int ti = tile_of(b - src * A.gpml, A.gpml);
   if (ti >= A.npml) return;
-  const Tile t = A.tiles_pml[ti];
+  const Tile t = uniform_tile(A.tiles_pml, ti);
   if (part == 0) pml_s_part<R, D, ADJ>(g, A, t, src, smem);
   else pml_u_part<R, D, ADJ>(g, A, t, src, smem);
 }
@@ -878,7 +935,7 @@ __global__ void __launch_bounds__((TileDims<TX, TY, TZ>::THREADS)) pml_gradient_
   for (int l = 0; l < BZ; ++l) gl[l] = gm[l] = 0.0;
   const int ti = xcd_tile(), grp = blockIdx.y;
   if (ti >= A.npml) return;
-  const Tile t = A.tiles_pml[ti];
+  const Tile t = uniform_tile(A.tiles_pml, ti);
   const int cx = t.c & 255, cy = (t.c >> 8) & 255, cz = (t.c >> 16) & 255;
   const Column c = tile_column<D>(t, cx, cy);
   const size_t nn = (size_t)g.sn, np = (size_t)g.sp;
@@ -896,8 +953,8 @@ __global__ void __launch_bounds__((TileDims<TX, TY, TZ>::THREADS)) pml_gradient_
     // addresses and stretch factors of all its nodes take 200 registers
     Column cs = c;
     asm volatile("" : "+v"(cs.gi), "+v"(cs.gj), "+v"(cs.gk0));
-    PmlColumn<R> pc{};
-    if (c.live) pc = pml_column<R>(g, cs);
+    PmlColumn<R, BZ> pc{};
+    if (c.live) pc = pml_column<R, BZ>(g, cs, cz);
     R ez[BZ][3];
     if (c.live) {
       const R* F = A.pfwd + (size_t)src * A.pfstride;
@@ -906,8 +963,8 @@ __global__ void __launch_bounds__((TileDims<TX, TY, TZ>::THREADS)) pml_gradient_
       for (int l = 0; l < BZ; ++l) {
         if (l <= 2 * cz) {
           const size_t p = shell_index(g, pc, cs.gk0, l);
-          const bool on = !side && c.gk0 + l > 0, hist = on && pc.nbeta + (pc.bz[l] > 0.0) >= 2;
-          const Stretch<R> s = stretch_at(pc, R(pc.az[l]), R(pc.bz[l]));
+          const bool on = !side && c.gk0 + l > 0, hist = on && pc.nbeta + (pc.bz[l] > 0) >= 2;
+          const Stretch<R> s = stretch_at(pc, l);
           const int n = threadIdx.x + D::NC * l;
 #pragma unroll
           for (int i = 0; i < 3; ++i) {

@@ -70,23 +70,6 @@ __device__ __forceinline__ float dlgl(int q, int a) {
 }
 __device__ __forceinline__ double wlgl(int a) { return a == 1 ? 4.0 / 3.0 : 1.0 / 3.0; }
 
-// The same derivatives in closed form, for the hot loops: with the LGL nodes
-// xi = -1, 0, 1, the basis functions l_0 = xi (xi - 1) / 2, l_1 = 1 - xi^2,
-// l_2 = xi (xi + 1) / 2 have l_p' (xi) = (3 (p - 1)^2 - 2) xi + (p - 1) / 2.
-// dbasis(x, a) = l_a'(x) for a known at compile time (unrolled loops), x the
-// point's coordinate xi_q = q - 1 (exact in any precision); dbasis_coef gives
-// the two factors for a basis index known only at run time.
-template <typename R>
-__device__ __forceinline__ R dbasis(R x, int a) {
-  return a == 0 ? x - R(0.5) : (a == 1 ? R(-2) * x : x + R(0.5));
-}
-template <typename R>
-__device__ __forceinline__ void dbasis_coef(int p, R& c1, R& c0) {
-  const int m = p - 1;
-  c1 = R(3 * m * m - 2);
-  c0 = R(0.5) * R(m);
-}
-
 struct Tile {  // bricks [x, x+cx) x [y, y+cy) x [z, z+cz)
   int x, y, z, c;  // c = cx | cy << 8 | cz << 16
 };
