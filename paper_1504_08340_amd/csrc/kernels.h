@@ -305,7 +305,7 @@ __device__ __forceinline__ void pml_node_setup(const Geo& g, int gi, int gj, int
 // row is read and written 8 times and an x2 row 13 times, against 16 times each
 // with acc += c K in every stage, and Xn takes one rounding of the sum instead
 // of one per stage.  Measured (62,500 bricks, 4 sources, mean per stage): FP32
-// 99 -> 80 us, FP64 232 -> 180 us; error of FP32 traces after 400 steps of 864
+// 99 -> 76 us, FP64 232 -> 174 us; error of FP32 traces after 400 steps of 864
 // bricks against FP64 4.0e-7 -> 2.1e-7.
 template <typename R>
 struct NodalArgs {
@@ -328,7 +328,7 @@ struct NodalArgs {
   R* pstore;                  // PML displacement fields of the produced register
   long long pstore_stride;    // [x1 u | x2 u | x0 u] x sp per source, or nullptr
   long long first, last;      // row range of this launch: [0, sn) node rows, then PML rows
-  unsigned rot;               // workgroup b takes rows of block (b + rot) mod grid
+  unsigned rot, nblocks;      // workgroup b takes rows of block (b + rot) mod nblocks, the grid
 };
 
 // Where a node's contributions sit in the partial arrays: array 0 always, and
@@ -393,7 +393,11 @@ __device__ __forceinline__ void gather_rows(const Part& P, const PartSlots& S, c
 // STORE = 2 also the PML displacement fields (full gradient).
 // Threads [0, sn) take the displacement rows of node gid (none past n_nodes),
 // threads [sn, sn + n_pml) the PML rows; every load of a thread is issued
-// before its first store.  The kept stage displacement is written, and Xn, the
+// before its first store, first those that need no table, then the tables, then
+// what these tell, so that few waits follow one another (62,500 bricks, 4
+// sources, stages 1, 2 and 4: FP32 60.5, 76.5, 98 -> 59.0, 75.7, 93.5 us; FP64
+// 141, 170, 227 -> 140, 166, 222 us).  With the history rows also before the
+// gather, the registers for them cost FP32 a wave and stage 4 98 us.  The kept stage displacement is written, and Xn, the
 // stage inputs and the residual partials are read, with non-temporal hints:
 // none of them is touched again before the next stage's nodal pass (the kept
 // displacement not before the adjoint), so they should not displace the stage
@@ -401,7 +405,7 @@ __device__ __forceinline__ void gather_rows(const Part& P, const PartSlots& S, c
 template <typename R, int MODE, int STORE>
 __global__ void __launch_bounds__(PMLFWI_NODAL_THREADS) nodal_rk_kernel(Geo g, NodalArgs<R> A) {
   const int src = blockIdx.y;
-  const unsigned blk = A.rot ? (blockIdx.x + A.rot) % gridDim.x : blockIdx.x;
+  const unsigned turned = blockIdx.x + A.rot, blk = turned < A.nblocks ? turned : turned - A.nblocks;
   const long long gid = A.first + (long long)blk * blockDim.x + threadIdx.x;
   if (gid >= A.last) return;
   const size_t nn = (size_t)g.sn, np = (size_t)g.sp;
@@ -444,9 +448,8 @@ __global__ void __launch_bounds__(PMLFWI_NODAL_THREADS) nodal_rk_kernel(Geo g, N
     const int j = r_ / g.NX, i = r_ - j * g.NX;
     if (is_dirichlet(g, i, j, k)) return;
     const bool pml = in_pml(g, i, j, k);
-    const PartSlots PS = part_slots(g, A.part, i, j, k);
+    // what needs no table goes out first, then the tables, then what they tell
     R u2[3], rr[3], x1[3], x2[3], y2[3] = {0, 0, 0}, y3[3] = {0, 0, 0};
-    gather_rows<R, 3, false>(A.part, PS, res, 3 * (size_t)node, rr);
     const size_t o1 = u_at(nn, 0, node), o2 = u_at(nn, 3, node);   // x1 u, x2 u of the node
     fetch(X, o1, x1);
     fetch(X, o2, x2);
@@ -461,6 +464,26 @@ __global__ void __launch_bounds__(PMLFWI_NODAL_THREADS) nodal_rk_kernel(Geo g, N
       fetch(Y3, o2, y3);
     }
     const R im = A.invMu[node];
+    const PartSlots PS = part_slots(g, A.part, i, j, k);
+    R kap = 0, cb = 0, cc = 0, cd = 0, h1[3] = {0, 0, 0}, h0[3] = {0, 0, 0};
+    if (pml) {
+      double mrd, mp;
+      lumped_masses_tab(g, i, j, k, mrd, mp);
+      const PmlCoef c = pml_coef_tab(g, i, j, k);
+      kap = R(mp) / (R(mrd) + R(c.a) * R(mp));
+      cb = R(c.b);
+      if (c.nbeta >= 2) {     // c and d vanish elsewhere
+        cc = R(c.c);
+        cd = R(c.d);
+        const R* P = Y + 6 * nn + p_at(np, P_X0U, (size_t)pml_index(g, i, j, k));
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          h1[d] = MODE == 0 ? x1[d] : Y[o1 + d];
+          h0[d] = P[d];
+        }
+      }
+    }
+    gather_rows<R, 3, false>(A.part, PS, res, 3 * (size_t)node, rr);
     R a2[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) a2[d] = -im * rr[d];
@@ -470,21 +493,8 @@ __global__ void __launch_bounds__(PMLFWI_NODAL_THREADS) nodal_rk_kernel(Geo g, N
       for (int d = 0; d < 3; ++d) a2[d] += im * R(A.src_dir[3 * src + d] * s);
     }
     if (pml) {
-      double mrd, mp;
-      lumped_masses_tab(g, i, j, k, mrd, mp);
-      const PmlCoef c = pml_coef_tab(g, i, j, k);
-      const R kap = R(mp) / (R(mrd) + R(c.a) * R(mp));
-      R t[3];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) t[d] = R(c.b) * u2[d];
-      if (c.nbeta >= 2) {     // c and d vanish elsewhere
-        const size_t p = (size_t)pml_index(g, i, j, k);
-        const R* P = Y + 6 * nn + p_at(np, P_X0U, p);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) t[d] += R(c.c) * (MODE == 0 ? x1[d] : Y[o1 + d]) + R(c.d) * P[d];
-      }
-#pragma unroll
-      for (int d = 0; d < 3; ++d) a2[d] -= kap * t[d];
+      for (int d = 0; d < 3; ++d) a2[d] -= kap * (cb * u2[d] + (cc * h1[d] + cd * h0[d]));
     }
     R out1[3], out2[3];
 #pragma unroll
@@ -518,16 +528,7 @@ __global__ void __launch_bounds__(PMLFWI_NODAL_THREADS) nodal_rk_kernel(Geo g, N
   const size_t p = (size_t)pp;
   int i, j, k;
   pml_coords(g, (int)p, i, j, k);
-  const PmlCoef c = pml_coef_tab(g, i, j, k);
-  double mrd, mp;
-  lumped_masses_tab(g, i, j, k, mrd, mp);
-  const bool hist = c.nbeta >= 2;
-  const bool hu = hist && !is_dirichlet(g, i, j, k);
   const size_t P0 = 6 * nn;                 // the registers' PML part
-  const PartSlots PS = part_slots(g, A.part, i, j, k);
-  const R ia = R(1) / R(c.a), iam = R(1) / (R(c.a) * R(mp));
-  const R cb = R(c.b), cc = R(c.c), cd = R(c.d);
-
   // x0 u: 3 components, on history nodes off the Dirichlet boundary; x0 S: 6,
   // on history nodes; x1 S, x2 S: 6 each.  A field's components move with one
   // vector load or store.
@@ -546,6 +547,14 @@ __global__ void __launch_bounds__(PMLFWI_NODAL_THREADS) nodal_rk_kernel(Geo g, N
     fetch(Y2, b2s, y2);
     fetch(Y3, b2s, y3);
   }
+  const PartSlots PS = part_slots(g, A.part, i, j, k);
+  const PmlCoef c = pml_coef_tab(g, i, j, k);
+  double mrd, mp;
+  lumped_masses_tab(g, i, j, k, mrd, mp);
+  const bool hist = c.nbeta >= 2;
+  const bool hu = hist && !is_dirichlet(g, i, j, k);
+  const R ia = R(1) / R(c.a), iam = R(1) / (R(c.a) * R(mp));
+  const R cb = R(c.b), cc = R(c.c), cd = R(c.d);
   gather_rows<R, 6, true>(A.part, PS, res, 3 * nn + 6 * p, rv);
 #pragma unroll
   for (int v = 0; v < 6; ++v) t[v] = cb * s2[v];

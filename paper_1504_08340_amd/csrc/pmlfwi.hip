@@ -1128,6 +1128,7 @@ struct Run {
       A.first = 0;
       A.last = rows;
       A.rot = (unsigned)(G.sn / NT) % nb;
+      A.nblocks = nb;
       kern<<<dim3(nb, p->nsrc), NT, 0, st>>>(G, A);
     }
     if (wav && p->nload > 0) {
