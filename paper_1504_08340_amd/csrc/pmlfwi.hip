@@ -1886,7 +1886,7 @@ fwi_status fwi_regularization(fwi_plan* p, void* stream, int kind, double eps, c
   hipStream_t st = (hipStream_t)stream;
   const Geo& G = p->g;
   const int k = kind == FWI_REG_TIKHONOV ? REG_TN : REG_TV;
-  if (grad) reg_gradient_kernel<<<blocks(G.n_int, 256), 256, 0, st>>>(G, k, eps, field, grad);
+  if (grad) reg_gradient_kernel<<<reg_tiles(G), REG_THREADS, 0, st>>>(G, k, eps, field, grad);
   if (value) {
     const int nb = red_parts(27LL * G.ex * G.ey * G.ez), slot = nb > 1 ? stream_slot(st) : -1;
     reg_value_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>(G, k, eps, field, value, nb, slot);

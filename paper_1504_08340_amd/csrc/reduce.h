@@ -45,18 +45,38 @@ struct RedMax {
   static __device__ double init() { return 0.0; }
   static __device__ double join(double a, double b) { return fmax(a, b); }
 };
-// Tree over the workgroup's values; the result is valid in thread 0.
+// Tree over the workgroup's values: the upper half onto the lower, and again.
+// Down to a wave's 64 values through LDS, below that between its lanes, without
+// a barrier a level.  The result is valid in thread 0.
 template <typename Op>
 __device__ __forceinline__ double red_tree(double v, double* sh) {
   sh[threadIdx.x] = v;
   __syncthreads();
-  for (int s = RED_THREADS / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] = Op::join(sh[threadIdx.x], sh[threadIdx.x + s]);
+  for (int s = RED_THREADS / 2; s >= 64; s >>= 1) {
+    if ((int)threadIdx.x < s) v = sh[threadIdx.x] = Op::join(v, sh[threadIdx.x + s]);
     __syncthreads();
   }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
+  for (int s = 32; s > 0; s >>= 1) v = Op::join(v, __shfl_down(v, s));
+  return v;
+}
+
+// add(load(i)) over this thread's entries of a part, in order: eight loads are in
+// flight together, where one by one each waits for memory (eight waits of an
+// average thread).
+template <typename L, typename A>
+__device__ __forceinline__ void red_entries(int part, long long n, long long step, L&& load, A&& add) {
+  constexpr int U = RED_PER_PART / RED_THREADS;
+  for (long long i = (long long)part * RED_THREADS + threadIdx.x; i < n; i += U * step) {
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long long j = i + u * step;
+      v[u] = load(j < n ? j : i);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (i + u * step < n) add(v[u]);
+  }
 }
 
 // Joins one value per part; grid: nb workgroups, or one that has left all nb
@@ -101,8 +121,9 @@ __global__ void __launch_bounds__(RED_THREADS) dot_kernel(long long n, const dou
   const long long step = (long long)nb * RED_THREADS;
   if (reduce_parts<RedSum>(nb, red_slot(slot), sh, r, [&](int part) {
         double acc = 0.0;
-        for (long long i = (long long)part * RED_THREADS + threadIdx.x; i < n; i += step)
-          acc += a[i] * b[i] * (w ? w[i] : 1.0);
+        auto add = [&](double v) { acc += v; };
+        if (w) red_entries(part, n, step, [&](long long i) { return a[i] * b[i] * w[i]; }, add);
+        else red_entries(part, n, step, [&](long long i) { return a[i] * b[i]; }, add);
         return acc;
       }) && threadIdx.x == 0)
     out[0] = r;
@@ -116,7 +137,7 @@ __global__ void __launch_bounds__(RED_THREADS) absmax_kernel(long long n, const 
   const long long step = (long long)nb * RED_THREADS;
   if (reduce_parts<RedMax>(nb, red_slot(slot), sh, r, [&](int part) {
         double m = 0.0;
-        for (long long i = (long long)part * RED_THREADS + threadIdx.x; i < n; i += step) m = fmax(m, fabs(x[i]));
+        red_entries(part, n, step, [&](long long i) { return x[i]; }, [&](double v) { m = fmax(m, fabs(v)); });
         return m;
       }) && threadIdx.x == 0)
     out[0] = r;

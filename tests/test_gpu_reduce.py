@@ -54,3 +54,26 @@ def test_dot_and_absmax(n):
         B.fwi_dot(None, n, ta, tb, tw, out[3:4])
         torch.cuda.synchronize()
         assert cap[0] == eager[0] and cap[1] == eager[2] and out[3] == eager[0]
+
+
+# The regularization's gradient by tiles of 4x4x2 bricks: one brick, one tile,
+# a brick more along every axis, several tiles with one short of full.
+@pytest.mark.parametrize("ne", [(1, 1, 1), (4, 4, 2), (5, 5, 3), (9, 3, 4), (3, 8, 7)])
+def test_regularization_gradient_at_tile_edges(ne):
+    """Sums of at most 72 terms with cancelling signs, FP64: 1e-12 of the largest."""
+    import torch
+    import paper_1504_08340_amd as P
+    import workloads as W
+    from oracle.regularize import Regularizer
+    wl = W.tiny(ne_int=ne, nsteps=2, seed=9)
+    r = Regularizer(wl.prob)
+    S = P.Solver(wl.prob, wl.src_node, wl.src_dir, wl.rec_node)
+    f = wl.lam / np.abs(wl.lam).max()
+    v, g = S.tensor(np.zeros(1)), S.tensor(np.zeros(f.size))
+    for kind, eps in ((P.FWI_REG_TIKHONOV, 0.0), (P.FWI_REG_TV, 1e-3)):
+        P.fwi_regularization(S.plan, None, kind, eps, S.tensor(f), v, g)
+        vo, go = r.tikhonov(f) if kind == P.FWI_REG_TIKHONOV else r.total_variation(f, eps)
+        assert abs(float(v[0]) - vo) <= 1e-12 * abs(vo)
+        assert np.abs(g.cpu().numpy() - go).max() <= 1e-12 * np.abs(go).max()
+    torch.cuda.synchronize()
+    S.close()
