@@ -190,79 +190,110 @@ conv3d_f32_kernel(ConvShape c, const float* __restrict__ src, const float* __res
 }
 
 // dw[co][ci][tap] = sum over batch and outputs of g * x, and db[co] = sum of g.
-// A workgroup of 4 waves takes one tile (taps (kd, kh) with all kw, 16 output
-// channels, 16 input channels) on v_mfma_f32_16x16x4f32 and one of nsplit shares
-// of the outputs; the waves take 16 outputs at a time in turn and their sums are
-// added in LDS in a fixed order.  The shares' sums meet in the stream's slot: the
-// last share of a tile to arrive adds them in order (a launch without a slot
-// takes the shares of a tile in turn in one workgroup: the same bits).  A lane
-// holds four neighbouring outputs of one channel (lane group q the outputs 4 q ..
-// 4 q + 3), so the g it loads serve 4 K products, and with SW = 1 or 2 (the w
-// stride; extents and pointers allow vector loads) so does one strip of x: the
-// K shifted operands come from two or three loads.  SW = 0: any shape, element
-// by element.  The workgroups of taps (0, 0) and input channel 0 also sum g.
-// Of the network's training step at batch 8 this takes 0.77 ms; one workgroup
-// per weight walking all outputs took 13.0 ms with the bias sums.
-constexpr int WGRAD_THREADS = 256, WGRAD_WAVES = WGRAD_THREADS / 64;
+// Order of the sums: the outputs, numbered through the batch, are dealt to 256
+// chains (output T to chain T mod 256), each chain adds its products one by one,
+// and the chains are joined in a tree (chain t and t + 128, then t + 64, ..).  As
+// in the forward pass the order is part of the result: an update that differs in
+// the last bit of a few weights can turn a ReLU mask of the next step.
+// A workgroup of 4 waves takes a tile (taps (kd, kh) with all kw, 16 output and 16
+// input channels) and a quarter of the chains, a wave 16 of them, on the one-product MFMA form
+// 16x16x1 in four blocks: block q and the step's product j hold chain
+// 16 cg + 4 q + j.  So a lane loads four neighbouring outputs of its channel at
+// once, which serve 4 K products, and with SW = 1 or 2 (the w stride; extents and
+// pointers allow vector loads) so does one strip of x; SW = 0: any shape, element
+// by element.  The
+// next WGRAD_AHEAD chunks of 16 outputs are in flight during the products of the
+// ones before.  The first two levels of the tree join the waves, in LDS; the
+// quarters meet in the stream's slot, where the last of a tile to arrive joins
+// them.  Without a slot, or with more tiles than one holds (then tiles enough to
+// fill the chip), one workgroup takes a tile's taps and quarters in turn (SPLIT =
+// false): the same bits.
+// The workgroups of taps (0, 0) and input channel 0 also sum g.
+// Of the network's training step at batch 8 this takes 0.67 ms; one workgroup
+// per weight walking all outputs, in the same order, took 13.0 ms with the bias
+// sums.  Eight chunks ahead, or the loads by neighbouring lanes and an exchange
+// through LDS, measured no faster, one tap instead of three to a wave slower
+// (0.86 ms); products of four outputs each (16x16x4, another order) took 0.77 ms.
+constexpr int WGRAD_THREADS = 256, WGRAD_WAVES = WGRAD_THREADS / 64, WGRAD_AHEAD = 4;
 constexpr int WGRAD_SLOTS = 4;              // streams that may hold a slot (per device)
-constexpr int WGRAD_TILES = 1024;           // most tiles of a split launch
-constexpr int WGRAD_ENTRY = 3 * 256 + 16;   // a tile's sums of one share, and its channels' sums of g
-constexpr int WGRAD_ENTRIES = 1280;         // tiles x shares of a split launch
+constexpr int WGRAD_TILES = 48;             // most tiles of a split launch
+constexpr int WGRAD_ENTRY = 3 * 256 + 16;   // sums of one chain: a tile's weights, its channels' g
 struct WgradSlot {
-  float part[WGRAD_ENTRIES][WGRAD_ENTRY];
+  float part[WGRAD_TILES][4][16][WGRAD_ENTRY];
   unsigned count[WGRAD_TILES];
 };
 static __device__ WgradSlot wgrad_slots[WGRAD_SLOTS];   // counts start at 0
 
-template <int K, int SW>
-__global__ void __launch_bounds__(WGRAD_THREADS)
+// One chunk of a lane: four outputs of channel co, and their strip of x or (SW =
+// 0) their places in x for each tap.
+template <int SW, int KT>
+struct WgradChunk {
+  v4f t, m;                 // dL/dy, and the activated output (ReLU) or 1
+  v4f x0, x1;               // strip of x
+  float el, er;             // its neighbours
+  bool on, in, hl, hr;      // the outputs exist; the taps' row does; the neighbours do
+};
+template <int KT>
+struct WgradChunk<0, KT> {
+  v4f e, g[KT], v[KT];      // g, g where the output has the tap, x there
+};
+
+template <int K, int SW, bool SPLIT>
+__global__ void __launch_bounds__(WGRAD_THREADS, 1)
 conv3d_wgrad_kernel(ConvShape c, const float* __restrict__ dy, const float* __restrict__ y, int relu,
                     const float* __restrict__ x, float* __restrict__ dw, float* __restrict__ db, FastDiv dWo,
-                    FastDiv dHo, int pchunks, int ntiles, int nsplit, int slot) {
+                    FastDiv dHo, FastDiv dP, int ntiles, int slot) {
   constexpr int T2 = K * K, pad = K / 2;
-  __shared__ float sAcc[WGRAD_WAVES][K * 256];
-  __shared__ float sB[WGRAD_WAVES][64];
+  constexpr int KT = SPLIT ? K : 1;          // taps along w at a time
+  __shared__ float sAcc[2][64][64 + 1];      // two waves' accumulators, a lane's 64 to a row
+  __shared__ float sB[WGRAD_WAVES][64][4];
   __shared__ bool last;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
   const int tile = blockIdx.x % ntiles;
   const int tap = tile % T2, kd = tap / K, kh = tap % K;
   const int ci_tiles = (c.Ci + 15) / 16, ct = tile / T2;
-  const int co = (ct / ci_tiles) * 16 + r, ci = (ct % ci_tiles) * 16 + r;
+  const int co0 = (ct / ci_tiles) * 16, ci0 = (ct % ci_tiles) * 16;
+  const int co = co0 + r, ci = ci0 + r;
   const bool von = co < c.Co, xon = ci < c.Ci;
   const int P = c.Do * c.Ho * c.Wo;
   const size_t vol = (size_t)c.D * c.H * c.W;
-  const bool bias = db && tap == 0 && ct % ci_tiles == 0;
-  // operands of one chunk: g (per tap: zero where the output lacks it), x, and
-  // the sum of g over the lane's outputs
-  auto load = [&](int n, int pc, float (&g)[K][4], float (&v)[K][4], float& gs) {
-    const int p = pc * 16 + 4 * q;
-    const unsigned pp = (unsigned)min(p, P - 1), row = div_by(pp, dWo);
+  const int cor = min(co, c.Co - 1), cir = min(ci, c.Ci - 1);   // rows past the last are not stored
+  const float* const mask = relu ? y : dy;
+  const bool bias = db && tap == 0 && ci0 == 0;
+  const long long total = (long long)c.N * P, chunks = (total + 15) / 16;
+  auto load = [&](int n, int p, bool on, int kw) {   // on: output p of sample n exists; kw: first tap
+    WgradChunk<SW, KT> k;
+    const unsigned pp = on ? (unsigned)p : 0u, row = div_by(pp, dWo);
+    if (!on) n = 0;
     int ow = (int)(pp - row * c.Wo);
     const unsigned od_ = div_by(row, dHo);
     int od = (int)od_, oh = (int)(row - od_ * c.Ho);
-    const float* gn = dy + ((size_t)n * c.Co + co) * P;
-    const float* yn = y + ((size_t)n * c.Co + co) * P;
-    const float* xn = x + ((size_t)n * c.Ci + ci) * vol;
     if constexpr (SW == 0) {
-      gs = 0.0f;
+      int pj = (int)pp;
+      const long long left = total - ((long long)n * P + pj);   // outputs from here on
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int id = od * c.sd + kd - pad, ih = oh * c.sh + kh - pad;
-        const bool row_in = p + j < P && id >= 0 && id < c.D && ih >= 0 && ih < c.H;
-        const float e = von && p + j < P ? pre_grad(gn, yn, relu, p + j) : 0.0f;
-        gs += e;
+        const bool here = on && j < left, row_in = here && id >= 0 && id < c.D && ih >= 0 && ih < c.H;
+        const size_t o = ((size_t)n * c.Co + co) * P;
+        k.e[j] = here && von ? pre_grad(dy + o, y + o, relu, pj) : 0.0f;
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-          const int iw = ow * c.sw + k - pad;
+        for (int i = 0; i < KT; ++i) {
+          const int iw = ow * c.sw + kw + i - pad;
           const bool in = row_in && iw >= 0 && iw < c.W;
-          g[k][j] = in ? e : 0.0f;
-          v[k][j] = in && xon ? xn[((size_t)id * c.H + ih) * c.W + iw] : 0.0f;
+          k.g[i][j] = in ? k.e[j] : 0.0f;
+          k.v[i][j] = in && xon ? x[((size_t)n * c.Ci + ci) * vol + ((size_t)id * c.H + ih) * c.W + iw] : 0.0f;
         }
+        ++pj;
         if (++ow == c.Wo) {
           ow = 0;
           if (++oh == c.Ho) {
             oh = 0;
-            ++od;
+            if (++od == c.Do) {
+              od = 0;
+              pj = 0;
+              n = min(n + 1, c.N - 1);
+            }
           }
         }
       }
@@ -270,134 +301,202 @@ conv3d_wgrad_kernel(ConvShape c, const float* __restrict__ dy, const float* __re
       // Wo a multiple of 4: the four outputs share a row; their strip of x is
       // [SW ow - 1, SW ow + 4 SW], all inside the row but for the ends below
       const int id = od * c.sd + kd - pad, ih = oh * c.sh + kh - pad;
-      const bool in = p < P && id >= 0 && id < c.D && ih >= 0 && ih < c.H;
-      v4f t = {0, 0, 0, 0}, m = {1, 1, 1, 1}, x0 = {0, 0, 0, 0}, x1 = {0, 0, 0, 0};
-      float el = 0.0f, er = 0.0f;
-      const bool hl = pad && ow > 0, hr = pad && SW == 1 && ow + 4 < c.W;   // neighbours of the strip
-      if (von && p < P) {
-        t = *(const v4f*)(gn + p);
-        if (relu) m = *(const v4f*)(yn + p);
+      k.on = on;
+      k.in = on && id >= 0 && id < c.D && ih >= 0 && ih < c.H;
+      k.hl = pad && k.in && ow > 0;
+      k.hr = pad && k.in && SW == 1 && ow + 4 < c.W;
+      // every load always, from a place that exists: behind a branch the number
+      // in flight is unknown to the compiler, and each chunk waits for them all
+      const size_t o = ((size_t)n * c.Co + cor) * P + pp;
+      k.t = *(const v4f*)(dy + o);
+      k.m = *(const v4f*)(mask + o);
+      const float* s = x + ((size_t)n * c.Ci + cir) * vol + (k.in ? ((size_t)id * c.H + ih) * c.W + SW * ow : 0);
+      k.x0 = *(const v4f*)s;
+      if (SW == 2) k.x1 = *(const v4f*)(s + 4);
+      if (pad) k.el = s[k.hl ? -1 : 0];
+      if (pad && SW == 1) k.er = s[k.hr ? 4 : 0];
+    }
+    return k;
+  };
+  WgradSlot* const S = SPLIT ? &wgrad_slots[slot] : nullptr;
+  const int t = threadIdx.x;
+  // tap (kw of the pass's first) of an operand pair of a chunk
+  auto operands = [&](const WgradChunk<SW, KT>& k, const float (&e)[4], int kw, int i, int j, float& g, float& v) {
+    if constexpr (SW == 0) {
+      g = k.g[i][j];
+      v = k.v[i][j];
+    } else {
+      const float strip[10] = {k.el, k.x0[0], k.x0[1], k.x0[2], k.x0[3], SW == 2 ? k.x1[0] : k.er,
+                               SW == 2 ? k.x1[1] : 0.0f, SW == 2 ? k.x1[2] : 0.0f, SW == 2 ? k.x1[3] : 0.0f, 0.0f};
+      const int at = KT == 1 ? kw : i;
+      const bool lost = (at < pad && j == 0 && !k.hl) || (SW == 1 && at > pad && j == 3 && !k.hr);
+      g = k.in && !lost ? e[j] : 0.0f;
+      if (KT == K) v = strip[SW * j + i + 1 - pad];
+      else v = at < pad ? strip[SW * j] : (at == pad ? strip[SW * j + 1] : strip[SW * j + 2]);
+      if (!k.in || lost) v = 0.0f;   // what was loaded instead may be no number
+    }
+  };
+#pragma unroll 1
+  for (int kw = 0; kw < K; kw += KT) {
+    // not SPLIT: joined quarters 0 + 2 and 1 + 3 of wave 0
+    v16f even[SPLIT ? 1 : 4], odd[SPLIT ? 1 : 4];
+    float evenb[4], oddb[4];
+#pragma unroll 1
+    for (int turn = 0; turn < (SPLIT ? 1 : 4); ++turn) {
+      const int quarter = SPLIT ? (int)(blockIdx.x / ntiles) : (turn >> 1 | (turn & 1) << 1);   // 0, 2, 1, 3
+      const int cg = quarter + 4 * wave;
+      v16f acc[KT][4] = {};
+      float bsum[4] = {0, 0, 0, 0};
+      // this lane's next output: T = 16 (cg + 16 step) + 4 q
+      long long T = 16LL * cg + 4 * q;
+      int n = (int)(T / P), p = (int)(T - (long long)n * P);
+      const long long steps = (chunks - cg + 15) / 16;
+      auto next = [&]() {
+        const WgradChunk<SW, KT> k = load(n, p, T < total, kw);
+        T += 256;
+        p += 256;
+        if (p >= P) {
+          const unsigned d = div_by((unsigned)p, dP);
+          n += (int)d;
+          p -= (int)(d * P);
+        }
+        return k;
+      };
+      WgradChunk<SW, KT> buf[WGRAD_AHEAD];
+#pragma unroll
+      for (int u = 0; u < WGRAD_AHEAD; ++u) buf[u] = next();
+      for (long long step = 0; step < steps; step += WGRAD_AHEAD) {
+#pragma unroll
+        for (int u = 0; u < WGRAD_AHEAD; ++u) {   // chunks past the last hold zeros
+          const WgradChunk<SW, KT> k = buf[u];
+          buf[u] = next();
+          float e[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if constexpr (SW == 0) e[j] = k.e[j];
+            else e[j] = k.on && (!relu || k.m[j] > 0.0f) ? k.t[j] : 0.0f;
+            bsum[j] += e[j];
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int i = 0; i < KT; ++i) {
+              float g, v;
+              operands(k, e, kw, i, j, g, v);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x1f32(g, v, acc[i][j], 0, 0, 0);
+            }
+        }
       }
-      if (in && xon) {
-        const float* s = xn + ((size_t)id * c.H + ih) * c.W + SW * ow;
-        x0 = *(const v4f*)s;
-        if (SW == 2) x1 = *(const v4f*)(s + 4);
-        if (hl) el = s[-1];
-        if (hr) er = s[4];
+      // the tree's levels 128 and 64: waves 0 + 2 and 1 + 3, then 0 + 1
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sB[wave][lane][j] = bsum[j];
+#pragma unroll
+      for (int i = 0; i < KT; ++i)
+#pragma unroll
+        for (int half = 2; half > 0; half >>= 1) {
+          if (wave >= half && wave < 2 * half)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int o = 0; o < 16; ++o) sAcc[wave - half][lane][16 * j + o] = acc[i][j][o];
+          __syncthreads();
+          if (wave < half)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+              for (int o = 0; o < 16; ++o) acc[i][j][o] += sAcc[wave][lane][16 * j + o];
+          __syncthreads();
+        }
+      if (wave == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bsum[j] = (sB[0][lane][j] + sB[2][lane][j]) + (sB[1][lane][j] + sB[3][lane][j]);
+        if constexpr (SPLIT) {   // agent scope: the quarters cross the caches of the XCDs
+          float (*const part)[WGRAD_ENTRY] = S->part[tile][quarter];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int i = 0; i < KT; ++i)
+#pragma unroll
+              for (int o = 0; o < 16; ++o)
+                __hip_atomic_store(&part[4 * (o >> 2) + j][256 * i + (4 * q + (o & 3)) * 16 + r], acc[i][j][o],
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&part[4 * q + j][256 * K + r], bsum[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            if (turn == 0) {
+              even[j] = acc[0][j];
+              evenb[j] = bsum[j];
+            } else if (turn == 1) {
+              even[j] += acc[0][j];
+              evenb[j] += bsum[j];
+            } else if (turn == 2) {
+              odd[j] = acc[0][j];
+              oddb[j] = bsum[j];
+            } else {
+              even[j] += odd[j] + acc[0][j];
+              evenb[j] += oddb[j] + bsum[j];
+            }
+          }
+        }
+      }
+      __syncthreads();
+    }
+    if constexpr (!SPLIT) {
+      if (wave != 0) continue;
+      // a lane's 16 chains (block q', product j) of four weights, then of its channel's g
+#pragma unroll
+      for (int o = 0; o < 4; ++o) {
+        float v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = (even[j][o] + even[j][o + 8]) + (even[j][o + 4] + even[j][o + 12]);
+        const int row = co0 + 4 * q + o;
+        if (row < c.Co && xon) dw[(((size_t)row * c.Ci + ci) * T2 + tap) * K + kw] = (v[0] + v[2]) + (v[1] + v[3]);
       }
       float e[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) e[j] = m[j] > 0.0f ? t[j] : 0.0f;
-      gs = (e[0] + e[1]) + (e[2] + e[3]);
-      const float strip[10] = {el, x0[0], x0[1], x0[2], x0[3], SW == 2 ? x1[0] : er, x1[1], x1[2], x1[3], 0.0f};
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          v[k][j] = strip[SW * j + k + 1 - pad];
-          const bool lost = (k < pad && j == 0 && !hl) || (SW == 1 && k > pad && j == 3 && !hr);
-          g[k][j] = in && !lost ? e[j] : 0.0f;
-        }
-    }
-  };
-  constexpr int U = K == 1 ? 4 : 2;          // chunks in flight
-  const int t = threadIdx.x;
-  const long long chunks = (long long)c.N * pchunks;
-  WgradSlot* const S = slot < 0 ? nullptr : &wgrad_slots[slot];
-  float dsum[K], gsum = 0.0f;                // this thread's entries of the tile, of db
-#pragma unroll
-  for (int k = 0; k < K; ++k) dsum[k] = 0.0f;
-  const int s0 = S ? (int)(blockIdx.x / ntiles) : 0, s1 = S ? s0 + 1 : nsplit;
-  for (int sp = s0; sp < s1; ++sp) {
-    v4f acc[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] = {0.0f, 0.0f, 0.0f, 0.0f};
-    float bsum = 0.0f;
-    const long long end = chunks * (sp + 1) / nsplit;
-    long long ch = chunks * sp / nsplit + wave;
-    int n = (int)(ch / pchunks), pc = (int)(ch - (long long)n * pchunks);
-    while (ch < end) {
-      float g[U][K][4], v[U][K][4], gs[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (ch < end) {
-          load(n, pc, g[u], v[u], gs[u]);
-          ch += WGRAD_WAVES;
-          pc += WGRAD_WAVES;
-          while (pc >= pchunks) {
-            pc -= pchunks;
-            ++n;
-          }
-        } else {
-          gs[u] = 0.0f;
-#pragma unroll
-          for (int k = 0; k < K; ++k)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) g[u][k][j] = v[u][k][j] = 0.0f;
-        }
+      for (int j = 0; j < 4; ++j) {
+        e[j] = evenb[j] + __shfl_xor(evenb[j], 32);
+        e[j] += __shfl_xor(e[j], 16);
       }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (bias) bsum += gs[u];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-          for (int k = 0; k < K; ++k)
-            acc[k] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[u][k][j], v[u][k][j], acc[k], 0, 0, 0);
-      }
+      if (bias && kw == 0 && q == 0 && von) db[co] = (e[0] + e[2]) + (e[1] + e[3]);
     }
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) sAcc[wave][256 * k + (4 * q + i) * 16 + r] = acc[k][i];
-    sB[wave][lane] = bsum;
-    __syncthreads();
-    float d[K], e = 0.0f;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-      d[k] = 0.0f;
-#pragma unroll
-      for (int wv = 0; wv < WGRAD_WAVES; ++wv) d[k] += sAcc[wv][256 * k + t];
-    }
-    if (t < 16)
-      for (int wv = 0; wv < WGRAD_WAVES; ++wv)
-        for (int j = 0; j < 4; ++j) e += sB[wv][16 * j + t];
-    if (S) {   // agent scope: the shares cross the caches of the XCDs
-      float* const part = S->part[(size_t)tile * nsplit + sp];
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-        __hip_atomic_store(&part[256 * k + t], d[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (t < 16) __hip_atomic_store(&part[256 * K + t], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-#pragma unroll
-      for (int k = 0; k < K; ++k) dsum[k] += d[k];
-      gsum += e;
-    }
-    __syncthreads();
   }
-  if (S) {
+  if constexpr (SPLIT) {
     __threadfence();
     __syncthreads();
-    if (t == 0)
-      last = __hip_atomic_fetch_add(&S->count[tile], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nsplit - 1;
+    if (t == 0) last = __hip_atomic_fetch_add(&S->count[tile], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == 3u;
     __syncthreads();
     if (!last) return;
-#pragma unroll 4
-    for (int sp = 0; sp < nsplit; ++sp) {
-      const float* const part = S->part[(size_t)tile * nsplit + sp];
+    // entry e of the chains: quarters 0 + 2 and 1 + 3, their sum, then the tree over the 16
+    auto join = [&](int e) {
+      float v[16], w[4][16];
 #pragma unroll
-      for (int k = 0; k < K; ++k)
-        dsum[k] += __hip_atomic_load(&part[256 * k + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (t < 16) gsum += __hip_atomic_load(&part[256 * K + t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int k = 0; k < 16; ++k)
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          w[h][k] = __hip_atomic_load(&S->part[tile][h][k][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int k = 0; k < 16; ++k) v[k] = (w[0][k] + w[2][k]) + (w[1][k] + w[3][k]);
+#pragma unroll
+      for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+        for (int k = 0; k < h; ++k) v[k] += v[k + h];
+      return v[0];
+    };
+    const int o = co0 + t / 16, i = ci0 + t % 16;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const float d = join(256 * k + t);
+      if (o < c.Co && i < c.Ci) dw[(((size_t)o * c.Ci + i) * T2 + tap) * K + k] = d;
+    }
+    if (bias && t < 16) {
+      const float e = join(256 * K + t);
+      if (co0 + t < c.Co) db[co0 + t] = e;
     }
     if (t == 0) __hip_atomic_store(&S->count[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  const int o = (ct / ci_tiles) * 16 + t / 16, i = (ct % ci_tiles) * 16 + t % 16;
-  if (o < c.Co && i < c.Ci) {
-#pragma unroll
-    for (int k = 0; k < K; ++k) dw[(((size_t)o * c.Ci + i) * T2 + tap) * K + k] = dsum[k];
-  }
-  if (bias && t < 16 && (ct / ci_tiles) * 16 + t < c.Co) db[(ct / ci_tiles) * 16 + t] = gsum;
 }
 
 // ---- BF16 inference on the matrix cores -----------------------------------

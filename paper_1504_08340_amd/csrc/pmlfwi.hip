@@ -2013,22 +2013,19 @@ fwi_status fwi_conv3d_backward(void* stream, const fwi_conv_shape* shape, const 
   auto on16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
   const bool vec = c.Wo % 4 == 0 && c.sw <= 2 && c.W == c.Wo * c.sw && on16(dy) && (!relu || on16(y)) && on16(x);
   const int sw = vec ? c.sw : 0;
-  const int pchunks = (int)(((long long)c.Do * c.Ho * c.Wo + 15) / 16);
   const long long ntiles = (long long)c.K * c.K * ((c.Co + 15) / 16) * ((c.Ci + 15) / 16);
-  // shares of the outputs per tile: about four workgroups a CU, at least 64
-  // chunks of 16 outputs each, and no more than a slot holds
-  const long long want = std::min({(1024 + ntiles - 1) / ntiles, (long long)c.N * pchunks / 64,
-                                   (long long)WGRAD_ENTRIES / ntiles});
-  const int nsplit = ntiles > WGRAD_TILES || want < 1 ? 1 : (int)want;
-  const int held = nsplit > 1 ? stream_slot(st) : -1, slot = held < WGRAD_SLOTS ? held : -1;
-  const unsigned nb = (unsigned)(ntiles * (slot < 0 ? 1 : nsplit));
-  using WK = void (*)(ConvShape, const float*, const float*, int, const float*, float*, float*, FastDiv, FastDiv, int,
-                      int, int, int);
-  static const WK table[2][3] = {
-      {conv3d_wgrad_kernel<1, 0>, conv3d_wgrad_kernel<1, 1>, conv3d_wgrad_kernel<1, 2>},
-      {conv3d_wgrad_kernel<3, 0>, conv3d_wgrad_kernel<3, 1>, conv3d_wgrad_kernel<3, 2>}};
-  table[c.K == 3][sw]<<<nb, WGRAD_THREADS, 0, st>>>(c, dy, y, relu, x, dw, db, fast_div((unsigned)c.Wo),
-                                                    fast_div((unsigned)c.Ho), pchunks, (int)ntiles, nsplit, slot);
+  const int held = ntiles <= WGRAD_TILES ? stream_slot(st) : -1;
+  const bool split = held >= 0 && held < WGRAD_SLOTS;
+  using WK = void (*)(ConvShape, const float*, const float*, int, const float*, float*, float*, FastDiv, FastDiv,
+                      FastDiv, int, int);
+  static const WK table[2][2][3] = {
+      {{conv3d_wgrad_kernel<1, 0, false>, conv3d_wgrad_kernel<1, 1, false>, conv3d_wgrad_kernel<1, 2, false>},
+       {conv3d_wgrad_kernel<1, 0, true>, conv3d_wgrad_kernel<1, 1, true>, conv3d_wgrad_kernel<1, 2, true>}},
+      {{conv3d_wgrad_kernel<3, 0, false>, conv3d_wgrad_kernel<3, 1, false>, conv3d_wgrad_kernel<3, 2, false>},
+       {conv3d_wgrad_kernel<3, 0, true>, conv3d_wgrad_kernel<3, 1, true>, conv3d_wgrad_kernel<3, 2, true>}}};
+  table[c.K == 3][split][sw]<<<(unsigned)(ntiles * (split ? 4 : 1)), WGRAD_THREADS, 0, st>>>(
+      c, dy, y, relu, x, dw, db, fast_div((unsigned)c.Wo), fast_div((unsigned)c.Ho),
+      fast_div((unsigned)(c.Do * c.Ho * c.Wo)), (int)ntiles, split ? held : 0);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
