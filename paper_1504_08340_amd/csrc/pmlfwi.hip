@@ -432,8 +432,8 @@ int count_faces(const fwi_problem& P, const Geo& g, int d) {
 // Groups of sources whose gradient terms are summed apart (each in accumulators
 // of its own, joined at the end).  A gradient workgroup takes its group's
 // sources one after another, so with few tiles the chip idles while each walks
-// them all: 1001 bricks and 3 sources (36 tiles), FP64, 35.7 us a stage in one
-// group, 19.9 us in three.  Where the tiles alone fill the chip's 256 CUs twice,
+// them all: 1001 bricks and 3 sources (36 tiles), FP64, 24.3 us a stage in one
+// group (and 30.1 us the PML terms), 12.7 us (14.0 us) in three.  Where the tiles alone fill the chip's 256 CUs twice,
 // groups only add accumulator traffic: 32,000 bricks and 4 sources (800 tiles),
 // FP32, 82 us in one group, 87 us in two, 95 us in four.
 constexpr size_t GRAD_WORKGROUPS = 512;

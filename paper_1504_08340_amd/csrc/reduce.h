@@ -7,8 +7,8 @@
 // forms the result and sets the count back, so that the launch needs no second
 // kernel and no clear.  One workgroup streams about 0.1 TB/s, which bounded
 // every inner product of the optimizer: 278,850 entries with weights took
-// 100 us in one workgroup and take 8.5 us in 137 (most of it the launch and
-// the two trees); an L-BFGS iteration's optimizer work (60 of them) 7.15 -> 1.78 ms.
+// 100 us in one workgroup and take 6.9 us in 137 (most of it the launch and
+// the two trees); an L-BFGS iteration's optimizer work (60 of them) 7.15 -> 1.6 ms.
 //
 // Whether nb workgroups or one (walking the parts in turn) carry it out does not
 // change a bit of the result.  A slot belongs to a stream, whose launches do
