@@ -80,6 +80,12 @@ struct ElementArgs {
   double gw;
   double* gacc;           // [ggrp][PG.per_src]
   Part PG;
+  // receivers (forward, FP64 and FP32): workgroups from brec on, grec a source,
+  // write the x1 displacement of Y there as the traces of a step
+  unsigned brec;
+  int grec, nrec, step, nsteps;
+  const int* rec;
+  double* traces;
 };
 
 // Entry i of a table that no kernel writes (tile lists, axis profiles), i the
@@ -872,10 +878,19 @@ __device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementAr
   if (c.live) add_gradient<BZ>(g, A.PG, c, cz, A.gw, gl, gm, A.gacc + (size_t)grp * A.PG.per_src);
 }
 
+// Traces of a step: tr (source, step) at receiver r from the displacements U.
+template <typename R>
+__device__ __forceinline__ void record_traces(const R* U, int sn, const int* rec, int nrec, int r, double* tr) {
+  const int node = rec[r];
+  for (int d = 0; d < 3; ++d) tr[3 * (size_t)r + d] = (double)U[u_at(sn, d, node)];
+}
+
 // The launch: 1D grid; first the gradient part (with GRAD; it walks the
 // sources and runs longest), then the stiffness, S-rows and u-rows.  Every
 // part's share is a multiple of 8 workgroups, so workgroup b runs on XCD
-// b mod 8 and each XCD walks a contiguous run of tiles.
+// b mod 8 and each XCD walks a contiguous run of tiles.  The first launch of a
+// forward step also records the traces of the step before, whose end is its
+// input: a launch of their own took 2.4 us of a step's 51 at 256 bricks in FP32.
 template <typename R, int TX, int TY, int TZ, bool ADJ, bool GRAD>
 __global__ void __launch_bounds__((TileDims<TX, TY, TZ>::THREADS), (GRAD ? (sizeof(R) == 4 ? 3 : 2) : 1))
 element_kernel(Geo g, ElementArgs<R> A) {
@@ -891,6 +906,16 @@ element_kernel(Geo g, ElementArgs<R> A) {
       return;
     }
     b -= A.ggint * A.ggrp;
+  }
+  if constexpr (!ADJ) {
+    if (blockIdx.x >= A.brec) {
+      b -= (int)A.brec;
+      const int src = b / A.grec, r = (b - src * A.grec) * D::THREADS + threadIdx.x;
+      if (r < A.nrec)
+        record_traces<R>(A.Y + (size_t)src * A.ystride, g.sn, A.rec, A.nrec, r,
+                         A.traces + ((size_t)src * (A.nsteps + 1) + A.step) * A.nrec * 3);
+      return;
+    }
   }
   if (b < A.gint * A.nsrc) {
     const int src = b / A.gint;

@@ -515,10 +515,7 @@ __global__ void receivers_kernel(const R* __restrict__ X, long long reg, int sn,
                                  int step, int nsteps) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x, src = blockIdx.y;
   if (r >= nrec) return;
-  const R* U = X + (size_t)src * reg;
-  double* T = traces + ((size_t)src * (nsteps + 1) + step) * nrec * 3 + (size_t)r * 3;
-  const int node = rec[r];
-  for (int d = 0; d < 3; ++d) T[d] = (double)U[u_at(sn, d, node)];
+  record_traces<R>(X + (size_t)src * reg, sn, rec, nrec, r, traces + ((size_t)src * (nsteps + 1) + step) * nrec * 3);
 }
 
 // Adjoint impulse after a reverse step: y2_u += M^{-1} dt w_n (u^n - u_m^n) at receivers.
@@ -937,6 +934,8 @@ struct Run {
   hipStream_t st;
   Layout L;
   char* ws;
+  double* due = nullptr;   // traces whose step due_step the next forward element launch records (0: none)
+  int due_step = 0;
   const Geo& g() const { return p->g; }
   R* lam() const { return (R*)(ws + L.off_lam); }
   R* mu() const { return (R*)(ws + L.off_mu); }
@@ -1078,8 +1077,16 @@ struct Run {
     return FWI_OK;
   }
 
-  void launch_elements(bool adj, bool grad, const ElementArgs<R>& A, hipStream_t s) {
-    const unsigned nb = (unsigned)(A.ggint * A.ggrp + (A.gint + 2 * A.gpml) * A.nsrc);
+  void launch_elements(bool adj, bool grad, ElementArgs<R>& A, hipStream_t s) {
+    unsigned nb = (unsigned)(A.ggint * A.ggrp + (A.gint + 2 * A.gpml) * A.nsrc);
+    A.brec = nb;
+    if (!adj && due_step > 0) {
+      A.grec = (int)blocks(p->nrec, TileDims<TX, TY, TZ>::THREADS);
+      A.nrec = p->nrec; A.rec = p->d_rec;
+      A.traces = due; A.step = due_step; A.nsteps = p->prob.nsteps;
+      due_step = 0;
+      nb += (unsigned)(A.grec * A.nsrc);
+    }
     constexpr int th = TileDims<TX, TY, TZ>::THREADS;
     if (grad) element_kernel<R, TX, TY, TZ, true, true><<<nb, th, 0, s>>>(g(), A);
     else if (adj) element_kernel<R, TX, TY, TZ, true, false><<<nb, th, 0, s>>>(g(), A);
@@ -1205,7 +1212,12 @@ struct Run {
                                   (size_t)P.nsrc * L.reg_elems * L.es, hipMemcpyDeviceToDevice, st));
       if ((e = step(false, 0, n, wav, keep_all ? n : -1, n + 1 < P.nsteps, -1)) != FWI_OK)
         return e;
-      if (p->nrec > 0) {
+      // the next step's first launch records the traces, but for the last step
+      // and the matrix-core precisions, which launch by parts
+      if (p->nrec > 0 && n + 1 < P.nsteps && (P.precision == FWI_FP64 || P.precision == FWI_FP32)) {
+        due = traces;
+        due_step = n + 1;
+      } else if (p->nrec > 0) {
         receivers_kernel<R><<<dim3(blocks(p->nrec, 128), P.nsrc), 128, 0, st>>>(
             reg(0), (long long)L.reg_elems, g().sn, p->d_rec, p->nrec, traces, n + 1, P.nsteps);
         HIP_TRY(p, hipGetLastError());

@@ -80,3 +80,22 @@ def test_gradient_of_several_sources_is_the_sum_of_each(P, ne, full):
             assert all(np.abs(a).max() > 0 and rel_l2(a, b) <= 1e-12 for a, b in zip(g, want))
         else:
             want = g if want is None else [a + b for a, b in zip(want, g)]
+
+
+@pytest.mark.parametrize("nrec", [1, 127, 128, 129, 169])
+def test_traces_do_not_depend_on_the_number_of_receivers(P, nrec):
+    """Receivers are recorded by workgroups of 128 of the next step's first launch, the
+    last step's by a launch of its own: every step's traces against a solver that
+    holds the receivers in another order, bit for bit."""
+    wl = W.tiny(ne_int=(6, 6, 2), npml_side=1, npml_bottom=1, nsteps=5, nsrc=2, seed=3)
+    assert len(wl.rec_node) == 169
+    order = np.random.default_rng(nrec).permutation(169)
+    for precision in (P.FWI_FP64, P.FWI_FP32):
+        got = []
+        for rec in (wl.rec_node[:nrec], wl.rec_node[order]):
+            S = P.Solver(wl.prob, wl.src_node, wl.src_dir, np.ascontiguousarray(rec), precision=precision)
+            got.append(S.forward(*(S.tensor(a) for a in (wl.rho, wl.lam, wl.mu, wl.wavelet))).cpu().numpy())
+            S.close()
+        back = np.argsort(order)[:nrec]
+        assert got[0].shape == (2, 6, nrec, 3) and np.array_equal(got[0], got[1][:, :, back])
+        assert all(np.abs(got[1][:, k]).max() > 0 for k in range(1, 6))
