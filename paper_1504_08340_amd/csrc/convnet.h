@@ -554,10 +554,12 @@ conv3d_bf16_mfma_kernel(ConvShape c, const unsigned short* __restrict__ x, const
       }
     } else {
       const int per_row = 16 * groups * T3;
+      // rows past the last stay as they are: nothing of them is stored (32 rows of 16
+      // channels cost a narrow layer more than its products)
 #pragma unroll 8
-      for (int i = threadIdx.x; i < ROWS * per_row; i += CONV_THREADS) {
+      for (int i = threadIdx.x; i < rows * per_row; i += CONV_THREADS) {
         const int row = i / per_row, e = i - row * per_row, ci = e / T3, t = e - ci * T3;
-        sA[(t * ROWS + row) * LC + ci] = ci < cn && row < rows ? wc[(size_t)row * c.Ci * T3 + e] : (unsigned short)0;
+        sA[(t * ROWS + row) * LC + ci] = ci < cn ? wc[(size_t)row * c.Ci * T3 + e] : (unsigned short)0;
       }
     }
     const unsigned short* xn = x + ((size_t)n * c.Ci + c0 + 8 * h) * vol;
