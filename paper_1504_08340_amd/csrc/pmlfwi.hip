@@ -2007,7 +2007,8 @@ fwi_status fwi_conv3d_forward_bf16(void* stream, const fwi_conv_shape* shape, co
   if (!conv_shape(shape, c) || !x || !w || !y) return FWI_ERR_ARG;
   const long long P = (long long)c.Do * c.Ho * c.Wo;
   if (c.N > 65535) return FWI_ERR_ARG;
-  const dim3 grid((unsigned)((P + 31) / 32), (unsigned)c.N, (unsigned)((c.Co + 31) / 32));
+  const int span = c.K == 3 ? 32 : 128;   // positions a workgroup
+  const dim3 grid((unsigned)((P + span - 1) / span), (unsigned)c.N, (unsigned)((c.Co + 31) / 32));
   (c.K == 3 ? conv3d_bf16_mfma_kernel<3> : conv3d_bf16_mfma_kernel<1>)<<<grid, CONV_THREADS, 0, (hipStream_t)stream>>>(
       c, (const unsigned short*)x, (const unsigned short*)w, b, relu, out_fp32,
       c.Ci % 8 == 0 && ((uintptr_t)w & 15) == 0, y);   // rows of weights start on 16 bytes
