@@ -40,14 +40,17 @@
  * Ownership: the caller allocates every array and the workspace (size from
  * fwi_query) and keeps them alive while work is enqueued.  A plan owns its
  * host metadata and a few KB of device metadata (brick tiles, source and
- * receiver tables, misfit partial sums) and a second stream with two events,
- * all created by fwi_plan_create and released by fwi_plan_destroy; the solves
- * allocate nothing.  All work is enqueued on the given stream (a hipStream_t,
- * passed as void*; NULL is the default stream).  The host waits for the
+ * receiver tables, partial values of the misfit and of the model check) and a
+ * second stream with two events, all created by fwi_plan_create and released
+ * by fwi_plan_destroy; the solves allocate nothing.  All work is enqueued on
+ * the given stream (a hipStream_t, passed as void*; NULL is the default
+ * stream).  On one plan a misfit may run on one stream beside a solve or a
+ * model check on another; two misfits, or two solves, must not overlap in
+ * time (they share the plan's partial sums and events).  The host waits for the
  * device only in fwi_plan_create (one upload), fwi_check_model, the model
  * check that fwi_forward, fwi_adjoint_gradient and fwi_adjoint_gradient_appb
- * run before their first launch (one small kernel, a 40-byte copy and a
- * synchronization of the stream), and fwi_timing_read.
+ * run before their first launch (one or two small kernels, a 40-byte copy and
+ * a synchronization of the stream), and fwi_timing_read.
  *
  * Errors: every call returns fwi_status; nothing throws across the ABI.  On
  * error no work has been enqueued (argument errors) or the HIP error is

@@ -186,7 +186,10 @@ struct fwi_plan {
   // mu = 0 and lam = 0, mu = 1 (stability bound of fwi_check_model)
   double c_lam = 0.0, c_mu = 0.0;
   double* d_info = nullptr;   // 8 doubles: model check [0, 5), power iteration [5, 8)
-  double* d_partials = nullptr;   // MISFIT_BLOCKS doubles: per-workgroup misfit sums
+  // per-workgroup values; two buffers, because a misfit on one stream may run
+  // beside a check (which a solve makes too) on another
+  double* d_partials = nullptr;   // MISFIT_BLOCKS doubles: misfit sums
+  double* d_check = nullptr;      // CHECK_PARTIALS doubles: model check, then power iteration
   double* h_info = nullptr;       // 8 doubles of pinned host memory: copy of d_info
   int device = 0;                 // device current at fwi_plan_create
   Schedule sched;                 // checkpoint schedule (ckpt_every > 0)
@@ -707,7 +710,8 @@ __global__ void gradient_reduce_kernel(Geo g, const double* __restrict__ gacc, P
 // at 138,000 material nodes; over CHECK_BLOCKS workgroups both launches take
 // about 15 us.
 constexpr int CHECK_BLOCKS = 256;
-static_assert(5 * CHECK_BLOCKS <= MISFIT_BLOCKS, "the partials fit the plan's buffer");
+constexpr int CHECK_PARTIALS = 2048;
+static_assert(5 * CHECK_BLOCKS <= CHECK_PARTIALS, "the partials fit the plan's buffer");
 
 __device__ __forceinline__ void check_tree(double v[5], double* __restrict__ out) {
   __shared__ double red[5][256];
@@ -1356,13 +1360,13 @@ struct Run {
     double* state = p->d_info + 5;
     power_init_kernel<R><<<blocks(G.n_nodes, 256), 256, 0, st>>>(G, reg(0), state);
     HIP_TRY(p, hipGetLastError());
-    const int nb = (int)std::min<size_t>(blocks(G.n_nodes, 256), MISFIT_BLOCKS / 3);
+    const int nb = (int)std::min<size_t>(blocks(G.n_nodes, 256), CHECK_PARTIALS / 3);
     for (int it = 0; it < iters; ++it) {
       R* X = reg(it & 1);
       R* Y = reg((it + 1) & 1);
       if ((e = elements(false, X, nullptr, 0.0, true)) != FWI_OK) return e;
-      power_step_kernel<R><<<nb, 256, 0, st>>>(G, X, Y, res(), L.part, rho, it == 0, state, p->d_partials);
-      power_reduce_kernel<<<1, 256, 0, st>>>(p->d_partials, nb, state);
+      power_step_kernel<R><<<nb, 256, 0, st>>>(G, X, Y, res(), L.part, rho, it == 0, state, p->d_check);
+      power_reduce_kernel<<<1, 256, 0, st>>>(p->d_check, nb, state);
       HIP_TRY(p, hipGetLastError());
     }
     return FWI_OK;
@@ -1403,8 +1407,8 @@ fwi_status dispatch(fwi_plan* p, hipStream_t st, void* ws, F&& f, bool keep = tr
 fwi_status check_model(fwi_plan* p, hipStream_t st, const double* rho, const double* lam, const double* mu,
                        double* info, const char* who, void* ws = nullptr, bool keep = true) {
   const int nb = std::min((int)blocks(p->g.n_int, 256), CHECK_BLOCKS);
-  model_check_kernel<<<nb, 256, 0, st>>>(p->g, rho, lam, mu, p->c_lam, p->c_mu, nb == 1 ? p->d_info : p->d_partials);
-  if (nb > 1) model_check_final_kernel<<<1, 256, 0, st>>>(p->d_partials, nb, p->d_info);
+  model_check_kernel<<<nb, 256, 0, st>>>(p->g, rho, lam, mu, p->c_lam, p->c_mu, nb == 1 ? p->d_info : p->d_check);
+  if (nb > 1) model_check_final_kernel<<<1, 256, 0, st>>>(p->d_check, nb, p->d_info);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(p->h_info, p->d_info, 5 * sizeof(double), hipMemcpyDeviceToHost, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
@@ -1604,6 +1608,10 @@ fwi_status fwi_plan_create(const fwi_problem* prob, const int32_t* src_node, con
     what = "misfit partial sums";
     e = hipMalloc((void**)&p->d_partials, MISFIT_BLOCKS * sizeof(double));
   }
+  if (e == hipSuccess) {
+    what = "model-check partial values";
+    e = hipMalloc((void**)&p->d_check, CHECK_PARTIALS * sizeof(double));
+  }
   // the stream the interior bricks run on beside the PML bricks, and its
   // fork / join events (created here so that the solves allocate nothing)
   if (e == hipSuccess) {
@@ -1772,6 +1780,7 @@ fwi_status fwi_plan_destroy(fwi_plan* p) {
   (void)hipFree(p->d_fo);
   (void)hipFree(p->d_info);
   (void)hipFree(p->d_partials);
+  (void)hipFree(p->d_check);
   if (p->h_info) (void)hipHostFree(p->h_info);
   delete p;
   return FWI_OK;
