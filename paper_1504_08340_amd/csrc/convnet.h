@@ -8,6 +8,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "mfma.h"
 #include "reduce.h"
 
@@ -42,6 +44,9 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 // product with 16 or 32 rows.  FP32 products are FP32 MFMA, never a split.
 
 constexpr int CONV_THREADS = 256;   // 4 waves
+// Most positions of a sample that 32-bit position arithmetic covers, the tiles'
+// and chunks' overhang included; beyond them it is done in 64 bits.
+constexpr long long CONV_NARROW = (1LL << 31) - 512;
 
 // g = dL/d(pre-activation) from dL/dy and, with ReLU, the activated output y.
 __device__ __forceinline__ float pre_grad(const float* dy, const float* y, int relu, long long i) {
@@ -195,307 +200,237 @@ conv3d_f32_kernel(ConvShape c, const float* __restrict__ src, const float* __res
 // and the chains are joined in a tree (chain t and t + 128, then t + 64, ..).  As
 // in the forward pass the order is part of the result: an update that differs in
 // the last bit of a few weights can turn a ReLU mask of the next step.
-// A workgroup of 4 waves takes a tile (taps (kd, kh) with all kw, 16 output and 16
-// input channels) and a quarter of the chains, a wave 16 of them, on the one-product MFMA form
-// 16x16x1 in four blocks: block q and the step's product j hold chain
-// 16 cg + 4 q + j.  So a lane loads four neighbouring outputs of its channel at
-// once, which serve 4 K products, and with SW = 1 or 2 (the w stride; extents and
-// pointers allow vector loads) so does one strip of x; SW = 0: any shape, element
-// by element.  The
-// next WGRAD_AHEAD chunks of 16 outputs are in flight during the products of the
-// ones before.  The first two levels of the tree join the waves, in LDS; the
-// quarters meet in the stream's slot, where the last of a tile to arrive joins
-// them.  Without a slot, or with more tiles than one holds (then tiles enough to
-// fill the chip), one workgroup takes a tile's taps and quarters in turn (SPLIT =
-// false): the same bits.
-// The workgroups of taps (0, 0) and input channel 0 also sum g.
-// Of the network's training step at batch 8 this takes 0.67 ms; one workgroup
-// per weight walking all outputs, in the same order, took 13.0 ms with the bias
-// sums.  Eight chunks ahead, or the loads by neighbouring lanes and an exchange
-// through LDS, measured no faster, one tap instead of three to a wave slower
-// (0.86 ms); products of four outputs each (16x16x4, another order) took 0.77 ms.
-constexpr int WGRAD_THREADS = 256, WGRAD_WAVES = WGRAD_THREADS / 64, WGRAD_AHEAD = 4;
-constexpr int WGRAD_SLOTS = 4;              // streams that may hold a slot (per device)
-constexpr int WGRAD_TILES = 48;             // most tiles of a split launch
-constexpr int WGRAD_ENTRY = 3 * 256 + 16;   // sums of one chain: a tile's weights, its channels' g
-struct WgradSlot {
-  float part[WGRAD_TILES][4][16][WGRAD_ENTRY];
-  unsigned count[WGRAD_TILES];
-};
-static __device__ WgradSlot wgrad_slots[WGRAD_SLOTS];   // counts start at 0
+// A workgroup takes the K taps of one row (kd, kh) of 4 T output and 4 T input
+// channels and all 256 chains, a wave 64 of them, on the one-product MFMA form
+// 4x4x1 in 16 blocks: lane 4 b + i holds channel i of four for block b, and each of
+// a step's four products is one output of 64 chains.  With SW = 1 or 2 (the w stride;
+// extents and pointers allow vector loads) a lane's four outputs are neighbours,
+// one vector of dL/dy, and their strip of x serves all K taps; SW = 0: any shape,
+// the outputs 64 apart, element by element.  Where the places lie is worked out once
+// for the four lanes of a quad and four steps (SW = 0: one step).  Neither the waves
+// nor the workgroups wait for one another before the tree, which is joined in LDS,
+// so a launch needs no memory but its operands and runs alike on every stream and
+// in a captured graph.
+// Bound by the loads: an operand serves 4 T rows, and channels a power of two apart
+// fall on the same channel of the L2 (products alone: 12 us of 109 at 32 x 32
+// channels and 8 x 16 x 16 x 16 outputs).  The network's training step at batch 8
+// takes 0.63 ms here; one workgroup per weight walking all outputs, in the same
+// order, took 12.9 ms.  16 x 16 channels and all chains of one tap in a workgroup of
+// 16 waves, operands shared through LDS: 98 us, but 497 us where 9 x 32 channels
+// leave 54 workgroups (here 240).
+// The workgroups of the first row and input channel 0 also sum g.
+constexpr int WGRAD_THREADS = 256;
 
-// One chunk of a lane: four outputs of channel co, and their strip of x or (SW =
-// 0) their places in x for each tap.
-template <int SW, int KT>
-struct WgradChunk {
-  v4f t, m;                 // dL/dy, and the activated output (ReLU) or 1
-  v4f x0, x1;               // strip of x
-  float el, er;             // its neighbours
-  bool on, in, hl, hr;      // the outputs exist; the taps' row does; the neighbours do
-};
-template <int KT>
-struct WgradChunk<0, KT> {
-  v4f e, g[KT], v[KT];      // g, g where the output has the tap, x there
-};
-
-template <int K, int SW, bool SPLIT>
-__global__ void __launch_bounds__(WGRAD_THREADS, 1)
-conv3d_wgrad_kernel(ConvShape c, const float* __restrict__ dy, const float* __restrict__ y, int relu,
+// WIDE: offsets in 64 bits (32 while both tensors have at most 2^30 entries).
+template <int K, int T, int SW, bool WIDE, bool RELU>
+__global__ void __launch_bounds__(WGRAD_THREADS, T == 1 ? 3 : 1)
+conv3d_wgrad_kernel(ConvShape c, const float* __restrict__ dy, const float* __restrict__ y,
                     const float* __restrict__ x, float* __restrict__ dw, float* __restrict__ db, FastDiv dWo,
-                    FastDiv dHo, FastDiv dP, int ntiles, int slot) {
-  constexpr int T2 = K * K, pad = K / 2;
-  constexpr int KT = SPLIT ? K : 1;          // taps along w at a time
-  __shared__ float sAcc[2][64][64 + 1];      // two waves' accumulators, a lane's 64 to a row
-  __shared__ float sB[WGRAD_WAVES][64][4];
-  __shared__ bool last;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r = lane & 15, q = lane >> 4;
-  const int tile = blockIdx.x % ntiles;
-  const int tap = tile % T2, kd = tap / K, kh = tap % K;
-  const int ci_tiles = (c.Ci + 15) / 16, ct = tile / T2;
-  const int co0 = (ct / ci_tiles) * 16, ci0 = (ct % ci_tiles) * 16;
-  const int co = co0 + r, ci = ci0 + r;
-  const bool von = co < c.Co, xon = ci < c.Ci;
-  const int P = c.Do * c.Ho * c.Wo;
-  const size_t vol = (size_t)c.D * c.H * c.W;
-  const int cor = min(co, c.Co - 1), cir = min(ci, c.Ci - 1);   // rows past the last are not stored
-  const float* const mask = relu ? y : dy;
-  const bool bias = db && tap == 0 && ci0 == 0;
-  const long long total = (long long)c.N * P, chunks = (total + 15) / 16;
-  auto load = [&](int n, int p, bool on, int kw) {   // on: output p of sample n exists; kw: first tap
-    WgradChunk<SW, KT> k;
-    const unsigned pp = on ? (unsigned)p : 0u, row = div_by(pp, dWo);
-    if (!on) n = 0;
-    int ow = (int)(pp - row * c.Wo);
-    const unsigned od_ = div_by(row, dHo);
-    int od = (int)od_, oh = (int)(row - od_ * c.Ho);
-    if constexpr (SW == 0) {
-      int pj = (int)pp;
-      const long long left = total - ((long long)n * P + pj);   // outputs from here on
+                    FastDiv dHo, FastDiv dP) {
+  using I = std::conditional_t<WIDE, long long, int>;
+  using O = std::conditional_t<WIDE, unsigned long long, unsigned>;
+  constexpr int T3 = K * K * K, pad = K / 2, AHEAD = SW ? 4 : 2;   // steps in flight
+  __shared__ float sh[4][16][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = lane >> 2, i = lane & 3;
+  const int co_tiles = (c.Co + 4 * T - 1) / (4 * T), ci_tiles = (c.Ci + 4 * T - 1) / (4 * T);
+  const int co0 = 4 * T * (blockIdx.x % co_tiles), rest = blockIdx.x / co_tiles;
+  const int ci0 = 4 * T * (rest % ci_tiles), kd = rest / ci_tiles / K, kh = rest / ci_tiles % K;
+  const I P = (I)c.Do * c.Ho * c.Wo, vol = (I)c.D * c.H * c.W;
+  // rows past the last repeat it and are not stored
+  O lo[T], li[T];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int id = od * c.sd + kd - pad, ih = oh * c.sh + kh - pad;
-        const bool here = on && j < left, row_in = here && id >= 0 && id < c.D && ih >= 0 && ih < c.H;
-        const size_t o = ((size_t)n * c.Co + co) * P;
-        k.e[j] = here && von ? pre_grad(dy + o, y + o, relu, pj) : 0.0f;
+  for (int h = 0; h < T; ++h) {
+    lo[h] = 4 * (O)(min(co0 + 4 * h + i, c.Co - 1) * P);
+    li[h] = 4 * (O)(min(ci0 + 4 * h + i, c.Ci - 1) * vol);
+  }
+  const bool bias = db && kd == 0 && kh == 0 && ci0 == 0;
+  const long long total = (long long)c.N * P, steps = (total + 255) / 256;
+  // byte offsets of an output in dL/dy and of its place in x at the middle tap, both
+  // from channel 0, and flags: the output exists, the row of taps does; the places
+  // left and right of it (of its strip) do
+  enum : unsigned { ON = 1, IN = 2, LEFT = 1, RIGHT = 2 };
+  struct Place {
+    O o, i;
+  };
+  auto place = [&](long long t) {
+    const bool on = t < total;
+    const I at = on ? (I)t : 0;
+    auto over = [](I v, FastDiv f, I d) { return WIDE ? v / d : (I)div_by((unsigned)v, f); };
+    const I n = over(at, dP, P), p = at - n * P, row = over(p, dWo, c.Wo), od = over(row, dHo, c.Ho);
+    const I id = od * c.sd + kd - pad, ih = (row - od * c.Ho) * c.sh + kh - pad, iw = (p - row * c.Wo) * c.sw;
+    const bool in = on && id >= 0 && id < c.D && ih >= 0 && ih < c.H;
+    Place s;
+    s.o = (on ? 4 * (O)(n * c.Co * P + p) | ON : 0) | (in ? IN : 0);
+    s.i = in ? 4 * (O)(n * c.Ci * vol + (id * c.H + ih) * c.W + iw) | (iw > 0 ? LEFT : 0) |
+                   (iw + (SW ? 4 * SW : 1) < c.W ? RIGHT : 0)
+             : 0;
+    return s;
+  };
+  auto of_quad = [](O v, auto k) {   // lane 4 b + k's value
+    constexpr int q = decltype(k)::value * 0x55;
+    O r = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)v, q, 0xf, 0xf, true);
+    if constexpr (WIDE) r |= (O)(unsigned)__builtin_amdgcn_update_dpp(0, (int)(v >> 32), q, 0xf, 0xf, true) << 32;
+    return r;
+  };
+  auto at = [](const float* base, O o) { return (const float*)((const char*)base + o); };
+  struct Chunk {             // four outputs of a lane: dL/dy, activated output, x at their taps, flags
+    v4f t[T], m[T];
+    v4f x0[T], x1[T];        // SW: the strip; SW = 0: the middle taps,
+    v4f l[T], r[T];          // left and right of it (SW: l[0], r[0])
+    unsigned f[SW ? 1 : 4];
+  };
+  // a step's loads: every one always, from a place that exists (behind a branch
+  // the number in flight is unknown to the compiler, and each step waits for all)
+  auto load = [&](Place s, auto k_) {
+    Chunk k;
+    if constexpr (SW != 0) {   // places of four steps, a quad's lanes one each
+      const O so = of_quad(s.o, k_), si = of_quad(s.i, k_);
+      k.f[0] = (unsigned)(so & 3) | (unsigned)(si & 3) << 2;
 #pragma unroll
-        for (int i = 0; i < KT; ++i) {
-          const int iw = ow * c.sw + kw + i - pad;
-          const bool in = row_in && iw >= 0 && iw < c.W;
-          k.g[i][j] = in ? k.e[j] : 0.0f;
-          k.v[i][j] = in && xon ? x[((size_t)n * c.Ci + ci) * vol + ((size_t)id * c.H + ih) * c.W + iw] : 0.0f;
-        }
-        ++pj;
-        if (++ow == c.Wo) {
-          ow = 0;
-          if (++oh == c.Ho) {
-            oh = 0;
-            if (++od == c.Do) {
-              od = 0;
-              pj = 0;
-              n = min(n + 1, c.N - 1);
-            }
-          }
-        }
+      for (int h = 0; h < T; ++h) {
+        const O o = (so & ~(O)3) + lo[h], p = (si & ~(O)3) + li[h];
+        k.t[h] = *(const v4f*)at(dy, o);
+        if (RELU) k.m[h] = *(const v4f*)at(y, o);
+        k.x0[h] = *(const v4f*)at(x, p);
+        if (SW == 2) k.x1[h] = *(const v4f*)at(x, p + 16);
+        if (K > 1) k.l[h][0] = *at(x, p - (si & LEFT ? 4 : 0));
+        if (K > 1 && SW == 1) k.r[h][0] = *at(x, p + (si & RIGHT ? 16 : 0));
       }
-    } else {
-      // Wo a multiple of 4: the four outputs share a row; their strip of x is
-      // [SW ow - 1, SW ow + 4 SW], all inside the row but for the ends below
-      const int id = od * c.sd + kd - pad, ih = oh * c.sh + kh - pad;
-      k.on = on;
-      k.in = on && id >= 0 && id < c.D && ih >= 0 && ih < c.H;
-      k.hl = pad && k.in && ow > 0;
-      k.hr = pad && k.in && SW == 1 && ow + 4 < c.W;
-      // every load always, from a place that exists: behind a branch the number
-      // in flight is unknown to the compiler, and each chunk waits for them all
-      const size_t o = ((size_t)n * c.Co + cor) * P + pp;
-      k.t = *(const v4f*)(dy + o);
-      k.m = *(const v4f*)(mask + o);
-      const float* s = x + ((size_t)n * c.Ci + cir) * vol + (k.in ? ((size_t)id * c.H + ih) * c.W + SW * ow : 0);
-      k.x0 = *(const v4f*)s;
-      if (SW == 2) k.x1 = *(const v4f*)(s + 4);
-      if (pad) k.el = s[k.hl ? -1 : 0];
-      if (pad && SW == 1) k.er = s[k.hr ? 4 : 0];
+    } else {                   // places of one step, a quad's lanes one output each
+      auto one = [&](auto j_) {
+        constexpr int j = decltype(j_)::value;
+        const O so = of_quad(s.o, j_), si = of_quad(s.i, j_);
+        k.f[j] = (unsigned)(so & 3) | (unsigned)(si & 3) << 2;
+#pragma unroll
+        for (int h = 0; h < T; ++h) {
+          const O o = (so & ~(O)3) + lo[h], p = (si & ~(O)3) + li[h];
+          k.t[h][j] = *at(dy, o);
+          if (RELU) k.m[h][j] = *at(y, o);
+          k.x0[h][j] = *at(x, p);
+          if (K > 1) k.l[h][j] = *at(x, p - (si & LEFT ? 4 : 0));
+          if (K > 1) k.r[h][j] = *at(x, p + (si & RIGHT ? 4 : 0));
+        }
+      };
+      one(std::integral_constant<int, 0>{});
+      one(std::integral_constant<int, 1>{});
+      one(std::integral_constant<int, 2>{});
+      one(std::integral_constant<int, 3>{});
     }
+    __builtin_amdgcn_sched_barrier(0);   // the loads in this order: a step waits for its own only
     return k;
   };
-  WgradSlot* const S = SPLIT ? &wgrad_slots[slot] : nullptr;
-  const int t = threadIdx.x;
-  // tap (kw of the pass's first) of an operand pair of a chunk
-  auto operands = [&](const WgradChunk<SW, KT>& k, const float (&e)[4], int kw, int i, int j, float& g, float& v) {
-    if constexpr (SW == 0) {
-      g = k.g[i][j];
-      v = k.v[i][j];
-    } else {
-      const float strip[10] = {k.el, k.x0[0], k.x0[1], k.x0[2], k.x0[3], SW == 2 ? k.x1[0] : k.er,
-                               SW == 2 ? k.x1[1] : 0.0f, SW == 2 ? k.x1[2] : 0.0f, SW == 2 ? k.x1[3] : 0.0f, 0.0f};
-      const int at = KT == 1 ? kw : i;
-      const bool lost = (at < pad && j == 0 && !k.hl) || (SW == 1 && at > pad && j == 3 && !k.hr);
-      g = k.in && !lost ? e[j] : 0.0f;
-      if (KT == K) v = strip[SW * j + i + 1 - pad];
-      else v = at < pad ? strip[SW * j] : (at == pad ? strip[SW * j + 1] : strip[SW * j + 2]);
-      if (!k.in || lost) v = 0.0f;   // what was loaded instead may be no number
-    }
-  };
-#pragma unroll 1
-  for (int kw = 0; kw < K; kw += KT) {
-    // not SPLIT: joined quarters 0 + 2 and 1 + 3 of wave 0
-    v16f even[SPLIT ? 1 : 4], odd[SPLIT ? 1 : 4];
-    float evenb[4], oddb[4];
-#pragma unroll 1
-    for (int turn = 0; turn < (SPLIT ? 1 : 4); ++turn) {
-      const int quarter = SPLIT ? (int)(blockIdx.x / ntiles) : (turn >> 1 | (turn & 1) << 1);   // 0, 2, 1, 3
-      const int cg = quarter + 4 * wave;
-      v16f acc[KT][4] = {};
-      float bsum[4] = {0, 0, 0, 0};
-      // this lane's next output: T = 16 (cg + 16 step) + 4 q
-      long long T = 16LL * cg + 4 * q;
-      int n = (int)(T / P), p = (int)(T - (long long)n * P);
-      const long long steps = (chunks - cg + 15) / 16;
-      auto next = [&]() {
-        const WgradChunk<SW, KT> k = load(n, p, T < total, kw);
-        T += 256;
-        p += 256;
-        if (p >= P) {
-          const unsigned d = div_by((unsigned)p, dP);
-          n += (int)d;
-          p -= (int)(d * P);
-        }
-        return k;
-      };
-      WgradChunk<SW, KT> buf[WGRAD_AHEAD];
-#pragma unroll
-      for (int u = 0; u < WGRAD_AHEAD; ++u) buf[u] = next();
-      for (long long step = 0; step < steps; step += WGRAD_AHEAD) {
-#pragma unroll
-        for (int u = 0; u < WGRAD_AHEAD; ++u) {   // chunks past the last hold zeros
-          const WgradChunk<SW, KT> k = buf[u];
-          buf[u] = next();
-          float e[4];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if constexpr (SW == 0) e[j] = k.e[j];
-            else e[j] = k.on && (!relu || k.m[j] > 0.0f) ? k.t[j] : 0.0f;
-            bsum[j] += e[j];
-          }
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int i = 0; i < KT; ++i) {
-              float g, v;
-              operands(k, e, kw, i, j, g, v);
-              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x1f32(g, v, acc[i][j], 0, 0, 0);
-            }
-        }
-      }
-      // the tree's levels 128 and 64: waves 0 + 2 and 1 + 3, then 0 + 1
-#pragma unroll
-      for (int j = 0; j < 4; ++j) sB[wave][lane][j] = bsum[j];
-#pragma unroll
-      for (int i = 0; i < KT; ++i)
-#pragma unroll
-        for (int half = 2; half > 0; half >>= 1) {
-          if (wave >= half && wave < 2 * half)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-              for (int o = 0; o < 16; ++o) sAcc[wave - half][lane][16 * j + o] = acc[i][j][o];
-          __syncthreads();
-          if (wave < half)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-              for (int o = 0; o < 16; ++o) acc[i][j][o] += sAcc[wave][lane][16 * j + o];
-          __syncthreads();
-        }
-      if (wave == 0) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bsum[j] = (sB[0][lane][j] + sB[2][lane][j]) + (sB[1][lane][j] + sB[3][lane][j]);
-        if constexpr (SPLIT) {   // agent scope: the quarters cross the caches of the XCDs
-          float (*const part)[WGRAD_ENTRY] = S->part[tile][quarter];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-#pragma unroll
-            for (int i = 0; i < KT; ++i)
-#pragma unroll
-              for (int o = 0; o < 16; ++o)
-                __hip_atomic_store(&part[4 * (o >> 2) + j][256 * i + (4 * q + (o & 3)) * 16 + r], acc[i][j][o],
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&part[4 * q + j][256 * K + r], bsum[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            if (turn == 0) {
-              even[j] = acc[0][j];
-              evenb[j] = bsum[j];
-            } else if (turn == 1) {
-              even[j] += acc[0][j];
-              evenb[j] += bsum[j];
-            } else if (turn == 2) {
-              odd[j] = acc[0][j];
-              oddb[j] = bsum[j];
-            } else {
-              even[j] += odd[j] + acc[0][j];
-              evenb[j] += oddb[j] + bsum[j];
-            }
-          }
-        }
-      }
-      __syncthreads();
-    }
-    if constexpr (!SPLIT) {
-      if (wave != 0) continue;
-      // a lane's 16 chains (block q', product j) of four weights, then of its channel's g
-#pragma unroll
-      for (int o = 0; o < 4; ++o) {
-        float v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = (even[j][o] + even[j][o + 8]) + (even[j][o + 4] + even[j][o + 12]);
-        const int row = co0 + 4 * q + o;
-        if (row < c.Co && xon) dw[(((size_t)row * c.Ci + ci) * T2 + tap) * K + kw] = (v[0] + v[2]) + (v[1] + v[3]);
-      }
-      float e[4];
+  float bsum[T][4] = {};
+  v4f acc[K][T][T][4] = {};
+  auto run = [&](auto bias_) {
+    // a step's products, zeros where the output or its tap is absent (what was
+    // loaded instead may be no number)
+    auto multiply = [&](const Chunk& k) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        e[j] = evenb[j] + __shfl_xor(evenb[j], 32);
-        e[j] += __shfl_xor(e[j], 16);
+        const unsigned f = k.f[SW ? 0 : j];
+        const bool in = f & IN, left = in && (f & LEFT << 2), right = in && (f & RIGHT << 2);
+        bool live[T];
+#pragma unroll
+        for (int h = 0; h < T; ++h) {
+          live[h] = !RELU || k.m[h][j] > 0.0f;
+          if constexpr (decltype(bias_)::value) bsum[h][j] += (f & ON) && live[h] ? k.t[h][j] : 0.0f;
+        }
+#pragma unroll
+        for (int w = 0; w < K; ++w) {
+          const bool has = w < pad && (SW == 0 || j == 0) ? left
+                           : (w > pad && (SW == 0 || (SW == 1 && j == 3)) ? right : in);
+          float g[T], v[T];
+#pragma unroll
+          for (int h = 0; h < T; ++h) {
+            const float strip[10] = {k.l[h][0], k.x0[h][0], k.x0[h][1], k.x0[h][2], k.x0[h][3],
+                                     SW == 2 ? k.x1[h][0] : k.r[h][0], k.x1[h][1], k.x1[h][2], k.x1[h][3], 0.0f};
+            const float e = SW ? strip[SW * j + w - pad + 1] : (w < pad ? k.l[h][j] : (w > pad ? k.r[h][j] : k.x0[h][j]));
+            g[h] = has && live[h] ? k.t[h][j] : 0.0f;
+            v[h] = has ? e : 0.0f;
+          }
+#pragma unroll
+          for (int o = 0; o < T; ++o)
+#pragma unroll
+            for (int h = 0; h < T; ++h)
+              acc[w][o][h][j] = __builtin_amdgcn_mfma_f32_4x4x1f32(g[o], v[h], acc[w][o][h][j], 0, 0, 0);
+        }
       }
-      if (bias && kw == 0 && q == 0 && von) db[co] = (e[0] + e[2]) + (e[1] + e[3]);
-    }
-  }
-  if constexpr (SPLIT) {
-    __threadfence();
-    __syncthreads();
-    if (t == 0) last = __hip_atomic_fetch_add(&S->count[tile], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == 3u;
-    __syncthreads();
-    if (!last) return;
-    // entry e of the chains: quarters 0 + 2 and 1 + 3, their sum, then the tree over the 16
-    auto join = [&](int e) {
-      float v[16], w[4][16];
-#pragma unroll
-      for (int k = 0; k < 16; ++k)
-#pragma unroll
-        for (int h = 0; h < 4; ++h)
-          w[h][k] = __hip_atomic_load(&S->part[tile][h][k][e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = (w[0][k] + w[2][k]) + (w[1][k] + w[3][k]);
-#pragma unroll
-      for (int h = 8; h > 0; h >>= 1)
-#pragma unroll
-        for (int k = 0; k < h; ++k) v[k] += v[k + h];
-      return v[0];
     };
-    const int o = co0 + t / 16, i = ci0 + t % 16;
+    // a lane's place: SW: of its step of the four of group g, SW = 0: of its output of step g
+    auto place_of = [&](long long g) {
+      return place(SW ? 1024 * g + 256 * i + 64 * wave + 4 * b : 256 * g + 64 * i + 16 * wave + b);
+    };
+    Chunk buf[AHEAD];
+    Place s{};
+    auto fetch = [&](long long first, auto k_) {   // step first + k
+      constexpr int k = decltype(k_)::value;
+      if (SW == 0) s = place_of(first + k);
+      buf[k] = load(s, k_);
+    };
+    auto each = [](auto&& f) {
+      f(std::integral_constant<int, 0>{});
+      f(std::integral_constant<int, 1>{});
+      if constexpr (AHEAD == 4) {
+        f(std::integral_constant<int, 2>{});
+        f(std::integral_constant<int, 3>{});
+      }
+    };
+    if (SW) s = place_of(0);
+    each([&](auto k) { fetch(0, k); });
+#pragma unroll 1
+    for (long long first = 0; first < steps; first += AHEAD) {   // steps past the last hold zeros
+      if (SW) s = place_of(first / AHEAD + 1);
+      each([&](auto k) {
+        multiply(buf[decltype(k)::value]);
+        fetch(first + AHEAD, k);
+      });
+    }
+  };
+  if (bias) run(std::true_type{});
+  else run(std::false_type{});
+  // The tree: thread (w, s) joins the chains s + 16 k of weight w (levels 128 .. 16),
+  // 16 neighbours the rest.  Chain 64 wave + 4 b + j, or (SW = 0) 64 j + 16 wave + b.
+  const int w = threadIdx.x >> 4, s16 = threadIdx.x & 15;
+  auto join = [&](int row, int col) {
+    float v[16];
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-      const float d = join(256 * k + t);
-      if (o < c.Co && i < c.Ci) dw[(((size_t)o * c.Ci + i) * T2 + tap) * K + k] = d;
+    for (int k = 0; k < 16; ++k) {
+      const int ch = s16 + 16 * k;
+      v[k] = SW ? sh[ch >> 6][4 * row + (ch & 3)][4 * ((ch >> 2) & 15) + col]
+                : sh[(ch >> 4) & 3][4 * row + (ch >> 6)][4 * (ch & 15) + col];
     }
-    if (bias && t < 16) {
-      const float e = join(256 * K + t);
-      if (co0 + t < c.Co) db[co0 + t] = e;
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+      for (int k = 0; k < h; ++k) v[k] += v[k + h];
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1) v[0] += __shfl_down(v[0], h);
+    return v[0];
+  };
+#pragma unroll
+  for (int k = 0; k < K * T * T; ++k) {
+    const int o = k / T % T, h = k % T, tap = k / (T * T);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int row = 0; row < 4; ++row) sh[wave][4 * row + j][lane] = acc[tap][o][h][j][row];
+    __syncthreads();
+    const float v = join(w >> 2, w & 3);
+    const int row = co0 + 4 * o + (w >> 2), col = ci0 + 4 * h + (w & 3);
+    if (s16 == 0 && row < c.Co && col < c.Ci) dw[((size_t)row * c.Ci + col) * T3 + (kd * K + kh) * K + tap] = v;
+    __syncthreads();
+  }
+  if (bias) {
+#pragma unroll
+    for (int h = 0; h < T; ++h)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sh[wave][4 * h + j][lane] = bsum[h][j];
+    __syncthreads();
+    if (w < 4 * T) {
+      const float v = join(w >> 2, w & 3);
+      if (s16 == 0 && co0 + w < c.Co) db[co0 + w] = v;
     }
-    if (t == 0) __hip_atomic_store(&S->count[tile], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 

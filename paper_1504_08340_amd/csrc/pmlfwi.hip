@@ -1992,6 +1992,21 @@ static void launch_conv(const ConvShape& c, const float* src, const float* act, 
   table[c.K == 3][big]<<<grid, CONV_THREADS, 0, st>>>(c, src, act, w, b, relu, ptiles, out);
 }
 
+using WgradKernel = void (*)(ConvShape, const float*, const float*, const float*, float*, float*, FastDiv, FastDiv,
+                             FastDiv);
+
+// Weight gradient of kernel size K in tiles of 4 T channels; which: the w stride of
+// the vector loads, 0 without them, 3 with 64-bit offsets (T = 1).
+template <int K, int T>
+static WgradKernel wgrad_kernel(int which, bool relu) {
+  switch (which) {
+    case 1: return relu ? conv3d_wgrad_kernel<K, T, 1, false, true> : conv3d_wgrad_kernel<K, T, 1, false, false>;
+    case 2: return relu ? conv3d_wgrad_kernel<K, T, 2, false, true> : conv3d_wgrad_kernel<K, T, 2, false, false>;
+    case 3: return relu ? conv3d_wgrad_kernel<K, 1, 0, true, true> : conv3d_wgrad_kernel<K, 1, 0, true, false>;
+    default: return relu ? conv3d_wgrad_kernel<K, T, 0, false, true> : conv3d_wgrad_kernel<K, T, 0, false, false>;
+  }
+}
+
 extern "C" {
 
 fwi_status fwi_conv3d_forward(void* stream, const fwi_conv_shape* shape, const float* x, const float* w,
@@ -2030,24 +2045,24 @@ fwi_status fwi_conv3d_backward(void* stream, const fwi_conv_shape* shape, const 
   if (!conv_shape(shape, c) || !x || !w || !dy || (relu && !y) || !dw) return FWI_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   if (dx) launch_conv<true>(c, dy, y, w, nullptr, relu, dx, st);
-  // vector loads: four neighbouring outputs lie in one row and on 16 bytes, and
-  // so do their places in x at w stride 1 or 2
+  const long long P = (long long)c.Do * c.Ho * c.Wo, vol = (long long)c.D * c.H * c.W;
+  const bool wide = (long long)c.N * std::max(c.Co * P, c.Ci * vol) > (1LL << 30);   // 4-byte offsets end there
+  // vector loads: four neighbouring outputs lie in one row and on 16 bytes, and so
+  // do their places in x at w stride 1 or 2
   auto on16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
-  const bool vec = c.Wo % 4 == 0 && c.sw <= 2 && c.W == c.Wo * c.sw && on16(dy) && (!relu || on16(y)) && on16(x);
-  const int sw = vec ? c.sw : 0;
-  const long long ntiles = (long long)c.K * c.K * ((c.Co + 15) / 16) * ((c.Ci + 15) / 16);
-  const int held = ntiles <= WGRAD_TILES ? stream_slot(st) : -1;
-  const bool split = held >= 0 && held < WGRAD_SLOTS;
-  using WK = void (*)(ConvShape, const float*, const float*, int, const float*, float*, float*, FastDiv, FastDiv,
-                      FastDiv, int, int);
-  static const WK table[2][2][3] = {
-      {{conv3d_wgrad_kernel<1, 0, false>, conv3d_wgrad_kernel<1, 1, false>, conv3d_wgrad_kernel<1, 2, false>},
-       {conv3d_wgrad_kernel<1, 0, true>, conv3d_wgrad_kernel<1, 1, true>, conv3d_wgrad_kernel<1, 2, true>}},
-      {{conv3d_wgrad_kernel<3, 0, false>, conv3d_wgrad_kernel<3, 1, false>, conv3d_wgrad_kernel<3, 2, false>},
-       {conv3d_wgrad_kernel<3, 0, true>, conv3d_wgrad_kernel<3, 1, true>, conv3d_wgrad_kernel<3, 2, true>}}};
-  table[c.K == 3][split][sw]<<<(unsigned)(ntiles * (split ? 4 : 1)), WGRAD_THREADS, 0, st>>>(
-      c, dy, y, relu, x, dw, db, fast_div((unsigned)c.Wo), fast_div((unsigned)c.Ho),
-      fast_div((unsigned)(c.Do * c.Ho * c.Wo)), (int)ntiles, split ? held : 0);
+  const bool vec = !wide && c.Wo % 4 == 0 && c.sw <= 2 && c.W == c.Wo * c.sw && on16(dy) && (!relu || on16(y)) && on16(x);
+  // tiles of 8 x 8 channels halve the loads of 4 x 4 ones but leave a quarter of the
+  // workgroups: they pay from two workgroups of 4 x 4 a CU on (8 samples of 16 x 16 x
+  // 16; 9 to 32 channels at stride (4, 2, 2), 216 workgroups: 240 us in tiles of 4,
+  // 481 in tiles of 8; 32 to 32, 576: 153 and 109; 64 to 64, 2304: 453 and 325)
+  auto tiles = [&](int t) { return (long long)c.K * c.K * ((c.Co + t - 1) / t) * ((c.Ci + t - 1) / t); };
+  const bool two = !wide && tiles(4) >= 512;
+  const WgradKernel kern = c.K == 3 ? (two ? wgrad_kernel<3, 2>(vec ? c.sw : 0, relu != 0)
+                                           : wgrad_kernel<3, 1>(wide ? 3 : (vec ? c.sw : 0), relu != 0))
+                                    : (two ? wgrad_kernel<1, 2>(vec ? c.sw : 0, relu != 0)
+                                           : wgrad_kernel<1, 1>(wide ? 3 : (vec ? c.sw : 0), relu != 0));
+  kern<<<(unsigned)tiles(two ? 8 : 4), WGRAD_THREADS, 0, st>>>(
+      c, dy, y, x, dw, db, fast_div((unsigned)c.Wo), fast_div((unsigned)c.Ho), fast_div(wide ? 1u : (unsigned)P));
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 

@@ -1,0 +1,94 @@
+"""Which convolution kernel takes a call, at the lines between them.
+
+The weight gradient works in tiles of 4 or of 8 channels (by the number of
+workgroups), with vector loads at w stride 1 or 2 or element by element; every form
+sums in the same order, so each is compared bit for bit with chains formed here.
+"""
+import time
+
+import numpy as np
+import pytest
+
+from test_gpu_conv_edges import _chains
+
+pytestmark = pytest.mark.gpu
+
+
+def _torch():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    return torch
+
+
+@pytest.mark.parametrize("xs,co,K,strides,relu", [
+    ((1, 29, 3, 4, 8), 31, 3, (1, 1, 1), True),     # 576 workgroups of 4 x 4 channels: tiles of 8; vector loads
+    ((2, 30, 3, 5, 16), 32, 3, (2, 1, 2), False),   # the same at w stride 2
+    ((1, 31, 4, 5, 7), 29, 3, (1, 2, 3), True),     # element by element
+    ((3, 90, 2, 3, 8), 92, 1, (1, 1, 1), True),     # 1x1x1, tiles of 8
+    ((2, 90, 2, 3, 5), 91, 1, (1, 1, 1), False),
+    ((5, 3, 1, 1, 4), 2, 1, (1, 1, 1), True),       # tiles of 4, fewer outputs than chains
+    ((1, 6, 5, 7, 9), 9, 3, (1, 1, 1), False),
+])
+def test_weight_gradient_forms(xs, co, K, strides, relu):
+    torch = _torch()
+    from paper_1504_08340_amd import binding as B
+    rng = np.random.default_rng(8)
+    N, ci, p = xs[0], xs[1], K // 2
+    x = rng.standard_normal(xs).astype(np.float32)
+    out = [(n + 2 * p - K) // s + 1 for n, s in zip(xs[2:], strides)]
+    y, dy = (rng.standard_normal((N, co, *out)).astype(np.float32) for _ in range(2))
+    g = (np.where(y > 0, dy, np.float32(0)) if relu else dy).transpose(1, 0, 2, 3, 4).reshape(co, -1)
+    xp = np.pad(x, [(0, 0), (0, 0)] + [(p, p)] * 3)
+    dw = np.empty((co, ci, K, K, K), np.float32)
+    for kd, kh, kw in np.ndindex(K, K, K):
+        at = [slice(k, k + (n - 1) * s + 1, s) for k, n, s in zip((kd, kh, kw), out, strides)]
+        v = xp[(slice(None), slice(None), *at)].transpose(1, 0, 2, 3, 4).reshape(ci, -1)
+        dw[:, :, kd, kh, kw] = _chains([t.copy() for t in np.broadcast_arrays(g[:, None], v[None])])
+    db = _chains((g, None))
+    X, Y, DY, Wt = (torch.tensor(a, device="cuda") for a in (x, y, dy, dw))
+    DW, DB = torch.empty_like(Wt), torch.empty(co, device="cuda")
+    B.fwi_conv3d_backward(None, B.conv_shape(*xs, co, K, strides), X, Wt, Y, DY, relu, None, DW, DB)
+    assert np.array_equal(DW.cpu().numpy(), dw) and np.array_equal(DB.cpu().numpy(), db)
+
+
+@pytest.mark.parametrize("xs,co", [((4, 3, 24, 32, 32), 5), ((2, 48, 8, 8, 8), 48)])
+def test_weight_gradient_takes_as_long_on_every_route(xs, co):
+    """Eager, captured, and on a stream after many others have been used: the same
+    launch, so about the same time (twice is allowed)."""
+    torch = _torch()
+    from paper_1504_08340_amd import binding as B
+    sh = B.conv_shape(*xs, co, 3, (1, 1, 1))
+    X = torch.randn(xs, device="cuda")
+    DY = torch.randn(xs[0], co, *xs[2:], device="cuda")
+    W = torch.empty(co, xs[1], 3, 3, 3, device="cuda")
+    DW = torch.empty_like(W)
+
+    def call(stream):
+        B.fwi_conv3d_backward(stream, sh, X, W, DY, DY, True, None, DW, None)
+
+    def best(f):
+        f()
+        torch.cuda.synchronize()
+        t = []
+        for _ in range(5):
+            t0 = time.perf_counter()
+            for _ in range(20):
+                f()
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    eager = best(lambda: call(None))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(None)
+    assert best(graph.replay) < 2 * eager
+    streams = [torch.cuda.Stream() for _ in range(12)]
+    a = torch.ones(4096, dtype=torch.float64, device="cuda")
+    o = torch.empty(1, dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    for s in streams[:-1]:
+        B.fwi_dot(s.cuda_stream, a.numel(), a, a, None, o)
+        torch.cuda.synchronize()
+    assert best(lambda: call(streams[-1].cuda_stream)) < 2 * eager
