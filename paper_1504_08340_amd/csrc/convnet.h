@@ -44,9 +44,6 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 // product with 16 or 32 rows.  FP32 products are FP32 MFMA, never a split.
 
 constexpr int CONV_THREADS = 256;   // 4 waves
-// Most positions of a sample that 32-bit position arithmetic covers, the tiles'
-// and chunks' overhang included; beyond them it is done in 64 bits.
-constexpr long long CONV_NARROW = (1LL << 31) - 512;
 
 // g = dL/d(pre-activation) from dL/dy and, with ReLU, the activated output y.
 __device__ __forceinline__ float pre_grad(const float* dy, const float* y, int relu, long long i) {
@@ -98,22 +95,34 @@ conv3d_f32_kernel(ConvShape c, const float* __restrict__ src, const float* __res
   const int C = DATA ? c.Co : c.Ci, M = DATA ? c.Ci : c.Co;
   const int PD = DATA ? c.D : c.Do, PH = DATA ? c.H : c.Ho, PW = DATA ? c.W : c.Wo;
   const int SD = DATA ? c.Do : c.D, SH = DATA ? c.Ho : c.H, SW = DATA ? c.Wo : c.W;
-  const int P = PD * PH * PW;
+  const long long P = (long long)PD * PH * PW;   // may pass 2^31
   const size_t svol = (size_t)SD * SH * SW;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int tile = blockIdx.x * 4 + wave;          // over the batch's position tiles
   const int n = min(tile / ptiles, c.N - 1);
-  const int p = tile < c.N * ptiles ? (tile - n * ptiles) * 64 + lane : P;
+  const long long p = tile < c.N * ptiles ? (tile - n * ptiles) * 64LL + lane : P;
   const int row0 = blockIdx.y * R;
   long long at[K * K];                              // places of the tap rows, and along w
   int aw[K];
   unsigned here = 0, any = 0;                       // taps this lane, this wave has
   {
-    const int q = min(p, P - 1), r = q / PW;
+    const long long q = min(p, P - 1);
+    int qd, qh, qw;
+    if (P <= 0x7fffffff) {   // divisions in 64 bits only where they are needed
+      const unsigned r = (unsigned)q / PW;
+      qd = r / PH;
+      qh = r % PH;
+      qw = (unsigned)q % PW;
+    } else {
+      const long long r = q / PW;
+      qd = (int)(r / PH);
+      qh = (int)(r % PH);
+      qw = (int)(q % PW);
+    }
     int ad[K], ah[K];
-    tap_places<K, DATA>(r / PH, c.sd, SD, ad);
-    tap_places<K, DATA>(r % PH, c.sh, SH, ah);
-    tap_places<K, DATA>(q % PW, c.sw, SW, aw);
+    tap_places<K, DATA>(qd, c.sd, SD, ad);
+    tap_places<K, DATA>(qh, c.sh, SH, ah);
+    tap_places<K, DATA>(qw, c.sw, SW, aw);
 #pragma unroll
     for (int t = 0; t < T3; ++t) {
       const int a = ad[t / (K * K)], d = ah[(t / K) % K];
@@ -186,7 +195,7 @@ conv3d_f32_kernel(ConvShape c, const float* __restrict__ src, const float* __res
 #pragma unroll
   for (int i = 0; i < NACC; ++i) {
     const int row = row0 + (R == 32 ? 8 * ((i >> 2) & 3) + 4 * (lane >> 5) + (i & 3) : 4 * (lane >> 4) + (i & 3));
-    const int pos = p - lane + (R == 32 ? 32 * (i >> 4) + (lane & 31) : 16 * (i >> 2) + (lane & 15));
+    const long long pos = p - lane + (R == 32 ? 32 * (i >> 4) + (lane & 31) : 16 * (i >> 2) + (lane & 15));
     if (row >= M || pos >= P || tile >= c.N * ptiles) continue;
     float v = acc[i];
     if (!DATA && relu && v < 0.0f) v = 0.0f;

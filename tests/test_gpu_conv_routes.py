@@ -92,3 +92,62 @@ def test_weight_gradient_takes_as_long_on_every_route(xs, co):
         B.fwi_dot(s.cuda_stream, a.numel(), a, a, None, o)
         torch.cuda.synchronize()
     assert best(lambda: call(streams[-1].cuda_stream)) < 2 * eager
+
+
+@pytest.mark.parametrize("K", [1, 3])
+def test_more_positions_than_32_bits_count(K):
+    """One sample and channel of 1291^3 = 2^31 + 4.2e6 positions: forward, data, weight
+    and bias gradients.  Small whole numbers, so that every sum is exact in FP32 (the
+    largest partial sums, of 2^31 terms of both signs, stay below 2^24)."""
+    torch = _torch()
+    from paper_1504_08340_amd import binding as B
+    n, p = 1291, K // 2
+    gen = torch.Generator(device="cuda").manual_seed(3)
+
+    def signs():
+        return torch.randint(-1, 2, (n, n, n), generator=gen, device="cuda", dtype=torch.int8).float()
+
+    X, DY = signs(), signs()
+    W = torch.randint(-3, 4, (1, 1, K, K, K), generator=gen, device="cuda").float()
+    b = torch.ones(1, device="cuda")
+    Y, DX = torch.full_like(X, 7.0), torch.full_like(X, 7.0)
+    DW, DB = torch.empty_like(W), torch.empty(1, device="cuda")
+    sh = B.conv_shape(1, 1, n, n, n, 1, K, (1, 1, 1))
+    B.fwi_conv3d_forward(None, sh, X, W, b, True, Y)
+    torch.cuda.synchronize()
+    print("forward done", flush=True)
+    B.fwi_conv3d_backward(None, sh, X, W, Y, DY, True, DX, DW, DB)
+    torch.cuda.synchronize()
+    print("backward done", flush=True)
+    taps = list(np.ndindex(K, K, K))
+    dw, db = torch.zeros(len(taps), dtype=torch.float64, device="cuda"), 0.0
+
+    def padded(t, a, e):            # planes [a - p, e + p) of t, zeros around
+        out = torch.zeros(e - a + 2 * p, n + 2 * p, n + 2 * p, device="cuda")
+        lo, hi = max(a - p, 0), min(e + p, n)
+        out[lo - a + p:hi - a + p, p:p + n, p:p + n] = t[lo:hi]
+        return out
+
+    def shifted(t, k, m):
+        return t[k[0]:k[0] + m, k[1]:k[1] + n, k[2]:k[2] + n]
+
+    for a in range(0, n, 64):
+        e = min(a + 64, n)
+        xp, m = padded(X, a, e), e - a
+        g = torch.where(Y[a:e] > 0, DY[a:e], torch.zeros((), device="cuda"))
+        y = torch.ones(m, n, n, device="cuda")
+        for i, k in enumerate(taps):
+            y += W[0, 0][k] * shifted(xp, k, m)
+            dw[i] += (g * shifted(xp, k, m)).sum(dtype=torch.float64)
+        assert torch.equal(Y[a:e], y.relu())
+        db += float(g.sum(dtype=torch.float64))
+    for a in range(0, n, 64):
+        e = min(a + 64, n)
+        lo, hi = max(a - p, 0), min(e + p, n)
+        G = torch.zeros(e - a + 2 * p, n + 2 * p, n + 2 * p, device="cuda")
+        G[lo - a + p:hi - a + p, p:p + n, p:p + n] = torch.where(Y[lo:hi] > 0, DY[lo:hi], torch.zeros((), device="cuda"))
+        dx = torch.zeros(e - a, n, n, device="cuda")
+        for k in taps:
+            dx += W[0, 0][k] * shifted(G, tuple(2 * p - q for q in k), e - a)
+        assert torch.equal(DX[a:e], dx)
+    assert torch.equal(DW.double().flatten(), dw) and float(DB) == db
