@@ -66,6 +66,56 @@ __device__ __forceinline__ void tap_places(int pos, int stride, int n, int (&at)
   }
 }
 
+// Place of position q among P = . x PH x PW; divisions in 64 bits only where needed.
+__device__ __forceinline__ void split_position(long long q, long long P, int PH, int PW, int& d, int& h, int& w) {
+  if (P <= 0x7fffffff) {
+    const unsigned r = (unsigned)q / PW;
+    d = r / PH;
+    h = r % PH;
+    w = (unsigned)q % PW;
+  } else {
+    const long long r = q / PW;
+    d = (int)(r / PH);
+    h = (int)(r % PH);
+    w = (int)(q % PW);
+  }
+}
+
+// One result of the forward pass or the data gradient: acc plus the products of the
+// taps it has, multiply-adds in the order (c, kd, kh, kw).  row: its channel, (pd, ph,
+// pw) its place in sample n.
+template <bool DATA>
+__device__ __forceinline__ float conv_one(const ConvShape& c, const float* __restrict__ src,
+                                          const float* __restrict__ act, const float* __restrict__ w, int relu,
+                                          int n, int row, int pd, int ph, int pw, float acc) {
+  const int C = DATA ? c.Co : c.Ci, SD = DATA ? c.Do : c.D, SH = DATA ? c.Ho : c.H, SW = DATA ? c.Wo : c.W;
+  const int K = c.K, T3 = K * K * K;
+  auto at = [&](int pos, int k, int stride, int size) {   // as tap_places
+    const int a = DATA ? pos + K / 2 - k : pos * stride + k - K / 2;
+    if (DATA) return a >= 0 && a % stride == 0 && a / stride < size ? a / stride : -1;
+    return a >= 0 && a < size ? a : -1;
+  };
+  for (int ch = 0; ch < C; ++ch) {
+    const long long base = ((long long)n * C + ch) * SD * SH * SW;
+    const float* wc = w + (DATA ? (long long)ch * c.Ci + row : (long long)row * c.Ci + ch) * T3;
+    for (int kd = 0; kd < K; ++kd) {
+      const int d = at(pd, kd, c.sd, SD);
+      if (d < 0) continue;
+      for (int kh = 0; kh < K; ++kh) {
+        const int h = at(ph, kh, c.sh, SH);
+        if (h < 0) continue;
+        for (int kw = 0; kw < K; ++kw) {
+          const int x = at(pw, kw, c.sw, SW);
+          if (x < 0) continue;
+          const long long o = base + ((long long)d * SH + h) * SW + x;
+          acc = fmaf(wc[(kd * K + kh) * K + kw], DATA ? pre_grad(src, act, relu, o) : src[o], acc);
+        }
+      }
+    }
+  }
+  return acc;
+}
+
 // FP32 forward (y = act(b + w * x)) and data gradient (dx = w^T * g):
 //   out[row][p] = b[row] + sum over channels c, taps t of A[row][c, t] src[c][place(p, t)]
 // A wave takes 64 positions, one per lane, and R rows on the one-product MFMA
@@ -77,18 +127,50 @@ __device__ __forceinline__ void tap_places(int pos, int stride, int n, int (&at)
 // once; the weights of 8 channels are staged in LDS for the workgroup; a channel's
 // gathers are in flight during the products of the one before; taps that no
 // position of the wave has (borders, the odd places of a strided data gradient)
-// are skipped.
+// are skipped.  A tap that some positions have and others not (a border) is a product
+// with zero for these, which an infinite or undefined weight turns into NaN: a wave
+// with a result that is not finite forms its results again, each from the taps it has.
 // 16 rows where 32 would leave less than one wave a SIMD.  Of the network's
 // training step at batch 8 the five forward launches take 0.33 ms (2.0 ms with a
 // thread per output) and the four data gradients 0.41 ms (4.9 ms); the chain of
 // 64-cycle products alone is 0.08 ms a pass.
 constexpr int CONV_STAGE = 8;   // channels staged together
 
+struct ConvArgs {
+  ConvShape c;
+  const float *src, *act, *w, *b;   // act: activated outputs (data gradient with ReLU); b: bias or null
+  float* out;
+  int relu, ptiles;                 // ptiles: tiles of 64 positions a sample
+};
+
+// A wave's results one by one: a lane those of its position.
+template <bool DATA, int R>
+__device__ __forceinline__ void conv_wave(const ConvArgs& A) {
+  const ConvShape& c = A.c;
+  const int M = DATA ? c.Ci : c.Co, PD = DATA ? c.D : c.Do, PH = DATA ? c.H : c.Ho, PW = DATA ? c.W : c.Wo;
+  const long long P = (long long)PD * PH * PW;
+  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), n = tile / A.ptiles;
+  const long long p = (tile - n * A.ptiles) * 64LL + (threadIdx.x & 63);
+  if (n >= c.N || p >= P) return;
+  int pd, ph, pw;
+  split_position(p, P, PH, PW, pd, ph, pw);
+  const int row0 = blockIdx.y * R;
+#pragma unroll 1
+  for (int row = row0; row < min(row0 + R, M); ++row) {
+    const float v = conv_one<DATA>(c, A.src, A.act, A.w, A.relu, n, row, pd, ph, pw, !DATA && A.b ? A.b[row] : 0.0f);
+    A.out[((size_t)n * M + row) * P + p] = !DATA && A.relu && v < 0.0f ? 0.0f : v;
+  }
+}
+
 template <int K, bool DATA, int R>
-__global__ void __launch_bounds__(CONV_THREADS, (DATA ? 2 : 3))
-conv3d_f32_kernel(ConvShape c, const float* __restrict__ src, const float* __restrict__ act,
-                  const float* __restrict__ w, const float* __restrict__ b, int relu, int ptiles,
-                  float* __restrict__ out) {
+__global__ void __launch_bounds__(CONV_THREADS, (DATA ? 2 : 3)) conv3d_f32_kernel(ConvArgs A) {
+  const ConvShape& c = A.c;
+  const float* __restrict__ const src = A.src;
+  const float* __restrict__ const act = A.act;
+  const float* __restrict__ const w = A.w;
+  const float* __restrict__ const b = A.b;
+  float* __restrict__ const out = A.out;
+  const int relu = A.relu, ptiles = A.ptiles;
   constexpr int T3 = K * K * K, LR = R + 1, NACC = R == 32 ? 32 : 16;
   typedef float vacc __attribute__((ext_vector_type(NACC)));
   __shared__ float sA[CONV_STAGE * T3 * LR];
@@ -108,17 +190,7 @@ conv3d_f32_kernel(ConvShape c, const float* __restrict__ src, const float* __res
   {
     const long long q = min(p, P - 1);
     int qd, qh, qw;
-    if (P <= 0x7fffffff) {   // divisions in 64 bits only where they are needed
-      const unsigned r = (unsigned)q / PW;
-      qd = r / PH;
-      qh = r % PH;
-      qw = (unsigned)q % PW;
-    } else {
-      const long long r = q / PW;
-      qd = (int)(r / PH);
-      qh = (int)(r % PH);
-      qw = (int)(q % PW);
-    }
+    split_position(q, P, PH, PW, qd, qh, qw);
     int ad[K], ah[K];
     tap_places<K, DATA>(qd, c.sd, SD, ad);
     tap_places<K, DATA>(qh, c.sh, SH, ah);
@@ -190,6 +262,18 @@ conv3d_f32_kernel(ConvShape c, const float* __restrict__ src, const float* __res
     }
 #pragma unroll
     for (int t = 0; t < T3; ++t) v[t] = DATA && !(mn[DATA ? t : 0] > 0.0f) ? 0.0f : vn[t];
+  }
+  float zero = 0.0f;
+#pragma unroll
+  for (int i = 0; i < NACC; ++i) zero = fmaf(acc[i], 0.0f, zero);
+  if (__ballot(zero != 0.0f)) {
+    // The arguments are read again: held until here for this rare pass, they do not
+    // fit the scalar registers beside the taps' masks (180 us in place of 167 at 64 x
+    // 64 channels and 32,768 positions).
+    const ConvArgs* args = (const ConvArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    conv_wave<DATA, R>(*args);
+    return;
   }
   // accumulator i of a lane: 32 rows: block i / 16 of 32 positions; 16: block i / 4 of 16
 #pragma unroll

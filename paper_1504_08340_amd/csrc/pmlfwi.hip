@@ -1986,10 +1986,10 @@ static void launch_conv(const ConvShape& c, const float* src, const float* act, 
   const long long tiles = (long long)ptiles * c.N;
   const int big = M > 16 && tiles * ((M + 31) / 32) >= 1024, R = big ? 32 : 16;
   const dim3 grid((unsigned)((tiles + 3) / 4), (unsigned)((M + R - 1) / R));
-  using CK = void (*)(ConvShape, const float*, const float*, const float*, const float*, int, int, float*);
+  using CK = void (*)(ConvArgs);
   static const CK table[2][2] = {{conv3d_f32_kernel<1, DATA, 16>, conv3d_f32_kernel<1, DATA, 32>},
                                  {conv3d_f32_kernel<3, DATA, 16>, conv3d_f32_kernel<3, DATA, 32>}};
-  table[c.K == 3][big]<<<grid, CONV_THREADS, 0, st>>>(c, src, act, w, b, relu, ptiles, out);
+  table[c.K == 3][big]<<<grid, CONV_THREADS, 0, st>>>(ConvArgs{c, src, act, w, b, out, relu, ptiles});
 }
 
 using WgradKernel = void (*)(ConvShape, const float*, const float*, const float*, float*, float*, FastDiv, FastDiv,

@@ -151,3 +151,60 @@ def test_more_positions_than_32_bits_count(K):
             dx += W[0, 0][k] * shifted(G, tuple(2 * p - q for q in k), e - a)
         assert torch.equal(DX[a:e], dx)
     assert torch.equal(DW.double().flatten(), dw) and float(DB) == db
+
+
+def _taps(n, k, s, K):
+    """Outputs along an axis that have tap k, and their places in the input."""
+    o = np.arange((n + 2 * (K // 2) - K) // s + 1)
+    i = o * s + k - K // 2
+    keep = (i >= 0) & (i < n)
+    return o[keep], i[keep]
+
+
+def _conv_both(x, w, b, g, strides):
+    """y = b + w * x and dx = w^T * g in FP64, tap by tap: a place outside contributes
+    nothing, whatever the weight."""
+    K = w.shape[2]
+    out = [(n + 2 * (K // 2) - K) // s + 1 for n, s in zip(x.shape[2:], strides)]
+    y = np.broadcast_to(b[None, :, None, None, None], (x.shape[0], w.shape[0], *out)).copy()
+    dx = np.zeros(x.shape)
+    with np.errstate(all="ignore"):
+        for k in np.ndindex(K, K, K):
+            o, i = zip(*(_taps(n, q, s, K) for n, q, s in zip(x.shape[2:], k, strides)))
+            oi, ii = (slice(None), slice(None), *np.ix_(*o)), (slice(None), slice(None), *np.ix_(*i))
+            wk = w[:, :, k[0], k[1], k[2]]
+            # products before sums: an infinite weight times 0 is no number, times a value infinite
+            y[oi] = y[oi] + (wk[None, :, :, None, None, None] * x[ii][:, None]).sum(2)
+            dx[ii] = dx[ii] + (wk[None, :, :, None, None, None] * g[oi][:, :, None]).sum(1)
+    return y, dx
+
+
+@pytest.mark.parametrize("xs,co,K,strides", [
+    ((2, 3, 5, 6, 7), 4, 3, (1, 1, 1)),
+    ((1, 9, 6, 5, 9), 20, 3, (2, 1, 2)),
+    ((2, 3, 4, 3, 5), 17, 1, (2, 1, 1)),
+])
+def test_a_weight_that_is_no_number_stays_with_its_tap(xs, co, K, strides):
+    """Infinite and undefined weights of border taps: results that do not have the tap
+    are what they are without it (FP32 within 1e-5 of the largest finite)."""
+    torch = _torch()
+    from paper_1504_08340_amd import binding as B
+    rng = np.random.default_rng(5)
+    x, w = rng.standard_normal(xs), rng.standard_normal((co, xs[1], K, K, K))
+    x, w, b = (a.astype(np.float32).astype(np.float64) for a in (x, w, rng.standard_normal(co)))
+    w[0, 1, 0, 0, 0] = np.inf
+    w[co - 1, 0, K - 1, K // 2, 0] = -np.inf
+    w[1, 2, K // 2, 0, K - 1] = np.nan
+    out = [(n + 2 * (K // 2) - K) // s + 1 for n, s in zip(xs[2:], strides)]
+    g = rng.standard_normal((xs[0], co, *out)).astype(np.float32).astype(np.float64)
+    y, dx = _conv_both(x, w, b, g, strides)
+    X, W, b_, G = (torch.tensor(a, dtype=torch.float32, device="cuda") for a in (x, w, b, g))
+    Y, DX, DW = torch.empty_like(G), torch.empty_like(X), torch.empty_like(W)
+    sh = B.conv_shape(*xs, co, K, strides)
+    B.fwi_conv3d_forward(None, sh, X, W, b_, False, Y)
+    B.fwi_conv3d_backward(None, sh, X, W, G, G, False, DX, DW, None)
+    for got, ref in ((Y, y), (DX, dx)):
+        got, fin = got.cpu().numpy(), np.isfinite(ref)
+        assert fin.any() and not fin.all()
+        assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+        assert np.abs(got[fin] - ref[fin]).max() <= 1e-5 * np.abs(ref[fin]).max()
