@@ -533,17 +533,74 @@ __global__ void to_bf16_kernel(long long n, const float* __restrict__ in, unsign
     out[i] = bf16_bits(in[i]);
 }
 
-// The same GEMM on v_mfma_f32_32x32x16_bf16 with FP32 accumulation, 32
+// The convolution as an implicit GEMM: C[co][p] = sum_k W[co][k] X[k][p], bias and ReLU
+// in FP32, output rounded to BF16 (hidden layers) or kept FP32 (the head).
+//
+// Few input channels: k = (ci, kd, kh, kw) as it comes, so that 16 k's are up to 16
+// taps of one channel.  One wave per 16 output positions and every 16-row tile of
+// output channels, v_mfma 16x16x16 BF16 with FP32 accumulation.  Bound by its index
+// arithmetic, 1.4 us a step of 16 k's and 16 rows where the positions are few.
+__global__ void __launch_bounds__(CONV_THREADS)
+conv3d_bf16_narrow_kernel(ConvShape c, const unsigned short* __restrict__ x, const unsigned short* __restrict__ w,
+                          const float* __restrict__ b, int relu, int out_fp32, void* __restrict__ y) {
+  const int P = c.Do * c.Ho * c.Wo;
+  const int KK = c.K * c.K * c.K, Kdim = c.Ci * KK, pad = c.K / 2;
+  const int n = blockIdx.y;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = lane & 15, g = lane >> 4;
+  const int col0 = blockIdx.x * 64 + wave * 16;
+  const int p = col0 + i;                        // this lane's output position (B column)
+  const bool pin = p < P;
+  const int ow = pin ? p % c.Wo : 0, oh = pin ? (p / c.Wo) % c.Ho : 0, od = pin ? p / (c.Wo * c.Ho) : 0;
+  const unsigned short* xn = x + (size_t)n * c.Ci * c.D * c.H * c.W;
+  const int nrt = (c.Co + 15) / 16;
+  for (int rt = 0; rt < nrt; ++rt) {
+    const int row = rt * 16 + i;                 // this lane's A row (output channel)
+    v4f acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int k0 = 0; k0 < Kdim; k0 += 16) {
+      v4s a, bb;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int k = k0 + 4 * g + j;
+        a[j] = (row < c.Co && k < Kdim) ? (short)w[(size_t)row * Kdim + k] : (short)0;
+        short v = 0;
+        if (pin && k < Kdim) {
+          const int ci = k / KK, r = k - ci * KK;
+          const int kd = r / (c.K * c.K), kh = (r / c.K) % c.K, kw = r % c.K;
+          const int id = od * c.sd + kd - pad, ih = oh * c.sh + kh - pad, iw = ow * c.sw + kw - pad;
+          if (id >= 0 && id < c.D && ih >= 0 && ih < c.H && iw >= 0 && iw < c.W)
+            v = (short)xn[(((size_t)ci * c.D + id) * c.H + ih) * c.W + iw];
+        }
+        bb[j] = v;
+      }
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bb, acc, 0, 0, 0);
+    }
+    // lane holds C[rt*16 + 4 g + r][col0 + i], r = 0..3
+    if (pin) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int co = rt * 16 + 4 * g + r;
+        if (co >= c.Co) continue;
+        float v = acc[r] + (b ? b[co] : 0.0f);
+        if (relu && v < 0.0f) v = 0.0f;
+        const size_t o = ((size_t)n * c.Co + co) * P + p;
+        if (out_fp32) ((float*)y)[o] = v;
+        else ((unsigned short*)y)[o] = bf16_bits(v);
+      }
+    }
+  }
+}
+
+// Otherwise v_mfma_f32_32x32x16_bf16 with FP32 accumulation, 32
 // positions and 32 rows a workgroup: lanes 0-31 hold channels 0-7, lanes 32-63
 // channels 8-15 of a group of 16 at their positions.  All taps' weights (27 x 32
 // rows x 32 channels, 69 KB) are staged once per 32 input channels (16 bytes a
 // load where rows allow), and the four waves share the positions, each taking
 // every fourth (tap, channel group), four of them in flight: the inference of
 // one set of traces has at most 256 tiles a layer, so it is the length of a
-// wave's chain that counts.  Bias and ReLU in FP32, output rounded to BF16
-// (hidden layers) or kept FP32 (the head).  32 x 64 x 16 x 16 to 32 channels at
-// stride (2, 1, 1): 12.7 us (139 us with one wave per 16 positions, no staging and
-// no gathers in flight).
+// wave's chain that counts.  32 x 64 x 16 x 16 to 32 channels at stride (2, 1, 1):
+// 12.7 us (139 us with one wave per 16 positions, no staging and no gathers in
+// flight).
 typedef unsigned short v8us __attribute__((ext_vector_type(8)));
 
 template <int K>
@@ -623,7 +680,6 @@ conv3d_bf16_mfma_kernel(ConvShape c, const unsigned short* __restrict__ x, const
                                                       0, 0, 0);
       }
     }
-    if (!staged) __syncthreads();   // a wave without steps
   }
   auto store = [&](int r, float v) {
     const int co = row0 + 8 * (r >> 2) + 4 * h + (r & 3);

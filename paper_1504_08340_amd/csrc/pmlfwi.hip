@@ -1992,6 +1992,24 @@ static void launch_conv(const ConvShape& c, const float* src, const float* act, 
   table[c.K == 3][big]<<<grid, CONV_THREADS, 0, st>>>(ConvArgs{c, src, act, w, b, out, relu, ptiles});
 }
 
+// Whether the kernel for few input channels is the faster one, from what both take,
+// in us: a chain of dependent steps that grows with the layer, or, with many
+// positions, a share of the chip for each.  Measured over 1 to 32 channels to 1 to 64
+// at 8 to 262,144 positions the choice is within 12 % of the faster one (this kernel
+// and the other: 1 to 16 channels, K = 3, 65,536 positions 9.0 and 35.2 us; 4 to 16,
+// 4,096 positions 11.8 and 9.2; 8 to 16, 65,536 positions 40.7 and 37.5; K = 1, 16 to
+// 16, 4,096 positions 4.5 and 5.5).
+static bool bf16_narrow(const ConvShape& c) {
+  auto up = [](int a, int b) { return (double)((a + b - 1) / b); };
+  const double m = (double)c.N * c.Do * c.Ho * c.Wo, steps = up(c.Ci * c.K * c.K * c.K, 16) * up(c.Co, 16);
+  const double rows = std::min(c.Co, 32), tiles = up(c.Co, 32), few = std::min(c.Ci, 4);
+  if (c.K == 3)
+    return std::max(2.4 + 1.43 * steps, 2.4 + 3.6e-5 * steps * m) <
+           std::max(6.2 + 0.213 * rows, 2.3 + (2.38e-4 + 1.49e-5 * rows) * tiles * m);
+  return std::max(2.3 + (1.05 + 0.25 * few) * steps, 2.4 + (2.4e-5 + 7.5e-6 * few) * steps * m) <
+         std::max(4.5 + 0.08 * rows, 2.6 + (2.3e-5 + 1e-6 * rows) * tiles * m);
+}
+
 using WgradKernel = void (*)(ConvShape, const float*, const float*, const float*, float*, float*, FastDiv, FastDiv,
                              FastDiv);
 
@@ -2031,6 +2049,11 @@ fwi_status fwi_conv3d_forward_bf16(void* stream, const fwi_conv_shape* shape, co
   if (!conv_shape(shape, c) || !x || !w || !y) return FWI_ERR_ARG;
   const long long P = (long long)c.Do * c.Ho * c.Wo;
   if (c.N > 65535) return FWI_ERR_ARG;
+  if (bf16_narrow(c)) {
+    conv3d_bf16_narrow_kernel<<<dim3((unsigned)((P + 63) / 64), (unsigned)c.N), CONV_THREADS, 0, (hipStream_t)stream>>>(
+        c, (const unsigned short*)x, (const unsigned short*)w, b, relu, out_fp32, y);
+    return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
+  }
   const int span = c.K == 3 ? 32 : 128;   // positions a workgroup
   const dim3 grid((unsigned)((P + span - 1) / span), (unsigned)c.N, (unsigned)((c.Co + 31) / 32));
   (c.K == 3 ? conv3d_bf16_mfma_kernel<3> : conv3d_bf16_mfma_kernel<1>)<<<grid, CONV_THREADS, 0, (hipStream_t)stream>>>(

@@ -208,3 +208,49 @@ def test_a_weight_that_is_no_number_stays_with_its_tap(xs, co, K, strides):
         assert fin.any() and not fin.all()
         assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
         assert np.abs(got[fin] - ref[fin]).max() <= 1e-5 * np.abs(ref[fin]).max()
+
+
+@pytest.mark.parametrize("xs,co,K,strides", [
+    ((2, 1, 7, 9, 11), 16, 3, (1, 1, 1)),       # few input channels: 16 taps a step
+    ((1, 3, 33, 32, 31), 19, 3, (1, 1, 1)),     # as many positions as make that the faster one
+    ((1, 3, 5, 7, 9), 19, 3, (2, 1, 2)),        # and as few as do not
+    ((3, 16, 3, 5, 7), 16, 1, (1, 1, 1)),       # 1x1x1
+    ((1, 17, 3, 5, 7), 33, 1, (1, 2, 1)),
+])
+@pytest.mark.parametrize("fp32", [0, 1])
+def test_bf16_narrow_layers(xs, co, K, strides, fp32):
+    """Against the FP64 oracle on the rounded operands, within one BF16 unit (FP32
+    output: the accumulation's 1e-5 of the largest)."""
+    torch = _torch()
+    import oracle.convnet as C
+    from paper_1504_08340_amd import binding as B
+    rng = np.random.default_rng(6)
+    x = rng.standard_normal(xs).astype(np.float32)
+    w = (rng.standard_normal((co, xs[1], K, K, K)) / np.sqrt(xs[1] * K ** 3)).astype(np.float32)
+    b = rng.standard_normal(co).astype(np.float32)
+    ref = C.conv3d_forward(C.bf16_round(x), C.bf16_round(w), b.astype(np.float64), strides, True)
+    X, W, b_ = (torch.tensor(a, device="cuda") for a in (x, w, b))
+    Y = torch.empty(ref.shape, dtype=torch.float32 if fp32 else torch.bfloat16, device="cuda")
+    B.fwi_conv3d_forward_bf16(None, B.conv_shape(*xs, co, K, strides), X.bfloat16(), W.bfloat16(), b_, True, fp32, Y)
+    got = Y.float().cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - ref) <= (0 if fp32 else 2.0 ** -7) * np.abs(ref) + 1e-5 * np.abs(ref).max())
+
+
+def test_bf16_layer_of_one_channel_is_quick():
+    """8 samples of 64x16x16, one channel to 16, stride (2, 1, 1): 9 us a call with the
+    kernel for few channels, 35 us without it."""
+    torch = _torch()
+    from paper_1504_08340_amd import binding as B
+    sh = B.conv_shape(8, 1, 64, 16, 16, 16, 3, (2, 1, 1))
+    X = torch.randn(8, 1, 64, 16, 16, device="cuda").bfloat16()
+    W = torch.randn(16, 1, 3, 3, 3, device="cuda").bfloat16()
+    Y = torch.empty(8, 16, 32, 16, 16, device="cuda", dtype=torch.bfloat16)
+    t = []
+    for _ in range(10):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(100):
+            B.fwi_conv3d_forward_bf16(None, sh, X, W, None, True, 0, Y)
+        torch.cuda.synchronize()
+        t.append((time.perf_counter() - t0) / 100)
+    assert min(t[1:]) < 20e-6
