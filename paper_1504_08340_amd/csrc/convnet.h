@@ -287,6 +287,22 @@ __global__ void __launch_bounds__(CONV_THREADS, (DATA ? 2 : 3)) conv3d_f32_kerne
   }
 }
 
+// The same results a thread each: layers of so few channels that a wave's rows are
+// mostly padding.
+template <bool DATA>
+__global__ void __launch_bounds__(CONV_THREADS) conv3d_direct_kernel(ConvArgs A) {
+  const ConvShape& c = A.c;
+  const int M = DATA ? c.Ci : c.Co, PD = DATA ? c.D : c.Do, PH = DATA ? c.H : c.Ho, PW = DATA ? c.W : c.Wo;
+  const long long P = (long long)PD * PH * PW, i = (long long)blockIdx.x * CONV_THREADS + threadIdx.x;
+  if (i >= (long long)c.N * M * P) return;
+  const long long nr = i / P;
+  const int n = (int)(nr / M), row = (int)(nr % M);
+  int pd, ph, pw;
+  split_position(i - nr * P, P, PH, PW, pd, ph, pw);
+  const float v = conv_one<DATA>(c, A.src, A.act, A.w, A.relu, n, row, pd, ph, pw, !DATA && A.b ? A.b[row] : 0.0f);
+  A.out[i] = !DATA && A.relu && v < 0.0f ? 0.0f : v;
+}
+
 // dw[co][ci][tap] = sum over batch and outputs of g * x, and db[co] = sum of g.
 // Order of the sums: the outputs, numbered through the batch, are dealt to 256
 // chains (output T to chain T mod 256), each chain adds its products one by one,

@@ -1975,6 +1975,33 @@ static bool conv_shape(const fwi_conv_shape* s, ConvShape& c) {
 
 }  // extern "C"
 
+// Whether a thread per result is faster than 16 rows a wave, from what both take, in
+// us: a chain of dependent steps through the channels, or, with many positions, a
+// share of the chip for each result or for each wave.  Measured over 1 to 16
+// channels to 1 to 32 at 8 to 524,288 positions the choice is within 9 % (0.7 us) of
+// the faster one (a thread per result and the other, K = 3: forward 1 to 1 channel,
+// 262,144 positions 7.6 and 11.9 us; 1 to 16, 4,096 positions 6.0 and 7.9; 2 to 8,
+// 65,536 positions 17.0 and 10.1; data gradient of 1 to 1, 524,288 positions 29 and
+// 54, 32,768 positions 11.4 and 10.7).
+static bool conv_one_by_one(const ConvShape& c, bool data) {
+  const int C = data ? c.Co : c.Ci, M = data ? c.Ci : c.Co;
+  const double np = (double)c.N * (data ? (double)c.D * c.H * c.W : (double)c.Do * c.Ho * c.Wo), n = np * M;
+  const double rows = (M + 15) / 16;
+  if (c.K == 1) return M == 1 && C <= (data ? 2 : 4);
+  if (C > 4 && np >= 65536) return false;
+  if (!data) {
+    auto used = [](int size, int out) { return 1 + (size > 1) + (out > 1); };   // taps that some position has
+    const int taps = used(c.D, c.Do) * used(c.H, c.Ho) * used(c.W, c.Wo);
+    return std::max(1.8 + C * (0.7 + 0.122 * taps), 3.8 + 1.25e-5 * C * n) <
+           std::max(4.6 + C * (1.2 + 0.02 * taps), 3.0 + (2.2e-5 + 1.25e-5 * C) * rows * np);
+  }
+  if (c.sd == 1 && c.sh == 1 && c.sw == 1)
+    return std::max(2.5 + 8.5 * C, 5.0 + 4.6e-5 * C * n) <
+           std::max(8.0 + 2.5 * C, 2.0 + (7.6e-5 + 2.3e-5 * C) * rows * np);
+  return std::max(2.0 + 6.5 * C, 4.0 + 2.5e-5 * C * n) <
+         std::max(7.2 + 2.1 * C, 2.0 + (4.8e-5 + 1.75e-5 * C) * rows * np);
+}
+
 // Forward (DATA = false) or data gradient of a convolution: 32 rows a wave where
 // that still gives every one of the 1024 SIMDs a wave, 16 (half the chain of
 // products per wave, twice the gathers in all) otherwise.
@@ -1986,6 +2013,11 @@ static void launch_conv(const ConvShape& c, const float* src, const float* act, 
   const long long tiles = (long long)ptiles * c.N;
   const int big = M > 16 && tiles * ((M + 31) / 32) >= 1024, R = big ? 32 : 16;
   const dim3 grid((unsigned)((tiles + 3) / 4), (unsigned)((M + R - 1) / R));
+  if (conv_one_by_one(c, DATA)) {
+    conv3d_direct_kernel<DATA><<<(unsigned)(((long long)c.N * M * P + CONV_THREADS - 1) / CONV_THREADS), CONV_THREADS, 0, st>>>(
+        ConvArgs{c, src, act, w, b, out, relu, ptiles});
+    return;
+  }
   using CK = void (*)(ConvArgs);
   static const CK table[2][2] = {{conv3d_f32_kernel<1, DATA, 16>, conv3d_f32_kernel<1, DATA, 32>},
                                  {conv3d_f32_kernel<3, DATA, 16>, conv3d_f32_kernel<3, DATA, 32>}};

@@ -254,3 +254,51 @@ def test_bf16_layer_of_one_channel_is_quick():
         torch.cuda.synchronize()
         t.append((time.perf_counter() - t0) / 100)
     assert min(t[1:]) < 20e-6
+
+
+@pytest.mark.parametrize("xs,co,K,strides", [
+    # a thread per result: one to two channels and many positions, one channel and few,
+    # one position; K = 1
+    ((3, 1, 45, 44, 46), 1, 3, (1, 1, 1)),
+    ((2, 2, 51, 53, 55), 1, 3, (1, 1, 1)),
+    ((2, 1, 9, 7, 5), 20, 3, (2, 1, 2)),
+    ((4, 3, 1, 1, 1), 2, 3, (1, 1, 1)),
+    ((2, 4, 7, 9, 11), 1, 1, (1, 2, 1)),
+    ((2, 1, 7, 9, 11), 2, 1, (1, 1, 1)),
+    # 32 rows a wave in both directions: 65,536 positions, or half as many and more than
+    # 32 rows; channels that are no multiple of 32, a last tile that is not full
+    ((2, 35, 26, 27, 25), 37, 3, (1, 1, 1)),
+    ((3, 18, 29, 28, 27), 20, 1, (1, 1, 1)),
+    # a position short of 65,536 (16 rows a wave)
+    ((1, 18, 63, 32, 32), 17, 1, (1, 1, 1)),
+])
+def test_fp32_forms(xs, co, K, strides):
+    """Forward and data gradient against FP64 sums (1e-5 of the largest magnitude)."""
+    torch = _torch()
+    from paper_1504_08340_amd import binding as B
+    rng = np.random.default_rng(11)
+    x = rng.standard_normal(xs).astype(np.float32)
+    w = (rng.standard_normal((co, xs[1], K, K, K)) / np.sqrt(xs[1] * K ** 3)).astype(np.float32)
+    b = rng.standard_normal(co).astype(np.float32)
+    X, W, b_ = (torch.tensor(a, device="cuda") for a in (x, w, b))
+    out = [(n + 2 * (K // 2) - K) // s + 1 for n, s in zip(xs[2:], strides)]
+    Y = torch.empty(xs[0], co, *out, device="cuda")
+    DY = torch.tensor(rng.standard_normal(Y.shape).astype(np.float32), device="cuda")
+    DX, DW = torch.empty_like(X), torch.empty_like(W)
+    sh = B.conv_shape(*xs, co, K, strides)
+    B.fwi_conv3d_forward(None, sh, X, W, b_, True, Y)
+    B.fwi_conv3d_backward(None, sh, X, W, Y, DY, True, DX, DW, None)
+    got = Y.cpu().numpy()
+    # the mask is the library's own output's: a value within rounding of 0 may fall either way
+    g = np.where(got > 0, DY.cpu().numpy(), 0).astype(np.float64)
+    y, dx = np.empty(got.shape), np.zeros(xs)
+    for n in range(xs[0]):
+        y[n] = b[:, None, None, None]
+        for k in np.ndindex(K, K, K):
+            o, i = zip(*(_taps(m, q, s, K) for m, q, s in zip(xs[2:], k, strides)))
+            oi, ii = (slice(None), *np.ix_(*o)), (slice(None), *np.ix_(*i))
+            wk = w[:, :, k[0], k[1], k[2]].astype(np.float64)
+            y[n][oi] += np.tensordot(wk, x[n][ii].astype(np.float64), 1)
+            dx[n][ii] += np.tensordot(wk.T, g[n][oi], 1)
+    for a, ref in ((got, np.maximum(y, 0)), (DX.cpu().numpy(), dx)):
+        assert np.abs(a - ref).max() <= 1e-5 * np.abs(ref).max()
