@@ -729,22 +729,21 @@ conv3d_bf16_mfma_kernel(ConvShape c, const unsigned short* __restrict__ x, const
 
 // L = 1/(2n) sum (y - t)^2 over n entries; grad = (y - t)/n (parts and slot as
 // in reduce.h).
-__global__ void __launch_bounds__(RED_THREADS) mse_kernel(long long n, const float* __restrict__ y,
-                                                          const float* __restrict__ t, float* __restrict__ loss,
-                                                          float* __restrict__ grad, int nb, int slot) {
+__global__ void __launch_bounds__(RED_ONE) mse_kernel(long long n, const float* __restrict__ y,
+                                                      const float* __restrict__ t, float* __restrict__ loss,
+                                                      float* __restrict__ grad, int nb, int slot) {
   __shared__ double sh[RED_THREADS];
   const float inv = 1.0f / (float)n;
-  const long long step = (long long)nb * RED_THREADS;
   double s;
-  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, s, [&](int part) {
-        double acc = 0.0;
-        for (long long i = (long long)part * RED_THREADS + threadIdx.x; i < n; i += step) {
-          const float r = y[i] - t[i];
-          acc += (double)r * (double)r;
-          if (grad) grad[i] = r * inv;
-        }
-        return acc;
-      }) && threadIdx.x == 0 && loss)
+  auto one = [&](int part, int th) {
+    double acc = 0.0;
+    red_entries(part, th, nb, n, [&](long long i) { return y[i] - t[i]; }, [&](float r, long long i) {
+      acc = fma((double)r, (double)r, acc);
+      if (grad) grad[i] = r * inv;
+    });
+    return acc;
+  };
+  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, s, one) && threadIdx.x == 0 && loss)
     loss[0] = (float)(0.5 * s / (double)n);
 }
 

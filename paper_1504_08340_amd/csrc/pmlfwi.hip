@@ -1518,6 +1518,10 @@ int stream_slot(hipStream_t st) {
   held[n] = st;
   return n++;
 }
+
+// Threads of a reduction's workgroups: its one workgroup takes more where it walks
+// several parts.
+int red_threads(int nb, int slot) { return nb > 1 && slot < 0 ? RED_ONE : RED_THREADS; }
 }  // namespace
 
 // ====================================================================== C ABI
@@ -1910,7 +1914,7 @@ fwi_status fwi_regularization(fwi_plan* p, void* stream, int kind, double eps, c
   if (grad) reg_gradient_kernel<<<reg_tiles(G), REG_THREADS, 0, st>>>(G, k, eps, field, grad);
   if (value) {
     const int nb = red_parts(27LL * G.ex * G.ey * G.ez), slot = nb > 1 ? stream_slot(st) : -1;
-    reg_value_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>(G, k, eps, field, value, nb, slot);
+    reg_value_kernel<<<slot < 0 ? 1 : nb, red_threads(nb, slot), 0, st>>>(G, k, eps, field, value, nb, slot);
   }
   HIP_TRY(p, hipGetLastError());
   return FWI_OK;
@@ -1944,7 +1948,7 @@ fwi_status fwi_dot(void* stream, int64_t n, const double* a, const double* b, co
   if (n < 0 || !out || (n > 0 && (!a || !b))) return FWI_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   const int nb = red_parts(n), slot = nb > 1 ? stream_slot(st) : -1;
-  dot_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>((long long)n, a, b, w, out, nb, slot);
+  dot_kernel<<<slot < 0 ? 1 : nb, red_threads(nb, slot), 0, st>>>((long long)n, a, b, w, out, nb, slot);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
@@ -1961,7 +1965,7 @@ fwi_status fwi_absmax(void* stream, int64_t n, const double* x, double* out) {
   if (n < 0 || !out || (n > 0 && !x)) return FWI_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   const int nb = red_parts(n), slot = nb > 1 ? stream_slot(st) : -1;
-  absmax_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>((long long)n, x, out, nb, slot);
+  absmax_kernel<<<slot < 0 ? 1 : nb, red_threads(nb, slot), 0, st>>>((long long)n, x, out, nb, slot);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
@@ -2125,7 +2129,7 @@ fwi_status fwi_mse(void* stream, int64_t n, const float* y, const float* t, floa
   if (n < 1 || !y || !t || (!loss && !grad)) return FWI_ERR_ARG;
   hipStream_t st = (hipStream_t)stream;
   const int nb = red_parts(n), slot = nb > 1 ? stream_slot(st) : -1;
-  mse_kernel<<<slot < 0 ? 1 : nb, RED_THREADS, 0, st>>>((long long)n, y, t, loss, grad, nb, slot);
+  mse_kernel<<<slot < 0 ? 1 : nb, red_threads(nb, slot), 0, st>>>((long long)n, y, t, loss, grad, nb, slot);
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 

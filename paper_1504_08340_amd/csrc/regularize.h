@@ -144,29 +144,29 @@ __global__ void __launch_bounds__(REG_THREADS) reg_gradient_kernel(Geo g, int ki
 }
 
 // value[0] = R(f) (parts and slot as in reduce.h: deterministic).
-__global__ void __launch_bounds__(RED_THREADS) reg_value_kernel(Geo g, int kind, double eps,
-                                                                const double* __restrict__ f,
-                                                                double* __restrict__ value, int nb, int slot) {
+__global__ void __launch_bounds__(RED_ONE) reg_value_kernel(Geo g, int kind, double eps,
+                                                            const double* __restrict__ f,
+                                                            double* __restrict__ value, int nb, int slot) {
   __shared__ double sh[RED_THREADS];
-  const long long npts = 27LL * g.ex * g.ey * g.ez, step = (long long)nb * RED_THREADS;
+  const long long npts = 27LL * g.ex * g.ey * g.ez, span = red_span(npts, nb);
   const double vol = 0.125 * g.h * g.h * g.h;
   double r;
-  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, r, [&](int part) {
-        double acc = 0.0;
-        for (long long t = (long long)part * RED_THREADS + threadIdx.x; t < npts; t += step) {
-          const int q = (int)(t % 27);
-          const unsigned e = (unsigned)(t / 27), er = e / (unsigned)g.ex;   // fewer bricks than nodes
-          const int ex = (int)(e - er * g.ex), ez = (int)(er / (unsigned)g.ey), ey = (int)(er - ez * g.ey);
-          const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
-          double G[3], val, coef;
-          point_grad(g, f, (2 * ex + qx) + g.NIX * ((2 * ey + qy) + g.NIY * (2 * ez + qz)), g.NIX, g.NIX * g.NIY, qx, qy,
-                     qz, G);
-          point_terms(kind, eps, G, vol * wlgl64(qx) * wlgl64(qy) * wlgl64(qz), &val, &coef);
-          acc += val;
-        }
-        return acc;
-      }) && threadIdx.x == 0)
-    value[0] = r;
+  auto one = [&](int part, int th) {
+    double acc = 0.0;
+    for (long long t = part * span + th; t < min(npts, (part + 1) * span); t += RED_THREADS) {
+      const int q = (int)(t % 27);
+      const unsigned e = (unsigned)(t / 27), er = e / (unsigned)g.ex;   // fewer bricks than nodes
+      const int ex = (int)(e - er * g.ex), ez = (int)(er / (unsigned)g.ey), ey = (int)(er - ez * g.ey);
+      const int qx = q % 3, qy = (q / 3) % 3, qz = q / 9;
+      double G[3], val, coef;
+      point_grad(g, f, (2 * ex + qx) + g.NIX * ((2 * ey + qy) + g.NIY * (2 * ez + qz)), g.NIX, g.NIX * g.NIY, qx, qy,
+                 qz, G);
+      point_terms(kind, eps, G, vol * wlgl64(qx) * wlgl64(qy) * wlgl64(qz), &val, &coef);
+      acc += val;
+    }
+    return acc;
+  };
+  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, r, one) && threadIdx.x == 0) value[0] = r;
 }
 
 // M~ diagonal (C.1a): interior lumped mass of every closed-interior node.
