@@ -291,7 +291,13 @@ fwi_status fwi_check_model(fwi_plan* plan, void* stream, const double* rho,
 
 /* out[0] = sum_i a_i b_i w_i (w null: weights 1), device vectors of length n;
  * a fixed summation order that depends on n alone (deterministic).  Used for the norms
- * of (24) and the inner products of the line search (Algorithm 1). */
+ * of (24) and the inner products of the line search (Algorithm 1).
+ * Reductions of more than 2,048 entries (fwi_dot, fwi_absmax, fwi_mse, the value of
+ * fwi_regularization) run in up to 256 workgroups, which meet in one of 64 slots of
+ * a static device array (150 KB) that a stream holds until another stream needs it
+ * (that call waits for a copy of 256 bytes).  Under capture, on the per-thread
+ * default stream and while all slots are in use they run in one workgroup: the same
+ * bits, at the rate of one. */
 fwi_status fwi_dot(void* stream, int64_t n, const double* a, const double* b,
                    const double* w, double* out);
 

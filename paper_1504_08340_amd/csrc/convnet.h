@@ -743,7 +743,7 @@ __global__ void __launch_bounds__(RED_ONE) mse_kernel(long long n, const float* 
     });
     return acc;
   };
-  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, s, one) && threadIdx.x == 0 && loss)
+  if (reduce_parts<RedSum>(nb, slot, sh, s, one) && threadIdx.x == 0 && loss)
     loss[0] = (float)(0.5 * s / (double)n);
 }
 

@@ -1493,30 +1493,73 @@ hipError_t scratch_address(int device, void** out) {
 
 // ------------------------------------------------ reduction slots (reduce.h)
 namespace {
-// Slot of a stream's many-workgroup reductions, or -1 (the reduction then runs
-// in one workgroup, with the same bits): for a stream being captured, whose
-// graph may later run beside its own eager launches; for the per-thread default
-// stream, one handle for many streams; and once RED_SLOTS streams hold one.  A
-// slot stays with its stream's handle; on every device the same index names
-// that device's own array, so the null stream needs one entry.
+struct SlotTable {        // of one device
+  std::mutex mu;
+  struct {
+    hipStream_t st = nullptr;
+    bool held = false;
+    unsigned issued = 0;  // launches given this slot (red_done counts those that have left it)
+  } slot[RED_SLOTS];
+  int skip = 0;           // calls before the next look for slots to give back
+};
+
+// Gives back the slots in which no launch is under way.  The copy waits for no
+// stream's work, and is made so that it leaves another thread's capture alone.
+void give_slots_back(SlotTable& T) {
+  unsigned done[RED_SLOTS];
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
+  hipStream_t s = nullptr;
+  bool ok = hipStreamCreateWithFlags(&s, hipStreamNonBlocking) == hipSuccess;
+  ok = ok && hipMemcpyFromSymbolAsync(done, HIP_SYMBOL(red_done), sizeof(done), 0, hipMemcpyDeviceToHost, s) == hipSuccess;
+  ok = ok && hipStreamSynchronize(s) == hipSuccess;
+  if (s) (void)hipStreamDestroy(s);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!ok) (void)hipGetLastError();
+  for (int i = 0; ok && i < RED_SLOTS; ++i)
+    if (T.slot[i].issued == done[i]) T.slot[i].held = false;
+}
+
+// Slot of a stream's many-workgroup reduction, or -1 (it then runs in one
+// workgroup, with the same bits): for a stream being captured, whose graph may
+// later run beside its own eager launches; for the per-thread default stream, one
+// handle for many streams; and while launches are under way in all slots, each on
+// a stream of its own.  A stream keeps its slot until another one needs it; a new
+// stream with the handle of a destroyed one may take it over (hipStreamDestroy
+// returns when the stream's work has ended).
 int stream_slot(hipStream_t st) {
-  static std::mutex mu;
-  static hipStream_t held[RED_SLOTS];
-  static int n = 0;
+  static SlotTable tables[MAX_DEVICES];
   if (st == hipStreamPerThread) return -1;
   if (st == hipStreamLegacy) st = nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &cs) != hipSuccess) {
+  int device = 0;
+  if (hipStreamIsCapturing(st, &cs) != hipSuccess || hipGetDevice(&device) != hipSuccess) {
     (void)hipGetLastError();
     return -1;
   }
-  if (cs != hipStreamCaptureStatusNone) return -1;
-  std::lock_guard<std::mutex> lk(mu);
-  for (int i = 0; i < n; ++i)
-    if (held[i] == st) return i;
-  if (n == RED_SLOTS) return -1;
-  held[n] = st;
-  return n++;
+  if (cs != hipStreamCaptureStatusNone || device < 0 || device >= MAX_DEVICES) return -1;
+  SlotTable& T = tables[device];
+  std::lock_guard<std::mutex> lk(T.mu);
+  int open = -1;
+  auto look = [&] {
+    for (int i = 0; i < RED_SLOTS; ++i) {
+      if (T.slot[i].held && T.slot[i].st == st) return i;
+      if (!T.slot[i].held && open < 0) open = i;
+    }
+    return -1;
+  };
+  int i = look();
+  if (i < 0 && open < 0 && T.skip-- <= 0) {
+    give_slots_back(T);
+    look();
+    T.skip = open < 0 ? 3 : 0;   // a look takes about as long as a short reduction in one workgroup
+  }
+  if (i < 0) i = open;
+  if (i < 0) return -1;
+  T.slot[i].st = st;
+  T.slot[i].held = true;
+  ++T.slot[i].issued;
+  return i;
 }
 
 // Threads of a reduction's workgroups: its one workgroup takes more where it walks

@@ -11,8 +11,8 @@
 // the two trees); an L-BFGS iteration's optimizer work (60 of them) 7.15 -> 1.6 ms.
 //
 // Whether nb workgroups or one carry it out does not change a bit of the result.
-// A slot belongs to a stream, whose launches do not overlap; a launch that has
-// none (see stream_slot) takes one workgroup of 16 waves, a wave a part: it forms
+// A slot belongs to a stream, whose launches do not overlap, until another stream
+// needs it and all launches in it have ended; a launch that has none (see stream_slot) takes one workgroup of 16 waves, a wave a part: it forms
 // what the part's 256 threads would, four a lane, and joins them between its lanes,
 // so that no wave waits for another before the last tree.  Of 16 parts or fewer the
 // waves take quarters, and meet once more.
@@ -36,7 +36,7 @@ struct RedSlot {
 };
 
 static __device__ RedSlot red_slots[RED_SLOTS];   // counts start at 0
-__device__ __forceinline__ RedSlot* red_slot(int i) { return i < 0 ? nullptr : &red_slots[i]; }
+static __device__ unsigned red_done[RED_SLOTS];   // launches that have left their slot
 
 __host__ __device__ inline int red_parts(long long n) {
   const long long nb = (n + RED_PER_PART - 1) / RED_PER_PART;
@@ -140,7 +140,7 @@ __device__ __forceinline__ void red_quads(int part, int lane, int nb, long long 
 // neighbouring lanes are faster).
 struct RedNone {};
 template <typename Op, typename F, typename Q = RedNone>
-__device__ __forceinline__ bool reduce_parts(int nb, RedSlot* slot, double* sh, double& result, F&& f, Q&& quads = {}) {
+__device__ __forceinline__ bool reduce_parts(int nb, int slot, double* sh, double& result, F&& f, Q&& quads = {}) {
   constexpr bool QUADS = !std::is_same<std::decay_t<Q>, RedNone>::value;
   if (blockDim.x > RED_THREADS) {
     __shared__ double parts[RED_PARTS];
@@ -187,17 +187,21 @@ __device__ __forceinline__ bool reduce_parts(int nb, RedSlot* slot, double* sh, 
     return true;
   }
   __shared__ bool last;
+  RedSlot* const S = &red_slots[slot];
   if (threadIdx.x == 0) {
     // agent scope: the parts cross the caches of the XCDs
-    __hip_atomic_store(&slot->part[blockIdx.x], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last = __hip_atomic_fetch_add(&slot->count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nb - 1;
+    __hip_atomic_store(&S->part[blockIdx.x], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(&S->count, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)nb - 1;
   }
   __syncthreads();
   if (!last) return false;
-  result = red_tree<Op>((int)threadIdx.x < nb ? __hip_atomic_load(&slot->part[threadIdx.x], __ATOMIC_RELAXED,
+  result = red_tree<Op>((int)threadIdx.x < nb ? __hip_atomic_load(&S->part[threadIdx.x], __ATOMIC_RELAXED,
                                                                   __HIP_MEMORY_SCOPE_AGENT)
                                               : Op::init(), sh);
-  if (threadIdx.x == 0) __hip_atomic_store(&slot->count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(&S->count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(&red_done[slot], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  }
   return true;
 }
 
@@ -227,7 +231,7 @@ __global__ void __launch_bounds__(RED_ONE) dot_kernel(long long n, const double*
     if (w) red_quads(part, lane, nb, n, weighted, add);
     else red_quads(part, lane, nb, n, plain, add);
   };
-  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, r, one, quads) && threadIdx.x == 0) out[0] = r;
+  if (reduce_parts<RedSum>(nb, slot, sh, r, one, quads) && threadIdx.x == 0) out[0] = r;
 }
 
 // out[0] = max_i |x_i|
@@ -244,7 +248,7 @@ __global__ void __launch_bounds__(RED_ONE) absmax_kernel(long long n, const doub
   auto quads = [&](int part, int lane, double (&v)[4]) {
     red_quads(part, lane, nb, n, load, [&](int k, double e, long long) { v[k] = fmax(v[k], fabs(e)); });
   };
-  if (reduce_parts<RedMax>(nb, red_slot(slot), sh, r, one, quads) && threadIdx.x == 0) out[0] = r;
+  if (reduce_parts<RedMax>(nb, slot, sh, r, one, quads) && threadIdx.x == 0) out[0] = r;
 }
 
 }  // namespace pmlfwi

@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(RED_ONE) reg_value_kernel(Geo g, int kind, dou
     }
     return acc;
   };
-  if (reduce_parts<RedSum>(nb, red_slot(slot), sh, r, one) && threadIdx.x == 0) value[0] = r;
+  if (reduce_parts<RedSum>(nb, slot, sh, r, one) && threadIdx.x == 0) value[0] = r;
 }
 
 // M~ diagonal (C.1a): interior lumped mass of every closed-interior node.

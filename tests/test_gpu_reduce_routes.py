@@ -92,3 +92,44 @@ def test_one_workgroup_streams():
         torch.cuda.synchronize()
         best = min(best, (time.perf_counter() - t0) / 10)
     assert best < 0.6e-3
+
+
+def test_slots_are_given_back():
+    """A program that has used 150 streams gets its next reductions as fast as the first
+    (64 slots; one workgroup takes more than 50 times as long), and the same bits."""
+    torch = _torch()
+    import ctypes
+    from paper_1504_08340_amd import binding as B
+    n = 4_000_000
+    a = torch.randn(n, dtype=torch.float64, device="cuda")
+    o = torch.zeros(160, dtype=torch.float64, device="cuda")
+    streams = []
+    for _ in range(150):
+        s = ctypes.c_void_p()
+        assert B._lib.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0
+        streams.append(s.value)
+
+    def best(stream, k):
+        t = []
+        for _ in range(4):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            B.fwi_dot(stream, n, a, a, None, o[k:k + 1])
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - t0)
+        return min(t)
+
+    first = best(streams[0], 0)
+    for k, s in enumerate(streams):
+        B.fwi_dot(s, n, a, a, None, o[k:k + 1])
+    torch.cuda.synchronize()
+    late = [best(streams[k], k) for k in (149, 0, 70, 149)]
+    assert max(late) < 5 * first, (first, late)
+    # two at once on streams that share no slot now
+    for _ in range(20):
+        for k in range(60, 150):
+            B.fwi_dot(streams[k], n // 8, a, a, None, o[k:k + 1])
+        torch.cuda.synchronize()
+        assert bool((o[60:150] == o[60]).all())
+    for s in streams:
+        assert B._lib.hipStreamDestroy(ctypes.c_void_p(s)) == 0
