@@ -708,13 +708,14 @@ __global__ void gradient_reduce_kernel(Geo g, const double* __restrict__ gacc, P
 // brick), then one workgroup joins them into out (minima and maxima: any order
 // gives the same bits).  In one workgroup the check took 0.4 ms of every solve
 // at 138,000 material nodes; over CHECK_BLOCKS workgroups both launches take
-// about 15 us.
-constexpr int CHECK_BLOCKS = 256;
+// about 15 us.  Up to CHECK_ONE nodes one workgroup of CHECK_THREADS threads is as
+// quick as both (2,601 nodes: a check of 20.6 us, 22.3 with two launches).
+constexpr int CHECK_BLOCKS = 256, CHECK_ONE = 4096, CHECK_THREADS = 1024;
 constexpr int CHECK_PARTIALS = 2048;
 static_assert(5 * CHECK_BLOCKS <= CHECK_PARTIALS, "the partials fit the plan's buffer");
 
 __device__ __forceinline__ void check_tree(double v[5], double* __restrict__ out) {
-  __shared__ double red[5][256];
+  __shared__ double red[5][CHECK_THREADS];
   for (int k = 0; k < 5; ++k) red[k][threadIdx.x] = v[k];
   __syncthreads();
   for (int s = blockDim.x / 2; s > 0; s >>= 1) {
@@ -728,10 +729,10 @@ __device__ __forceinline__ void check_tree(double v[5], double* __restrict__ out
     for (int k = 0; k < 5; ++k) out[k] = red[k][0];
 }
 
-__global__ void __launch_bounds__(256) model_check_kernel(Geo g, const double* __restrict__ rho,
-                                                          const double* __restrict__ lam,
-                                                          const double* __restrict__ mu, double c_lam,
-                                                          double c_mu, double* __restrict__ partials) {
+__global__ void __launch_bounds__(CHECK_THREADS) model_check_kernel(Geo g, const double* __restrict__ rho,
+                                                                    const double* __restrict__ lam,
+                                                                    const double* __restrict__ mu, double c_lam,
+                                                                    double c_mu, double* __restrict__ partials) {
   double v[5] = {1e300, 1e300, 1e300, 0.0, 0.0};
   const int first = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
   for (int j = first; j < g.n_int; j += step) {
@@ -1406,8 +1407,8 @@ fwi_status dispatch(fwi_plan* p, hipStream_t st, void* ws, F&& f, bool keep = tr
 
 fwi_status check_model(fwi_plan* p, hipStream_t st, const double* rho, const double* lam, const double* mu,
                        double* info, const char* who, void* ws = nullptr, bool keep = true) {
-  const int nb = std::min((int)blocks(p->g.n_int, 256), CHECK_BLOCKS);
-  model_check_kernel<<<nb, 256, 0, st>>>(p->g, rho, lam, mu, p->c_lam, p->c_mu, nb == 1 ? p->d_info : p->d_check);
+  const int nb = p->g.n_int <= CHECK_ONE ? 1 : std::min((int)blocks(p->g.n_int, 256), CHECK_BLOCKS);
+  model_check_kernel<<<nb, nb == 1 ? CHECK_THREADS : 256, 0, st>>>(p->g, rho, lam, mu, p->c_lam, p->c_mu, nb == 1 ? p->d_info : p->d_check);
   if (nb > 1) model_check_final_kernel<<<1, 256, 0, st>>>(p->d_check, nb, p->d_info);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(p->h_info, p->d_info, 5 * sizeof(double), hipMemcpyDeviceToHost, st);
