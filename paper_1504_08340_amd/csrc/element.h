@@ -880,7 +880,7 @@ __device__ __forceinline__ void interior_grad_part(const Geo& g, const ElementAr
 
 // Traces of a step: tr (source, step) at receiver r from the displacements U.
 template <typename R>
-__device__ __forceinline__ void record_traces(const R* U, int sn, const int* rec, int nrec, int r, double* tr) {
+__device__ __forceinline__ void record_traces(const R* U, int sn, const int* rec, int r, double* tr) {
   const int node = rec[r];
   for (int d = 0; d < 3; ++d) tr[3 * (size_t)r + d] = (double)U[u_at(sn, d, node)];
 }
@@ -912,7 +912,7 @@ element_kernel(Geo g, ElementArgs<R> A) {
       b -= (int)A.brec;
       const int src = b / A.grec, r = (b - src * A.grec) * D::THREADS + threadIdx.x;
       if (r < A.nrec)
-        record_traces<R>(A.Y + (size_t)src * A.ystride, g.sn, A.rec, A.nrec, r,
+        record_traces<R>(A.Y + (size_t)src * A.ystride, g.sn, A.rec, r,
                          A.traces + ((size_t)src * (A.nsteps + 1) + A.step) * A.nrec * 3);
       return;
     }

@@ -327,8 +327,8 @@ struct NodalArgs {
   long long store_stride;     // interior closure (per source stride), or nullptr
   R* pstore;                  // PML displacement fields of the produced register
   long long pstore_stride;    // [x1 u | x2 u | x0 u] x sp per source, or nullptr
-  long long first, last;      // row range of this launch: [0, sn) node rows, then PML rows
-  unsigned rot, nblocks;      // workgroup b takes rows of block (b + rot) mod nblocks, the grid
+  long long rows;             // rows of this launch: [0, sn) node rows, then PML rows
+  unsigned rot;               // workgroup b takes rows of block (b + rot) mod the grid
 };
 
 // Where a node's contributions sit in the partial arrays: array 0 always, and
@@ -405,9 +405,9 @@ __device__ __forceinline__ void gather_rows(const Part& P, const PartSlots& S, c
 template <typename R, int MODE, int STORE>
 __global__ void __launch_bounds__(PMLFWI_NODAL_THREADS) nodal_rk_kernel(Geo g, NodalArgs<R> A) {
   const int src = blockIdx.y;
-  const unsigned turned = blockIdx.x + A.rot, blk = turned < A.nblocks ? turned : turned - A.nblocks;
-  const long long gid = A.first + (long long)blk * blockDim.x + threadIdx.x;
-  if (gid >= A.last) return;
+  const unsigned turned = blockIdx.x + A.rot, blk = turned < gridDim.x ? turned : turned - gridDim.x;
+  const long long gid = (long long)blk * blockDim.x + threadIdx.x;
+  if (gid >= A.rows) return;
   const size_t nn = (size_t)g.sn, np = (size_t)g.sp;
   const size_t so = (size_t)src * A.reg;
   const R* Y = A.Yin + so;

@@ -518,7 +518,7 @@ __global__ void receivers_kernel(const R* __restrict__ X, long long reg, int sn,
                                  int step, int nsteps) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x, src = blockIdx.y;
   if (r >= nrec) return;
-  record_traces<R>(X + (size_t)src * reg, sn, rec, nrec, r, traces + ((size_t)src * (nsteps + 1) + step) * nrec * 3);
+  record_traces<R>(X + (size_t)src * reg, sn, rec, r, traces + ((size_t)src * (nsteps + 1) + step) * nrec * 3);
 }
 
 // Adjoint impulse after a reverse step: y2_u += M^{-1} dt w_n (u^n - u_m^n) at receivers.
@@ -1137,10 +1137,8 @@ struct Run {
       constexpr int NT = PMLFWI_NODAL_THREADS;
       // the (heavier) PML-row blocks are dispatched first
       const unsigned nb = (unsigned)blocks((size_t)rows, NT);
-      A.first = 0;
-      A.last = rows;
+      A.rows = rows;
       A.rot = (unsigned)(G.sn / NT) % nb;
-      A.nblocks = nb;
       kern<<<dim3(nb, p->nsrc), NT, 0, st>>>(G, A);
     }
     if (wav && p->nload > 0) {
