@@ -24,7 +24,8 @@ struct ConvShape {
 
 __host__ __device__ inline int conv_out(int n, int K, int s) { return (n + 2 * (K / 2) - K) / s + 1; }
 
-// x / d for 0 <= x < 2^31 and a divisor known to the host.
+// x / d for 0 <= x < 2^31 and a divisor known to the host: the round-up
+// multiplier of Granlund and Montgomery (1994).
 struct FastDiv {
   unsigned m, s;
 };

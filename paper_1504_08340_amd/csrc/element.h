@@ -11,8 +11,9 @@
 //   u-rows     from the stresses
 // The parts write disjoint rows, so they need no order among them.
 //
-// What bounds it and why it is split this way.  All parts move 148 MB a stage
-// (62,500 bricks, 4 sources, FP32), 29 us at the rate of a 1 GiB copy; with a
+// What bounds it and why it is split this way.  All parts together need
+// 148 MB a stage (62,500 bricks, 4 sources, FP32) and move 209 MB (counters; the
+// tiles' halo planes and upper faces), 33 us at the 6.3 TB/s of a 1 GiB copy; with a
 // thread per point the launches were bound by VALU issue (75 us of it a
 // stage, two thirds of that index arithmetic, coefficient selects and
 // divergent gathers), so here

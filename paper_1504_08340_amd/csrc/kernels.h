@@ -301,12 +301,16 @@ __device__ __forceinline__ void pml_node_setup(const Geo& g, int gi, int gj, int
 //                x0, x1 rows: K_s is the x1, x2 row of Y_s, so they sum rates;
 //                x2 rows:     h/2 K1 = Y2 - Xn, h/2 K2 = Y3 - Xn, h K3 = Y4 - Xn
 //                (differences of near values, exact or nearly so), K4 at hand.
-// Bound by HBM.  Kept registers cost less than an accumulator: per step an x1
-// row is read and written 8 times and an x2 row 13 times, against 16 times each
-// with acc += c K in every stage, and Xn takes one rounding of the sum instead
-// of one per stage.  Measured (62,500 bricks, 4 sources, mean per stage): FP32
-// 99 -> 76 us, FP64 232 -> 174 us; error of FP32 traces after 400 steps of 864
-// bricks against FP64 4.0e-7 -> 2.1e-7.
+// Bound by HBM: FP32 moves its counted bytes at 5.1-5.5 TB/s, FP64 at 4.6-4.9,
+// where a plain stream of 3 reads and 2 writes of the same sizes reaches 6.4.
+// Kept registers cost less than an accumulator: per step an x1 row is read and
+// written 8 times and an x2 row 13 times, against 16 times each with acc += c K
+// in every stage.  The x0 S and x1 rows take one rounding of the sum instead of
+// one per stage; the x2 rows, and the stage 1 term of the x0 u rows, carry the
+// roundings of the stages' registers as an accumulator would.  Measured (62,500
+// bricks, 4 sources, mean per stage): FP32 99 -> 76 us, FP64 232 -> 174 us;
+// error of FP32 traces after 400 steps of 864 bricks against FP64 4.0e-7 ->
+// 2.1e-7.
 template <typename R>
 struct NodalArgs {
   const R* Yin;

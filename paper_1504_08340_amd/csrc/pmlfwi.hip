@@ -1390,7 +1390,7 @@ struct Run {
   }
 };
 
-// Model check before a solve: one small kernel, a copy of 5 doubles and a
+// Model check before a solve: one or two small kernels, a copy of 5 doubles and a
 // stream synchronization.  info: 6 host doubles (see fwi_check_model).
 // With a workspace, a time step above the brick-by-brick bound is checked
 // again against a power-iteration estimate of the largest frequency of the

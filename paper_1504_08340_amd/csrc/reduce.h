@@ -12,10 +12,11 @@
 //
 // Whether nb workgroups or one carry it out does not change a bit of the result.
 // A slot belongs to a stream, whose launches do not overlap, until another stream
-// needs it and all launches in it have ended; a launch that has none (see stream_slot) takes one workgroup of 16 waves, a wave a part: it forms
-// what the part's 256 threads would, four a lane, and joins them between its lanes,
-// so that no wave waits for another before the last tree.  Of 16 parts or fewer the
-// waves take quarters, and meet once more.
+// needs it and all launches in it have ended; a launch that has none (see
+// stream_slot) takes one workgroup of 16 waves, a wave a part: it forms what the
+// part's 256 threads would, four a lane, and joins them between its lanes, so that
+// no wave waits for another before the last tree.  Of 16 parts or fewer the waves
+// take quarters, and meet once more.
 #pragma once
 #include <hip/hip_runtime.h>
 
