@@ -18,8 +18,8 @@ Usage: python bench.py [--steps K] [--warmup W]
 --copy-probe-mib runs one plain element-wise copy of that size after the timed
 region; hardware-counter runs use it to scale FETCH_SIZE / WRITE_SIZE.  The
 roofline ``traffic`` field is read from the counter summary committed under
-profiles/ and reported only while the kernel sources hash to the value
-recorded there.
+profiles/ and reported only while the sources of the counted kernels hash to
+the value recorded there.
 """
 from __future__ import annotations
 
@@ -57,13 +57,15 @@ def useful_flops_per_tile(ne):
 
 
 CSRC = os.path.join(ROOT, "paper_1504_08340_amd", "csrc")
+# what the counted kernels are compiled from (their code, tiles and layouts)
+TRAFFIC_SOURCES = ("element.h", "geometry.h", "kernels.h")
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "hbm_traffic__kernels__cfg40x40x20_4src_fp32.md")
 
 
 def kernel_source_hash():
-    """sha256 over the HIP sources, in name order."""
+    """sha256 over the sources of the counted kernels, in name order."""
     h = hashlib.sha256()
-    for name in sorted(os.listdir(CSRC)):
+    for name in TRAFFIC_SOURCES:
         with open(os.path.join(CSRC, name), "rb") as f:
             h.update(name.encode() + b"\0" + f.read())
     return h.hexdigest()
@@ -74,7 +76,7 @@ def recorded_traffic(cls, precision):
 
     The summary holds lines ``traffic <class> <precision> <bytes>`` and one
     ``source_sha256 <hex>`` line; None when the file is absent, the class is not
-    listed, or the sources changed since the counters were taken.
+    listed, or those sources changed since the counters were taken.
     """
     try:
         with open(TRAFFIC_SUMMARY) as f:

@@ -27,6 +27,13 @@
 #pragma once
 #include "geometry.h"
 
+// Element tiles (bricks per axis).  5x4x2 cuts the 5-brick PML and the
+// 40x40x20-brick interior without ragged tiles along x and y.
+#ifndef PMLFWI_TX
+#define PMLFWI_TX 5
+#define PMLFWI_TY 4
+#define PMLFWI_TZ 2
+#endif
 // Threads that hold one node each of a tile's node box: 512 fits the
 // 11 x 9 x 5 node box of a 5x4x2 tile.
 #ifndef PMLFWI_ETHREADS

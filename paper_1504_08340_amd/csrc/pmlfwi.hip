@@ -225,13 +225,6 @@ struct TimedLaunch {
 
 namespace {
 
-// Element tiles (bricks per axis).  5x4x2 cuts the 5-brick PML and the
-// 40x40x20-brick interior without ragged tiles along x and y.
-#ifndef PMLFWI_TX
-#define PMLFWI_TX 5
-#define PMLFWI_TY 4
-#define PMLFWI_TZ 2
-#endif
 constexpr int TX = PMLFWI_TX, TY = PMLFWI_TY, TZ = PMLFWI_TZ;
 // Threads that hold one box node each (the FP32 matrix-core workgroups); the
 // scalar element launch keeps a column of box nodes per thread (TileDims).

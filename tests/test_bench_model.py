@@ -8,6 +8,8 @@ adjoint pass over n_X register values costs 2 x 16 n_X values.  The nodal
 launch, averaged over the four stage modes, moves 4 register values per
 register entry (3 besides the stage input).  These cases isolate each term.
 """
+import os
+import shutil
 import types
 
 import pytest
@@ -52,3 +54,21 @@ def test_nodal_bytes_per_free_node():
     for es, nsrc in ((4, 1), (4, 3), (8, 2)):
         d = bench.algorithmic_bytes("nodal", s1, prob, nsrc, es) - bench.algorithmic_bytes("nodal", s0, prob, nsrc, es)
         assert d == pytest.approx(es * nsrc * (4 * 6 + 3) + es, rel=1e-12)
+
+
+def test_counter_hash_follows_the_counted_kernels(tmp_path, monkeypatch):
+    """Recorded counters hold as long as the sources of their kernels do, and
+    an edit of another kernel's source does not touch them."""
+    for name in os.listdir(bench.CSRC):
+        shutil.copy(os.path.join(bench.CSRC, name), tmp_path / name)
+    was = bench.kernel_source_hash()
+    monkeypatch.setattr(bench, "CSRC", str(tmp_path))
+    assert bench.kernel_source_hash() == was
+    for name in ("convnet.h", "reduce.h", "regularize.h"):
+        (tmp_path / name).write_bytes(b"// edited\n" + (tmp_path / name).read_bytes())
+    assert bench.kernel_source_hash() == was
+    for name in ("element.h", "geometry.h", "kernels.h"):
+        kept = (tmp_path / name).read_bytes()
+        (tmp_path / name).write_bytes(b"// edited\n" + kept)
+        assert bench.kernel_source_hash() != was, name
+        (tmp_path / name).write_bytes(kept)
