@@ -132,8 +132,8 @@ __device__ __forceinline__ float conv_one(const ConvShape& c, const float* __res
 // with zero for these, which an infinite or undefined weight turns into NaN: a wave
 // with a result that is not finite forms its results again, each from the taps it has.
 // 16 rows where 32 would leave less than one wave a SIMD.  Of the network's
-// training step at batch 8 the five forward launches take 0.33 ms (2.0 ms with a
-// thread per output) and the four data gradients 0.41 ms (4.9 ms); the chain of
+// training step at batch 8 the five forward launches take 0.34 ms (2.0 ms with a
+// thread per output) and the four data gradients 0.35 ms (4.9 ms); the chain of
 // 64-cycle products alone is 0.08 ms a pass.
 constexpr int CONV_STAGE = 8;   // channels staged together
 
@@ -324,7 +324,7 @@ __global__ void __launch_bounds__(CONV_THREADS) conv3d_direct_kernel(ConvArgs A)
 // Bound by the loads: an operand serves 4 T rows, and channels a power of two apart
 // fall on the same channel of the L2 (products alone: 12 us of 109 at 32 x 32
 // channels and 8 x 16 x 16 x 16 outputs).  The network's training step at batch 8
-// takes 0.63 ms here; one workgroup per weight walking all outputs, in the same
+// takes 0.65 ms here; one workgroup per weight walking all outputs, in the same
 // order, took 12.9 ms.  16 x 16 channels and all chains of one tap in a workgroup of
 // 16 waves, operands shared through LDS: 98 us, but 497 us where 9 x 32 channels
 // leave 54 workgroups (here 240).
