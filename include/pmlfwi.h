@@ -337,7 +337,7 @@ fwi_status fwi_conv3d_backward(void* stream, const fwi_conv_shape* shape, const 
  * and w [Co][Ci][K][K][K] in BF16, as an implicit GEMM on BF16 MFMA with FP32
  * accumulation; bias (FP32) and ReLU in FP32; y is BF16 (out_fp32 = 0, hidden
  * layers) or FP32 (out_fp32 = 1, the head).  Same shapes as
- * fwi_conv3d_forward; N <= 65535. */
+ * fwi_conv3d_forward; N <= 65535, Do Ho Wo <= 2^32 - 256. */
 fwi_status fwi_to_bf16(void* stream, int64_t n, const float* in, uint16_t* out);
 fwi_status fwi_conv3d_forward_bf16(void* stream, const fwi_conv_shape* shape, const uint16_t* x,
                                    const uint16_t* w, const float* b, int relu, int out_fp32, void* y);

@@ -46,6 +46,10 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 constexpr int CONV_THREADS = 256;   // 4 waves
 
+// Most workgroups of a launch: the threads of an axis are counted in 32 bits, and of
+// more only what is left past a multiple of 2^32 runs, without an error.
+constexpr long long CONV_GRID = (1LL << 32) / CONV_THREADS - 1;
+
 // g = dL/d(pre-activation) from dL/dy and, with ReLU, the activated output y.
 __device__ __forceinline__ float pre_grad(const float* dy, const float* y, int relu, long long i) {
   return (relu && !(y[i] > 0.0f)) ? 0.0f : dy[i];
@@ -141,7 +145,7 @@ struct ConvArgs {
   ConvShape c;
   const float *src, *act, *w, *b;   // act: activated outputs (data gradient with ReLU); b: bias or null
   float* out;
-  int relu, ptiles;                 // ptiles: tiles of 64 positions a sample
+  int relu, ptiles, first;          // ptiles: tiles of 64 positions a sample; first: tile of this launch
 };
 
 // A wave's results one by one: a lane those of its position.
@@ -150,7 +154,7 @@ __device__ __forceinline__ void conv_wave(const ConvArgs& A) {
   const ConvShape& c = A.c;
   const int M = DATA ? c.Ci : c.Co, PD = DATA ? c.D : c.Do, PH = DATA ? c.H : c.Ho, PW = DATA ? c.W : c.Wo;
   const long long P = (long long)PD * PH * PW;
-  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), n = tile / A.ptiles;
+  const int tile = A.first + blockIdx.x * 4 + (threadIdx.x >> 6), n = tile / A.ptiles;
   const long long p = (tile - n * A.ptiles) * 64LL + (threadIdx.x & 63);
   if (n >= c.N || p >= P) return;
   int pd, ph, pw;
@@ -181,7 +185,7 @@ __global__ void __launch_bounds__(CONV_THREADS, (DATA ? 2 : 3)) conv3d_f32_kerne
   const long long P = (long long)PD * PH * PW;   // may pass 2^31
   const size_t svol = (size_t)SD * SH * SW;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int tile = blockIdx.x * 4 + wave;          // over the batch's position tiles
+  const int tile = A.first + blockIdx.x * 4 + wave;   // over the batch's position tiles
   const int n = min(tile / ptiles, c.N - 1);
   const long long p = tile < c.N * ptiles ? (tile - n * ptiles) * 64LL + lane : P;
   const int row0 = blockIdx.y * R;
@@ -559,16 +563,16 @@ __global__ void to_bf16_kernel(long long n, const float* __restrict__ in, unsign
 // arithmetic, 1.4 us a step of 16 k's and 16 rows where the positions are few.
 __global__ void __launch_bounds__(CONV_THREADS)
 conv3d_bf16_narrow_kernel(ConvShape c, const unsigned short* __restrict__ x, const unsigned short* __restrict__ w,
-                          const float* __restrict__ b, int relu, int out_fp32, void* __restrict__ y) {
-  const int P = c.Do * c.Ho * c.Wo;
+                          const float* __restrict__ b, int relu, int out_fp32, unsigned first, void* __restrict__ y) {
+  const unsigned P = (unsigned)c.Do * c.Ho * c.Wo;   // below 2^32
   const int KK = c.K * c.K * c.K, Kdim = c.Ci * KK, pad = c.K / 2;
   const int n = blockIdx.y;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i = lane & 15, g = lane >> 4;
-  const int col0 = blockIdx.x * 64 + wave * 16;
-  const int p = col0 + i;                        // this lane's output position (B column)
+  const unsigned p = (first + blockIdx.x) * 64 + wave * 16 + i;   // this lane's output position (B column)
   const bool pin = p < P;
-  const int ow = pin ? p % c.Wo : 0, oh = pin ? (p / c.Wo) % c.Ho : 0, od = pin ? p / (c.Wo * c.Ho) : 0;
+  const unsigned pr = pin ? p / c.Wo : 0;
+  const int ow = pin ? p % c.Wo : 0, oh = pr % c.Ho, od = pr / c.Ho;
   const unsigned short* xn = x + (size_t)n * c.Ci * c.D * c.H * c.W;
   const int nrt = (c.Co + 15) / 16;
   for (int rt = 0; rt < nrt; ++rt) {
@@ -592,7 +596,7 @@ conv3d_bf16_narrow_kernel(ConvShape c, const unsigned short* __restrict__ x, con
       }
       acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, bb, acc, 0, 0, 0);
     }
-    // lane holds C[rt*16 + 4 g + r][col0 + i], r = 0..3
+    // lane holds C[rt*16 + 4 g + r][p], r = 0..3
     if (pin) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -623,7 +627,7 @@ typedef unsigned short v8us __attribute__((ext_vector_type(8)));
 template <int K>
 __global__ void __launch_bounds__(CONV_THREADS)
 conv3d_bf16_mfma_kernel(ConvShape c, const unsigned short* __restrict__ x, const unsigned short* __restrict__ w,
-                        const float* __restrict__ b, int relu, int out_fp32, int wvec, void* __restrict__ y) {
+                        const float* __restrict__ b, int relu, int out_fp32, int wvec, unsigned first, void* __restrict__ y) {
   constexpr int T3 = K * K * K, ROWS = 32, LC = 40;   // LDS row of 32 channels, padded to spread the banks
   // K = 1: one step a channel group, so the waves take 32 positions each instead
   // (24 x 18 x 26 x 32 to 7 channels: 7.9 us a call sharing them, 7.6 us)
@@ -631,12 +635,13 @@ conv3d_bf16_mfma_kernel(ConvShape c, const unsigned short* __restrict__ x, const
   constexpr int WS = OWN ? 1 : 4;                     // distance of a wave's steps
   constexpr int NA = T3 * ROWS * LC, NS = 2 * 4 * 16 * 64;
   __shared__ __align__(16) unsigned short sA[NA > NS ? NA : NS];
-  const int P = c.Do * c.Ho * c.Wo;
+  const unsigned P = (unsigned)c.Do * c.Ho * c.Wo;   // below 2^32
   const size_t vol = (size_t)c.D * c.H * c.W;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, col = lane & 31, h = lane >> 5;
-  const int n = blockIdx.y, p = (OWN ? blockIdx.x * 4 + wave : blockIdx.x) * 32 + col, row0 = blockIdx.z * ROWS;
-  const int pq = min(p, P - 1), pr = pq / c.Wo;
-  const int d0 = (pr / c.Ho) * c.sd - K / 2, h0 = (pr % c.Ho) * c.sh - K / 2, w0 = (pq % c.Wo) * c.sw - K / 2;
+  const int n = blockIdx.y, row0 = blockIdx.z * ROWS;
+  const unsigned p = (OWN ? (first + blockIdx.x) * 4 + wave : first + blockIdx.x) * 32 + col;
+  const unsigned pq = min(p, P - 1), pr = pq / c.Wo;
+  const int d0 = (int)(pr / c.Ho) * c.sd - K / 2, h0 = (int)(pr % c.Ho) * c.sh - K / 2, w0 = (int)(pq % c.Wo) * c.sw - K / 2;
   v16f acc = {};
   for (int c0 = 0; c0 < c.Ci; c0 += 32) {
     const int cn = min(32, c.Ci - c0), groups = (cn + 15) / 16, rows = min(ROWS, c.Co - row0);

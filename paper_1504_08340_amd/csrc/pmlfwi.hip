@@ -2051,16 +2051,18 @@ static void launch_conv(const ConvShape& c, const float* src, const float* act, 
   const int M = DATA ? c.Ci : c.Co, ptiles = (int)((P + 63) / 64);
   const long long tiles = (long long)ptiles * c.N;
   const int big = M > 16 && tiles * ((M + 31) / 32) >= 1024, R = big ? 32 : 16;
-  const dim3 grid((unsigned)((tiles + 3) / 4), (unsigned)((M + R - 1) / R));
-  if (conv_one_by_one(c, DATA)) {
-    conv3d_direct_kernel<DATA><<<(unsigned)(((long long)c.N * M * P + CONV_THREADS - 1) / CONV_THREADS), CONV_THREADS, 0, st>>>(
-        ConvArgs{c, src, act, w, b, out, relu, ptiles});
+  const long long each = ((long long)c.N * M * P + CONV_THREADS - 1) / CONV_THREADS;
+  if (each <= CONV_GRID && conv_one_by_one(c, DATA)) {
+    conv3d_direct_kernel<DATA><<<(unsigned)each, CONV_THREADS, 0, st>>>(ConvArgs{c, src, act, w, b, out, relu, ptiles, 0});
     return;
   }
   using CK = void (*)(ConvArgs);
   static const CK table[2][2] = {{conv3d_f32_kernel<1, DATA, 16>, conv3d_f32_kernel<1, DATA, 32>},
                                  {conv3d_f32_kernel<3, DATA, 16>, conv3d_f32_kernel<3, DATA, 32>}};
-  table[c.K == 3][big]<<<grid, CONV_THREADS, 0, st>>>(ConvArgs{c, src, act, w, b, out, relu, ptiles});
+  for (long long first = 0; first < tiles; first += 4 * CONV_GRID) {
+    const dim3 grid((unsigned)((std::min(tiles - first, 4 * CONV_GRID) + 3) / 4), (unsigned)((M + R - 1) / R));
+    table[c.K == 3][big]<<<grid, CONV_THREADS, 0, st>>>(ConvArgs{c, src, act, w, b, out, relu, ptiles, (int)first});
+  }
 }
 
 // Whether the kernel for few input channels is the faster one, from what both take,
@@ -2119,17 +2121,20 @@ fwi_status fwi_conv3d_forward_bf16(void* stream, const fwi_conv_shape* shape, co
   ConvShape c;
   if (!conv_shape(shape, c) || !x || !w || !y) return FWI_ERR_ARG;
   const long long P = (long long)c.Do * c.Ho * c.Wo;
-  if (c.N > 65535) return FWI_ERR_ARG;
-  if (bf16_narrow(c)) {
-    conv3d_bf16_narrow_kernel<<<dim3((unsigned)((P + 63) / 64), (unsigned)c.N), CONV_THREADS, 0, (hipStream_t)stream>>>(
-        c, (const unsigned short*)x, (const unsigned short*)w, b, relu, out_fp32, y);
-    return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
+  if (c.N > 65535 || P > (1LL << 32) - 256) return FWI_ERR_ARG;
+  const bool narrow = bf16_narrow(c);
+  const int span = narrow ? 64 : (c.K == 3 ? 32 : 128);   // positions a workgroup
+  const long long all = (P + span - 1) / span;
+  for (long long first = 0; first < all; first += CONV_GRID) {
+    const dim3 grid((unsigned)std::min(all - first, CONV_GRID), (unsigned)c.N, narrow ? 1 : (unsigned)((c.Co + 31) / 32));
+    if (narrow)
+      conv3d_bf16_narrow_kernel<<<grid, CONV_THREADS, 0, (hipStream_t)stream>>>(
+          c, (const unsigned short*)x, (const unsigned short*)w, b, relu, out_fp32, (unsigned)first, y);
+    else
+      (c.K == 3 ? conv3d_bf16_mfma_kernel<3> : conv3d_bf16_mfma_kernel<1>)<<<grid, CONV_THREADS, 0, (hipStream_t)stream>>>(
+          c, (const unsigned short*)x, (const unsigned short*)w, b, relu, out_fp32,
+          c.Ci % 8 == 0 && ((uintptr_t)w & 15) == 0, (unsigned)first, y);   // rows of weights start on 16 bytes
   }
-  const int span = c.K == 3 ? 32 : 128;   // positions a workgroup
-  const dim3 grid((unsigned)((P + span - 1) / span), (unsigned)c.N, (unsigned)((c.Co + 31) / 32));
-  (c.K == 3 ? conv3d_bf16_mfma_kernel<3> : conv3d_bf16_mfma_kernel<1>)<<<grid, CONV_THREADS, 0, (hipStream_t)stream>>>(
-      c, (const unsigned short*)x, (const unsigned short*)w, b, relu, out_fp32,
-      c.Ci % 8 == 0 && ((uintptr_t)w & 15) == 0, y);   // rows of weights start on 16 bytes
   return hipGetLastError() == hipSuccess ? FWI_OK : FWI_ERR_HIP;
 }
 
