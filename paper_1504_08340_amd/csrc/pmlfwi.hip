@@ -702,7 +702,8 @@ __global__ void gradient_reduce_kernel(Geo g, const double* __restrict__ gacc, P
 // gives the same bits).  In one workgroup the check took 0.4 ms of every solve
 // at 138,000 material nodes; over CHECK_BLOCKS workgroups both launches take
 // about 15 us.  Up to CHECK_ONE nodes one workgroup of CHECK_THREADS threads is as
-// quick as both (2,601 nodes: a check of 20.6 us, 22.3 with two launches).
+// quick as both (2,601 nodes: a check of 20.6 us, 22.3 with two launches); of 256 nodes
+// or fewer, 256 threads are enough (125 nodes: 21.5 us, 22.0 with 1,024).
 constexpr int CHECK_BLOCKS = 256, CHECK_ONE = 4096, CHECK_THREADS = 1024;
 constexpr int CHECK_PARTIALS = 2048;
 static_assert(5 * CHECK_BLOCKS <= CHECK_PARTIALS, "the partials fit the plan's buffer");
@@ -1399,7 +1400,8 @@ fwi_status dispatch(fwi_plan* p, hipStream_t st, void* ws, F&& f, bool keep = tr
 fwi_status check_model(fwi_plan* p, hipStream_t st, const double* rho, const double* lam, const double* mu,
                        double* info, const char* who, void* ws = nullptr, bool keep = true) {
   const int nb = p->g.n_int <= CHECK_ONE ? 1 : std::min((int)blocks(p->g.n_int, 256), CHECK_BLOCKS);
-  model_check_kernel<<<nb, nb == 1 ? CHECK_THREADS : 256, 0, st>>>(p->g, rho, lam, mu, p->c_lam, p->c_mu, nb == 1 ? p->d_info : p->d_check);
+  const int threads = nb == 1 && p->g.n_int > 256 ? CHECK_THREADS : 256;
+  model_check_kernel<<<nb, threads, 0, st>>>(p->g, rho, lam, mu, p->c_lam, p->c_mu, nb == 1 ? p->d_info : p->d_check);
   if (nb > 1) model_check_final_kernel<<<1, 256, 0, st>>>(p->d_check, nb, p->d_info);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpyAsync(p->h_info, p->d_info, 5 * sizeof(double), hipMemcpyDeviceToHost, st);
